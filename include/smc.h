@@ -220,9 +220,10 @@ smc_status smc_set_frames(smc_ctx *ctx, uint32_t n_extra, const smc_volume *src_
  * prepared on the stream.  particles_per_group: particles sharing one pass
  * over a target column, 4, 8 or 16.  tile_depth: target
  * slices per tile, 1 .. 256 (a tile is 32 x 8 x tile_depth voxels; shallower
- * tiles cull more exactly -- a tile whose image cannot reach the source, or
- * in the filter the source mask's bounding box or any occupied 2^3-voxel
- * cell of the source mask, is skipped -- at the cost of more partial sums).  A negative value keeps the current setting.  Defaults
+ * tiles cull more exactly -- a tile whose image cannot reach the source is
+ * skipped -- at the cost of more partial sums).  The filter's mask launches
+ * use neither (they decide blocks of the target by the source's distance
+ * field); smc_evaluate on masks does.  A negative value keeps the current setting.  Defaults
  * come from measurements on MI355X: 4 particles per group; tile depth 16 for
  * masks and 256 for images.  A packed layout addresses its source
  * with 32-bit offsets: SMC_EINVAL if the packed source reaches 4 GiB or one
@@ -264,17 +265,16 @@ smc_status smc_profile(smc_ctx *ctx, int32_t enable);
 smc_status smc_profile_read(smc_ctx *ctx, double *score_ms, uint64_t *score_launches, double *filter_ms,
                             uint64_t *filter_launches);
 
-/* Work of the filter's culled mask launches (masks, Methods: the Dice
- * evaluation; image contexts report 0).  Tile culling skips a particle for a
- * target tile, and a tile's runs of four slices at its bottom and top for all
- * its particles, when no sample there can read an "on" source voxel: the
- * image's box misses the source mask's bounding box or covers only
- * unoccupied 2^3-voxel cells.  Returns, since the previous call (or
- * smc_init), the particle x voxel pairs those launches evaluated, the pairs
- * they covered (the skipped ones included) and, of the evaluated ones, those
- * of tiles whose every sample the cull bound places inside the source (scored
- * without the per-sample inside test), and clears all three.  Syncs the
- * context's stream.  Outputs may be NULL. */
+/* Work of the filter's mask launches (masks, Methods: the Dice evaluation;
+ * image contexts report 0).  A block of the target whose every sample reads
+ * the same value -- by the distance from the image of its centre to the
+ * nearest source voxel of the other state -- is counted whole; the others are
+ * split down to 4^3 voxels and sampled.  Returns, since the previous call (or
+ * smc_init), the particle x voxel pairs those launches evaluated (sampled),
+ * the pairs they covered (the ones counted whole included) and, of the
+ * evaluated ones, those of 32 x 16 x 16 tiles whose image's bounding box lies
+ * inside the source (sampled without the per-sample inside test), and clears
+ * all three.  Syncs the context's stream.  Outputs may be NULL. */
 smc_status smc_profile_work(smc_ctx *ctx, uint64_t *evaluated, uint64_t *covered, uint64_t *interior);
 
 /* Free everything the context owns (after syncing its stream).  NULL is a no-op. */

@@ -447,8 +447,8 @@ class Registration:
         return smc_profile_read(self.ctx)
 
     def profile_work(self):
-        """Particle x voxel pairs the culled mask launches evaluated, covered
-        and evaluated on interior tiles since the previous call."""
+        """Particle x voxel pairs the filter's mask launches sampled, covered
+        and sampled on interior tiles since the previous call."""
         return smc_profile_work(self.ctx)
 
     def gather_probe(self, reps=1):

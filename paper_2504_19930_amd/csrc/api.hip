@@ -29,8 +29,8 @@ thread_local std::string g_err;
 // (measured on MI355X: packed octets, 4 particles per workgroup; see smc_autotune)
 constexpr int kDefaultLayout = kLayoutLerp;
 constexpr int kDefaultPT = 4;
-// default tile depths, from measurements on MI355X: masks 16 (culling against
-// the source mask's bounding box pays at shallow tiles), images 256
+// default tile depths, from measurements on MI355X: masks 16 (smc_evaluate;
+// the filter's mask launches have no tiles), images 256
 constexpr int kDefaultZChunkMask = 16, kDefaultZChunkImage = 256;
 
 smc_status fail(smc_status st, const char *fmt, ...) {
@@ -157,11 +157,9 @@ struct smc_ctx {
     int32_t sn[3] = {0, 0, 0}, tn[3] = {0, 0, 0};
     const uint8_t *src = nullptr, *src_fov = nullptr, *tgt = nullptr, *tgt_fov = nullptr;
     uint8_t *src_prep = nullptr, *tgt_prep = nullptr, *src_ok = nullptr;
-    uint32_t *src_bits = nullptr;  // masks: bitmap of the source's on bits
+    ScoreLaunch::Dice dice;  // masks: structures of the filter's launches
     int layout = kDefaultLayout, pt = kDefaultPT, zchunk = kDefaultZChunkMask;
-    int32_t box_lo[3] = {1, 1, 1}, box_hi[3] = {-1, -1, -1};  // source mask bounding box (empty)
-    uint32_t *occ = nullptr;  // masks: summed-area table of the source's occupied cells (or none)
-    unsigned long long *work = nullptr;  // masks: pairs evaluated and covered by the culled launches
+    unsigned long long *work = nullptr;  // masks: pairs sampled and covered by the filter's launches
     void *packed[kLayouts] = {};
     uint64_t sentinel[kLayouts] = {};  // per packed layout: value marking elements outside the source FOV
     bool has_sentinel[kLayouts] = {};
@@ -183,13 +181,6 @@ struct smc_ctx {
     std::string sticky_msg;
     // smc_gather_probe checksum word
     uint32_t *probe_out = nullptr;
-    // masks: culled item lists of the filter's launches (capacity item_cap),
-    // sized for launches of items_np particles (a frame pair's context scores
-    // the particles of the context it belongs to)
-    uint32_t items_np = 0;
-    void *items = nullptr;
-    uint32_t *item_counters = nullptr;
-    uint64_t item_cap = 0;
     // smc_evaluate workspace
     uint32_t eval_cap = 0;
     double *x_eval = nullptr;
@@ -232,16 +223,11 @@ struct smc_ctx {
         ScoreLaunch L;
         L.mode = mode;
         L.zchunk = zchunk;
-        L.cull_box = filter && mode == kModeMask;
-        for (int d = 0; d < 3; ++d) {
-            L.box_lo[d] = box_lo[d];
-            L.box_hi[d] = box_hi[d];
-        }
+        L.ac = filter && mode == kModeMask;
         if (mode == kModeMask) {
             L.src = src_prep;
-            L.src_bits = src_bits;
-            L.occ = L.cull_box ? occ : nullptr;
-            L.work = L.cull_box ? work : nullptr;
+            L.dice = dice;
+            L.work = L.ac ? work : nullptr;
             L.src_ok = nullptr;
             L.tgt = tgt_prep;
             L.tgt_fov = nullptr;
@@ -264,9 +250,6 @@ struct smc_ctx {
         }
         L.p0 = p0;
         L.np = np;
-        L.items = items;
-        L.item_counters = item_counters;
-        L.item_cap = item_cap;
         return L;
     }
 
@@ -382,37 +365,12 @@ smc_status launch_prior(smc_ctx *c) {
     return SMC_OK;
 }
 
-// Mask contexts: item lists large enough for a filter launch (N + 1
-// particles) under the current tuning; smaller buffers are freed.
 // Every filter launch must fit one grid (masks and images alike).
 smc_status check_items(const smc_ctx *c) {
     const uint64_t items = score_items_for(c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true));
     if (items > kMaxScoreItems)
         return fail(SMC_EINVAL, "%llu work items per scoring launch exceed %llu: use deeper tiles or fewer particles",
                     (unsigned long long)items, (unsigned long long)kMaxScoreItems);
-    return SMC_OK;
-}
-
-smc_status ensure_items(smc_ctx *c) {
-    smc_status st;
-    if ((st = check_items(c)) != SMC_OK) return st;
-    if (c->mode != kModeMask) return SMC_OK;
-    if (!c->item_counters && (st = c->alloc(&c->item_counters, kItemCounterWords)) != SMC_OK) return st;
-    const uint32_t np = std::max(c->f.n + 1, c->items_np);
-    const uint64_t need = score_items_for(c->score_launch(c->f.words, c->f.sums, 0, np, true));
-    if (need > kMaxScoreItems) return SMC_OK;  // such launches run as a grid (and are refused there)
-    if (need <= c->item_cap) return SMC_OK;
-    if (c->items) {
-        if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(SMC_EDEVICE, "stream sync failed");
-        c->allocs.erase(std::remove(c->allocs.begin(), c->allocs.end(), c->items), c->allocs.end());
-        (void)hipFree(c->items);
-        c->items = nullptr;
-        c->item_cap = 0;
-    }
-    uint2 *buf = nullptr;
-    if ((st = c->alloc(&buf, need)) != SMC_OK) return st;
-    c->items = buf;
-    c->item_cap = need;
     return SMC_OK;
 }
 
@@ -526,10 +484,24 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     if (c->mode == kModeMask) {
         if ((st = c->alloc(&c->src_prep, vs)) != SMC_OK) return bail(st);
         if ((st = c->alloc(&c->tgt_prep, vt)) != SMC_OK) return bail(st);
-        if ((st = c->alloc((uint8_t **)&c->src_bits, mask_bits_bytes(c->sn))) != SMC_OK) return bail(st);
+        const DiceSizes ds = dice_sizes(c->sn, c->tn);
+        uint8_t *bits, *gap_x, *gap_y, *field, *t4, *t8, *t16;
+        if ((st = c->alloc(&bits, ds.bits)) != SMC_OK || (st = c->alloc(&gap_x, ds.gap_x)) != SMC_OK ||
+            (st = c->alloc(&gap_y, ds.gap_y)) != SMC_OK || (st = c->alloc(&field, ds.field)) != SMC_OK ||
+            (st = c->alloc(&t4, ds.t4)) != SMC_OK || (st = c->alloc(&t8, ds.t8)) != SMC_OK ||
+            (st = c->alloc(&t16, ds.t16)) != SMC_OK || (st = c->alloc(&c->work, kWorkSlots * kWorkSlotWords)) != SMC_OK)
+            return bail(st);
+        c->dice.bits = (const uint32_t *)bits;
+        c->dice.field = field;
+        c->dice.t4 = t4;
+        c->dice.t8 = (const uint32_t *)t8;
+        c->dice.t16 = (const uint32_t *)t16;
         if (launch_prep_mask(src->data, src->fov, c->src_prep, vs, c->stream) != hipSuccess ||
             launch_prep_mask(tgt->data, tgt->fov, c->tgt_prep, vt, c->stream) != hipSuccess ||
-            launch_pack_mask_bits(c->src_prep, c->sn, c->src_bits, c->stream) != hipSuccess)
+            launch_dice_source(c->src_prep, c->sn, (uint32_t *)bits, (uint16_t *)gap_x, (uint16_t *)gap_y, field,
+                               c->stream) != hipSuccess ||
+            launch_dice_target(c->tgt_prep, c->tn, t4, (uint32_t *)t8, (uint32_t *)t16, c->stream) != hipSuccess ||
+            launch_fill_u64(c->work, kWorkSlots * kWorkSlotWords, c->stream) != hipSuccess)
             return bail(fail(SMC_EDEVICE, "mask preparation launch failed"));
     } else if (src->fov) {
         if (c->mode == kModeImageTrilinear) {
@@ -543,34 +515,6 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
 
     if (!layout_fits(c->layout, c->sn)) c->layout = layout_fits(kLayoutOct, c->sn) ? kLayoutOct : kLayoutRaw;
     if ((st = prepare_layout(c, c->layout)) != SMC_OK) return bail(st);
-
-    if (c->mode == kModeMask) {
-        int32_t *dbox = nullptr;
-        const int32_t init[6] = {INT32_MAX, INT32_MAX, INT32_MAX, -1, -1, -1};
-        int32_t hb[6];
-        if ((st = c->alloc(&dbox, 6)) != SMC_OK) return bail(st);
-        if (hipMemcpyAsync(dbox, init, sizeof init, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-            launch_mask_bbox(c->src_prep, c->sn, dbox, c->stream) != hipSuccess ||
-            hipMemcpyAsync(hb, dbox, sizeof hb, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-            hipStreamSynchronize(c->stream) != hipSuccess)
-            return bail(fail(SMC_EDEVICE, "source mask bounding box failed"));
-        if (hb[3] >= 0)
-            for (int d = 0; d < 3; ++d) {
-                c->box_lo[d] = hb[d];
-                c->box_hi[d] = hb[3 + d];
-            }
-        // occupancy of 2^3-voxel cells for the culled launches, when its table
-        // is modest (flat volumes would make its zero borders large)
-        if ((st = c->alloc(&c->work, kWorkSlots * kWorkSlotWords)) != SMC_OK) return bail(st);
-        if (launch_fill_u64(c->work, kWorkSlots * kWorkSlotWords, c->stream) != hipSuccess)
-            return bail(fail(SMC_EDEVICE, "work counter fill failed"));
-        const uint64_t ow = mask_occ_words(c->sn);
-        if (ow <= kOccMaxWords) {
-            if ((st = c->alloc(&c->occ, ow)) != SMC_OK) return bail(st);
-            if (launch_mask_occupancy(c->src_prep, c->sn, c->occ, c->stream) != hipSuccess)
-                return bail(fail(SMC_EDEVICE, "source mask occupancy launch failed"));
-        }
-    }
 
     // exact per-volume sums -> statistics
     unsigned long long *vsum = nullptr;
@@ -630,7 +574,7 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         if (launch_fill_u64((unsigned long long *)c->hist, words / 2, c->stream) != hipSuccess)
             return bail(fail(SMC_EDEVICE, "histogram clear failed"));
     }
-    if ((st = ensure_items(c)) != SMC_OK) return bail(st);
+    if ((st = check_items(c)) != SMC_OK) return bail(st);
     if ((st = launch_prior(c)) != SMC_OK) return bail(st);
     *out = c;
     return SMC_OK;
@@ -1025,7 +969,6 @@ smc_status smc_set_frames(smc_ctx *c, uint32_t n_extra, const smc_volume *src_fr
             return fail(st, "frame %u: %s", q + 1, msg.c_str());
         }
         c->frames.push_back(fr);
-        fr->items_np = c->f.n + 1;  // it scores this context's particles
         if ((st = smc_set_tuning(fr, c->layout, c->pt, c->zchunk)) != SMC_OK) return c->mark(st);
     }
     pool_frame_constants(c);
@@ -1061,7 +1004,7 @@ smc_status smc_set_tuning(smc_ctx *c, int32_t layout, int32_t pt, int32_t tile_d
         if ((st = smc_set_tuning(fr, layout, pt, tile_depth)) != SMC_OK) return c->mark(st);
     if (pt >= 0) c->pt = pt;
     if (tile_depth > 0) c->zchunk = tile_depth;
-    if ((st = ensure_items(c)) != SMC_OK) return c->mark(st);
+    if ((st = check_items(c)) != SMC_OK) return c->mark(st);
     return SMC_OK;
 }
 
@@ -1355,7 +1298,7 @@ int device_cus() {
 // items, range x going to XCD x, so every XCD sweeps one eighth of each
 // volume (its L2 holds that part of the source instead of a whole large
 // volume) and the lists stay balanced whatever the mix of pairs.
-smc_status plan_class(smc_batch *b, smc_batch::Class &C, int mode, int vmode) {
+smc_status plan_class(smc_batch *b, smc_batch::Class &C, int vmode) {
     const uint32_t n = (uint32_t)C.members.size();
     C.has_first = false;
     if (n == 0) {
@@ -1370,8 +1313,6 @@ smc_status plan_class(smc_batch *b, smc_batch::Class &C, int mode, int vmode) {
     for (uint32_t q = 0; q < n; ++q) {
         smc_ctx *c = b->pairs[C.members[q]];
         ScoreLaunch L = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true);
-        // the persistent mask launch reads every pair's source bitmap
-        if (mode == kModeMask && !L.src_bits) return fail(SMC_EINVAL, "mask pair %u has no source bitmap", C.members[q]);
         if (q == 0) {
             pt = L.pt;
             layout = L.layout;
@@ -1408,21 +1349,11 @@ smc_status plan_class(smc_batch *b, smc_batch::Class &C, int mode, int vmode) {
         (st = b->alloc(&C.kmax, n)) != SMC_OK || (st = b->alloc(&C.lists, flat.size())) != SMC_OK ||
         (st = b->alloc(&C.plan.counters, 8ull * std::max(1u, b->kmax_all))) != SMC_OK)
         return st;
-    if (mode == kModeMask) {
-        // live item lists of the cull pre-pass (one list buffer, counts per iteration)
-        uint2 *live = nullptr;
-        uint32_t *lc = nullptr;
-        if ((st = b->alloc(&live, std::max<size_t>(1, flat.size()))) != SMC_OK ||
-            (st = b->alloc(&lc, (size_t)(kItemCounterWords / 2) * std::max(1u, b->kmax_all))) != SMC_OK)
-            return st;
-        C.plan.live = live;
-        C.plan.live_counts = lc;
-    }
     HIP_TRY(hipMemcpy(C.args, args.data(), args.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(C.offs, offs.data(), 4 * (n + 1), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(C.kmax, kmax.data(), 4 * n, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(C.lists, flat.data(), 4 * flat.size(), hipMemcpyHostToDevice));
-    C.plan.mode = mode;
+    C.plan.mode = kModeImageTrilinear;
     C.plan.layout = layout;
     C.plan.pt = pt;
     C.plan.vmode = vmode;
@@ -1434,31 +1365,73 @@ smc_status plan_class(smc_batch *b, smc_batch::Class &C, int mode, int vmode) {
     // persistent grid: as many workgroups as stay resident, a multiple of the 8 XCDs
     const uint32_t per_cu = (uint32_t)batch_blocks_per_cu(C.plan);
     C.plan.grid = 8 * (((uint32_t)device_cus() * per_cu + 7) / 8);
-    if (mode == kModeImageTrilinear) {
-        // a first-iteration plan when every pair scores its uniform prior from
-        // the same other layout with the same items and FOV mode
-        std::vector<uint8_t> fargs(ab * n);
-        bool ok = true;
-        int flayout = -1;
-        for (uint32_t q = 0; q < n && ok; ++q) {
-            const smc_ctx *c = b->pairs[C.members[q]];
-            const ScoreLaunch F = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true, true);
-            if (q == 0) flayout = F.layout;
-            ok = !c->f.has_proposal && F.layout == flayout && F.layout != layout && F.pt == pt &&
-                 score_vmode(F) == vmode && score_items(F) == offs[q + 1] - offs[q];
-            if (ok) score_args(F, fargs.data() + ab * q);
-        }
-        if (ok) {
-            if ((st = b->alloc((uint8_t **)&C.fargs, fargs.size())) != SMC_OK) return st;
-            HIP_TRY(hipMemcpy(C.fargs, fargs.data(), fargs.size(), hipMemcpyHostToDevice));
-            C.plan_first = C.plan;
-            C.plan_first.layout = flayout;
-            C.plan_first.pairs = C.fargs;
-            const uint32_t fper = (uint32_t)batch_blocks_per_cu(C.plan_first);
-            C.plan_first.grid = 8 * (((uint32_t)device_cus() * fper + 7) / 8);
-            C.has_first = true;
-        }
+    // a first-iteration plan when every pair scores its uniform prior from
+    // the same other layout with the same items and FOV mode
+    std::vector<uint8_t> fargs(ab * n);
+    bool ok = true;
+    int flayout = -1;
+    for (uint32_t q = 0; q < n && ok; ++q) {
+        const smc_ctx *c = b->pairs[C.members[q]];
+        const ScoreLaunch F = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true, true);
+        if (q == 0) flayout = F.layout;
+        ok = !c->f.has_proposal && F.layout == flayout && F.layout != layout && F.pt == pt &&
+             score_vmode(F) == vmode && score_items(F) == offs[q + 1] - offs[q];
+        if (ok) score_args(F, fargs.data() + ab * q);
     }
+    if (ok) {
+        if ((st = b->alloc((uint8_t **)&C.fargs, fargs.size())) != SMC_OK) return st;
+        HIP_TRY(hipMemcpy(C.fargs, fargs.data(), fargs.size(), hipMemcpyHostToDevice));
+        C.plan_first = C.plan;
+        C.plan_first.layout = flayout;
+        C.plan_first.pairs = C.fargs;
+        const uint32_t fper = (uint32_t)batch_blocks_per_cu(C.plan_first);
+        C.plan_first.grid = 8 * (((uint32_t)device_cus() * fper + 7) / 8);
+        C.has_first = true;
+    }
+    return SMC_OK;
+}
+
+// The mask class: one launch over the workgroups of all pairs, the largest
+// pairs first.
+smc_status plan_masks(smc_batch *b, smc_batch::Class &C) {
+    C.plan = BatchPlan{};
+    const uint32_t n = (uint32_t)C.members.size();
+    if (n == 0) return SMC_OK;
+    const size_t ab = dice_args_bytes();
+    std::vector<uint8_t> one(ab * n), args(ab * n);
+    std::vector<uint64_t> groups(n);
+    std::vector<uint32_t> order(n), offs(n + 1, 0), kmax(n);
+    for (uint32_t q = 0; q < n; ++q) {
+        const smc_ctx *c = b->pairs[C.members[q]];
+        groups[q] = dice_args(c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true), one.data() + ab * q);
+        order[q] = q;
+    }
+    const auto voxels = [&](uint32_t q) {
+        const smc_ctx *c = b->pairs[C.members[q]];
+        return (double)c->tn[0] * c->tn[1] * c->tn[2] * (double)c->f.n;
+    };
+    std::sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return voxels(x) > voxels(y); });
+    uint64_t total = 0;
+    for (uint32_t q = 0; q < n; ++q) {
+        memcpy(args.data() + ab * q, one.data() + ab * order[q], ab);
+        kmax[q] = b->pairs[C.members[order[q]]]->f.n_iters;
+        total += groups[order[q]];
+        if (total > kMaxScoreItems) return fail(SMC_EINVAL, "the batch's mask pairs exceed one launch");
+        offs[q + 1] = (uint32_t)total;
+    }
+    smc_status st;
+    if ((st = b->alloc((uint8_t **)&C.args, args.size())) != SMC_OK || (st = b->alloc(&C.offs, n + 1)) != SMC_OK ||
+        (st = b->alloc(&C.kmax, n)) != SMC_OK)
+        return st;
+    HIP_TRY(hipMemcpy(C.args, args.data(), args.size(), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(C.offs, offs.data(), 4 * (n + 1), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(C.kmax, kmax.data(), 4 * n, hipMemcpyHostToDevice));
+    C.plan.mode = kModeMask;
+    C.plan.pairs = C.args;
+    C.plan.offs = C.offs;
+    C.plan.kmax = C.kmax;
+    C.plan.n_pairs = n;
+    C.plan.grid = (uint32_t)total;
     return SMC_OK;
 }
 
@@ -1487,9 +1460,9 @@ smc_status plan_all(smc_batch *b) {
         b->cls[1 + vm].members.push_back(i);
     }
     smc_status st;
-    for (int q = 0; q < 4; ++q)
-        if ((st = plan_class(b, b->cls[q], q == 0 ? kModeMask : kModeImageTrilinear, q == 0 ? 0 : q - 1)) != SMC_OK)
-            return st;
+    if ((st = plan_masks(b, b->cls[0])) != SMC_OK) return st;
+    for (int q = 1; q < 4; ++q)
+        if ((st = plan_class(b, b->cls[q], q - 1)) != SMC_OK) return st;
     return SMC_OK;
 }
 
@@ -1498,13 +1471,10 @@ smc_status record_run(smc_batch *b) {
     HIP_TRY(launch_init_batch(b->states_dev, (uint32_t)b->pairs.size(), b->max_threads, b->stream));
     for (smc_ctx *c : b->pairs) HIP_TRY(launch_fill_u64(c->f.sums, 6ull * (c->f.n + 1), b->stream));
     // the item queues start empty on every run (a fill kernel, so graph replays clear them too)
-    for (int q = 0; q < 4; ++q)
+    for (int q = 1; q < 4; ++q)
         if (b->cls[q].plan.n_pairs)
             HIP_TRY(launch_fill_u64((unsigned long long *)b->cls[q].plan.counters, 4ull * std::max(1u, b->kmax_all),
                                     b->stream));
-    if (b->cls[0].plan.n_pairs && b->cls[0].plan.live_counts)
-        HIP_TRY(launch_fill_u64((unsigned long long *)b->cls[0].plan.live_counts,
-                                (uint64_t)(kItemCounterWords / 4) * std::max(1u, b->kmax_all), b->stream));
     for (uint32_t k = 1; k <= b->kmax_all; ++k) {
         for (int q = 0; q < 4; ++q) {
             const smc_batch::Class &C = b->cls[q];

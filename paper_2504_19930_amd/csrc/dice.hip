@@ -1,0 +1,708 @@
+// Mask warp-and-score of the filter's launches (Eq. 4 on LV masks): per
+// particle the counts a (target voxels in the FOV whose nearest-neighbour
+// sample of the source is on) and c (those that are on in the target too).
+//
+// Most of a mask is far from its surface, where every sample of a block of
+// target voxels reads the same value.  A distance field of the source (one
+// byte per voxel: its state and the distance from its box to the nearest box
+// of a voxel of the other state) decides that for a whole block: the
+// image of a cubic block under the recipe lies in a ball about the image of
+// its centre, so when the field there exceeds the ball's radius the block adds
+// nothing (off) or its precomputed target counts (on).  Blocks of 16^3 are
+// tested first, the undecided ones are split into 8^3 and then 4^3, and only
+// undecided 4^3 blocks are sampled -- the counts are exactly those of sampling
+// every voxel.
+//
+// A wave takes one particle and up to 64 of the target's 16^3 blocks: one lane
+// per block and test, survivors compacted through a per-wave LDS list, no
+// workgroup barrier, no list in memory and no pre-pass.  Sampling gives a
+// 4^3 block to a quarter-wave: 16 lanes are a 4 x 4 patch of a slice (the
+// texture path serves a quarter together and a 4 x 4 patch's image touches few
+// rows and slices), each walking four slices, eight gathers in flight a lane.
+// The sampled bits of a lane's four slices form a nibble that is counted
+// against the target's nibbles with two population counts.
+//
+// What it measured (224 x 208 x 176 filled LV masks, N = 4096, K = 40, a whole
+// registration): 79.2 ms with every 32 x 8 x 16 tile of the occupied part
+// sampled (13.6 % of the pairs, 1.50 ms a launch); 38.4 ms with blocks down to
+// 4^3 by a field of 2^3-voxel cells and 19 VALU instructions a gather; 26.7 ms
+// with the block list in floats, a byte of target bits a lane and eighths of a
+// voxel (15); 24.0 ms with the field at voxels.  Bound: VALU issue (1.2
+// instructions a CU and clock) and, close behind, the texture path; six to
+// eight waves a SIMD (fewer registers) ran no faster than five.
+#include <string.h>
+
+#include <algorithm>
+
+#include "internal.h"
+
+namespace smc {
+namespace {
+
+constexpr int kWaves = 4;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kBufferWord3 = 0x00020000;
+// Bound on the partial sums of the recipe below which a sample's and a block
+// centre's FP32 coordinates are each within 0.023 voxel of the exact map, so
+// that kMargin covers both; beyond it every voxel is sampled.
+constexpr float kCoordLimit = 262144.0f;
+constexpr float kMargin = 0.0625f;
+// Field byte: distance in eighths of a voxel (below 16 voxels), state bit.
+constexpr uint32_t kFieldOn = 128u, kFieldDist = 127u;
+constexpr float kFieldUnit = 8.0f;
+constexpr int kWindow = 16;  // voxels searched on either side
+constexpr int kStrip = 16;   // voxels of a line a thread of the field's passes makes
+
+#if defined(__HIP_DEVICE_COMPILE__)
+#define SMC_CONSTANT_AS __attribute__((address_space(4)))
+#else
+#define SMC_CONSTANT_AS
+#endif
+template <typename T>
+__device__ __forceinline__ const SMC_CONSTANT_AS T *as_const(const T *p) {
+    return (const SMC_CONSTANT_AS T *)p;
+}
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+// 32-bit load at element `vindex` of a buffer with a record stride; records
+// past the end read zero.
+__device__ uint32_t struct_load_u32(v4i rsrc, int vindex, int voffset, int soffset,
+                                    int aux) __asm("llvm.amdgcn.struct.buffer.load.i32");
+
+struct Args {
+    // source bitmap: dword y + ny (x / 32 + W z), bit 31 - x % 32.  A 4 x 4
+    // patch's image spans about five rows and one or two slices: rows four
+    // bytes apart put a slice's part of it in one cache line
+    const uint32_t *bits;
+    const uint8_t *field;  // source distance field, one byte per voxel
+    // target 4^3 blocks, 16 bytes: byte l of the column (l % 4, l / 4), slice s
+    // in bit 3 - s (FOV) and 7 - s (on)
+    const uint4 *t4;
+    uint32_t t4_bytes;
+    const uint32_t *t8, *t16;  // target counts of 8^3 and 16^3 blocks: FOV | on << 16
+    const float *words;
+    unsigned long long *sums, *work;
+    int32_t sn[3], tn[3];
+    uint32_t ny, WH, bwords;  // bitmap strides (dwords) of 32 voxels in x and of a slice
+    uint32_t fx, fxy, fbytes;
+    uint32_t g4[3], g8[3], g16[3], n16;
+    uint32_t p0, np;
+    uint32_t blocks, parts;  // 16^3 blocks per wave, waves per particle
+};
+
+// A block of a list: x | y << 16, z, and in z's word the flag that the image
+// of its 32 x 16 x 16 tile lies inside the source.
+constexpr uint32_t kInner = 0x80000000u;
+
+// A block to sample: the floats of its first voxel, then its index in t4 with
+// the flag.
+struct WaveLds {
+    uint2 l16[64], l8[64];
+    uint4 u[72];
+};
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ uint32_t rank_of(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+// One particle over 16^3 blocks [part * blocks, (part + 1) * blocks).  PROBE:
+// the same tests, coordinates and source loads, the loaded words XORed into
+// the result instead of counted.
+template <bool PROBE, typename A>
+__device__ __forceinline__ uint32_t dice_wave(const A &a, uint32_t part, uint32_t p, WaveLds &q) {
+    const uint32_t lane = threadIdx.x % 64u;
+    const auto *wp = as_const(a.words) + 12 * (size_t)p;
+    float w[12];
+#pragma unroll
+    for (int e = 0; e < 12; ++e) w[e] = wp[e];
+
+    // ball radii: the farthest image of a corner of the unit half-cube
+    float rho2 = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        float d2 = 0.0f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float v = w[4 * d] + (s & 1 ? w[4 * d + 1] : -w[4 * d + 1]) + (s & 2 ? w[4 * d + 2] : -w[4 * d + 2]);
+            d2 = fmaf(v, v, d2);
+        }
+        rho2 = fmaxf(rho2, d2);
+    }
+    const float rho = sqrtf(rho2);
+    bool bounded = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const float b = fabsf(w[4 * d]) * (float)(a.tn[0] + 16) + fabsf(w[4 * d + 1]) * (float)(a.tn[1] + 16) +
+                        fabsf(w[4 * d + 2]) * (float)(a.tn[2] + 16) + fabsf(w[4 * d + 3]);
+        bounded = bounded && b < kCoordLimit;
+    }
+    // least field distance (in its units) that decides a block of each size
+    const auto threshold = [&](float half) {
+        return bounded ? (uint32_t)fminf(ceilf(kFieldUnit * (half * rho + kMargin)), 255.0f) : 255u;
+    };
+    const uint32_t need16 = threshold(7.5f), need8 = threshold(3.5f), need4 = threshold(1.5f);
+    // half extents of the image's box of a 32 x 16 x 16 tile
+    float rt[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        rt[d] = fmaf(15.5f, fabsf(w[4 * d]), fmaf(7.5f, fabsf(w[4 * d + 1]), 7.5f * fabsf(w[4 * d + 2]))) + kMargin;
+
+    const __amdgpu_buffer_rsrc_t rs_f =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.field), (short)0, (int)a.fbytes, kBufferWord3);
+    const uint64_t bits_addr = (uint64_t)a.bits;
+    const v4i rs_b = {(int)(uint32_t)bits_addr, (int)((uint32_t)(bits_addr >> 32) & 0xFFFFu) | (4 << 16), (int)a.bwords,
+                      kBufferWord3};
+    const float n0 = (float)a.sn[0], n1 = (float)a.sn[1], n2 = (float)a.sn[2];
+
+    // field byte at the image u of a block centre (clipped into the source:
+    // a point outside it is no nearer to an on voxel than its clipped point)
+    const auto field_at = [&](float cx, float cy, float cz, float u[3]) {
+        u[0] = fmaf(w[2], cz, fmaf(w[1], cy, fmaf(w[0], cx, w[3])));
+        u[1] = fmaf(w[6], cz, fmaf(w[5], cy, fmaf(w[4], cx, w[7])));
+        u[2] = fmaf(w[10], cz, fmaf(w[9], cy, fmaf(w[8], cx, w[11])));
+        const uint32_t x = floor_u32(__builtin_amdgcn_fmed3f(u[0], 0.0f, n0 - 0.5f));
+        const uint32_t y = floor_u32(__builtin_amdgcn_fmed3f(u[1], 0.0f, n1 - 0.5f));
+        const uint32_t z = floor_u32(__builtin_amdgcn_fmed3f(u[2], 0.0f, n2 - 0.5f));
+        const uint32_t o = mad_u24(z, a.fxy, mad_u24(y, a.fx, x));
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rs_f, o, 0, 0);
+    };
+
+    uint32_t na = 0u, nc = 0u, chk = 0u;  // a, c of this lane
+    uint32_t ev = 0u, evi = 0u;           // pairs sampled; those of interior blocks
+
+    // this lane's column in a sampled block
+    const uint32_t l16 = lane % 16u, quarter = lane / 16u;
+    const float dx = (float)(l16 % 4u), dy = (float)(l16 / 4u);
+    const __amdgpu_buffer_rsrc_t rs_t =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.t4), (short)0, (int)a.t4_bytes, kBufferWord3);
+
+    // sample units base .. base + n - 1 (n <= 8) of the list
+    const auto sample = [&](uint32_t base, uint32_t n) {
+        float mx[2], my[2], mz[2], fk[2];
+        uint32_t tb[2];
+        bool inner = true;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const uint32_t i = 4u * g + quarter;
+            const bool ok = i < n;
+            const uint4 e = q.u[base + (ok ? i : 0u)];
+            inner = inner && (e.w & kInner) != 0u;
+            // (the shift drops the flag; a record past the end reads zero)
+            if (!PROBE) tb[g] = __builtin_amdgcn_raw_buffer_load_b8(rs_t, ok ? (e.w << 4) | l16 : a.t4_bytes, 0, 0);
+            const float fi = __uint_as_float(e.x) + dx, fj = __uint_as_float(e.y) + dy;
+            fk[g] = __uint_as_float(e.z);
+            mx[g] = fmaf(w[1], fj, fmaf(w[0], fi, w[3]));
+            my[g] = fmaf(w[5], fj, fmaf(w[4], fi, w[7]));
+            mz[g] = fmaf(w[9], fj, fmaf(w[8], fi, w[11]));
+        }
+        uint32_t ix[2][4], word[2][4];
+        if (__all(inner)) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const float k = s ? fk[g] + (float)s : fk[g];
+                    ix[g][s] = floor_u32(fmaf(w[2], k, mx[g]));
+                    const uint32_t iy = floor_u32(fmaf(w[6], k, my[g])), iz = floor_u32(fmaf(w[10], k, mz[g]));
+                    word[g][s] = struct_load_u32(rs_b, (int)mad_u24(iz, a.WH, mad_u24(ix[g][s] >> 5, a.ny, iy)), 0, 0, 0);
+                }
+        } else {
+            // inside iff 0 <= u < n per axis, as unsigned compares of bit
+            // patterns (coordinates are never -0); outside samples load past
+            // the end: zero, no cache line touched
+            const uint32_t b0 = __float_as_uint(n0), b1 = __float_as_uint(n1), b2 = __float_as_uint(n2);
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const float k = s ? fk[g] + (float)s : fk[g];
+                    const float ux = fmaf(w[2], k, mx[g]), uy = fmaf(w[6], k, my[g]), uz = fmaf(w[10], k, mz[g]);
+                    ix[g][s] = floor_u32(ux);
+                    const bool in = (__float_as_uint(ux) < b0) & (__float_as_uint(uy) < b1) & (__float_as_uint(uz) < b2);
+                    const uint32_t o = mad_u24(floor_u32(uz), a.WH, mad_u24(ix[g][s] >> 5, a.ny, floor_u32(uy)));
+                    word[g][s] = struct_load_u32(rs_b, (int)(in ? o : a.bwords), 0, 0, 0);
+                }
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            uint32_t b = 0u;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (PROBE) chk ^= word[g][s];
+                else b = __builtin_amdgcn_alignbit(b, word[g][s] << (ix[g][s] & 31u), 31u);
+            }
+            if (!PROBE) {
+                const uint32_t t = tb[g] & (b | (b << 4));
+                na += (uint32_t)__popc(t & 15u);
+                nc += (uint32_t)__popc(t >> 4);
+            }
+        }
+    };
+
+    // 16^3 blocks, one a lane
+    uint32_t n_l16;
+    {
+        const uint32_t id = part * a.blocks + lane;
+        const bool valid = lane < a.blocks && id < a.n16;
+        const uint32_t row = id / a.g16[0], bx = id - row * a.g16[0], bz = row / a.g16[1], by = row - bz * a.g16[1];
+        float u[3];
+        const uint32_t f = field_at(fmaf(16.0f, (float)bx, 7.5f), fmaf(16.0f, (float)by, 7.5f),
+                                    fmaf(16.0f, (float)bz, 7.5f), u);
+        const uint32_t t = valid ? a.t16[id] : 0u;
+        const bool decided = (f & kFieldDist) >= need16;
+        if (decided && (f & kFieldOn)) {
+            na += t & 0xFFFFu;
+            nc += t >> 16;
+        }
+        // (t = 0: no target voxel of the block is in the FOV)
+        const bool open = !decided && t != 0u;
+        const uint64_t m = __ballot(open);
+        n_l16 = (uint32_t)__popcll(m);
+        // every sample of the block's 32 x 16 x 16 tile lies inside the source:
+        // the block's parts skip the inside test.  (u moves by half a tile from
+        // the block's centre to the tile's.)
+        const float e = bx & 1u ? -8.0f : 8.0f;
+        bool inner = bounded;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float ut = fmaf(w[4 * d], e, u[d]);
+            inner = inner && ut - rt[d] >= 0.0f && ut + rt[d] < (float)a.sn[d];
+        }
+        if (open) q.l16[rank_of(m)] = make_uint2(bx | (by << 16), bz | (inner ? kInner : 0u));
+        wave_sync();
+    }
+    uint32_t n_u = 0u;
+    for (uint32_t s16 = 0; s16 < n_l16; s16 += 8u) {
+        // the eight 8^3 blocks of eight 16^3 blocks
+        const uint32_t child = lane % 8u;
+        uint32_t n_l8;
+        {
+            const uint32_t i = s16 + lane / 8u;
+            const uint2 e = q.l16[min(i, n_l16 - 1u)];
+            const uint32_t x = 2u * (e.x & 0xFFFFu) + (child & 1u), y = 2u * (e.x >> 16) + ((child >> 1) & 1u),
+                           z = 2u * (e.y & ~kInner) + (child >> 2);
+            const bool valid = i < n_l16 && x < a.g8[0] && y < a.g8[1] && z < a.g8[2];
+            float u[3];
+            const uint32_t f = field_at(fmaf(8.0f, (float)x, 3.5f), fmaf(8.0f, (float)y, 3.5f),
+                                        fmaf(8.0f, (float)z, 3.5f), u);
+            const uint32_t t = valid ? a.t8[x + a.g8[0] * (y + a.g8[1] * z)] : 0u;
+            const bool decided = (f & kFieldDist) >= need8;
+            if (decided && (f & kFieldOn)) {
+                na += t & 0xFFFFu;
+                nc += t >> 16;
+            }
+            const bool open = !decided && t != 0u;
+            const uint64_t m = __ballot(open);
+            n_l8 = (uint32_t)__popcll(m);
+            wave_sync();  // the previous list of 8^3 blocks has been read
+            if (open) q.l8[rank_of(m)] = make_uint2(x | (y << 16), z | (e.y & kInner));
+            wave_sync();
+        }
+        for (uint32_t s8 = 0; s8 < n_l8; s8 += 8u) {
+            const uint32_t i = s8 + lane / 8u;
+            const uint2 e = q.l8[min(i, n_l8 - 1u)];
+            const uint32_t x = 2u * (e.x & 0xFFFFu) + (child & 1u), y = 2u * (e.x >> 16) + ((child >> 1) & 1u),
+                           z = 2u * (e.y & ~kInner) + (child >> 2);
+            const bool valid = i < n_l8 && x < a.g4[0] && y < a.g4[1] && z < a.g4[2];
+            float u[3];
+            const uint32_t f = field_at(fmaf(4.0f, (float)x, 1.5f), fmaf(4.0f, (float)y, 1.5f),
+                                        fmaf(4.0f, (float)z, 1.5f), u);
+            const bool decided = (f & kFieldDist) >= need4;
+            const uint32_t id = x + a.g4[0] * (y + a.g4[1] * z);
+            if (!PROBE && valid && decided && (f & kFieldOn)) {
+                const uint4 t = a.t4[id];
+                const uint32_t all[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    na += (uint32_t)__popc(all[d] & 0x0F0F0F0Fu);
+                    nc += (uint32_t)__popc(all[d] & 0xF0F0F0F0u);
+                }
+            }
+            const bool open = valid && !decided;
+            const uint64_t m = __ballot(open);
+            if (open) {
+                q.u[n_u + rank_of(m)] = make_uint4(__float_as_uint(4.0f * (float)x), __float_as_uint(4.0f * (float)y),
+                                                   __float_as_uint(4.0f * (float)z), id | (e.y & kInner));
+                const uint32_t pairs = min(4u, (uint32_t)a.tn[0] - 4u * x) * min(4u, (uint32_t)a.tn[1] - 4u * y) *
+                                       min(4u, (uint32_t)a.tn[2] - 4u * z);
+                ev += pairs;
+                evi += (e.y & kInner) ? pairs : 0u;
+            }
+            n_u += (uint32_t)__popcll(m);
+            wave_sync();
+            while (n_u >= 8u) {
+                n_u -= 8u;
+                sample(n_u, 8u);
+            }
+            wave_sync();  // the sampled units have been read
+        }
+    }
+    if (n_u) sample(0u, n_u);
+    if (PROBE) return chk;
+
+    if (__any((na | ev) != 0u)) {
+        na = wave_sum(na);
+        nc = wave_sum(nc);
+        ev = wave_sum(ev);
+        evi = wave_sum(evi);
+        if (lane == 0u) {
+            if (na) atomicAdd(a.sums + 6 * (size_t)p + 1, (unsigned long long)na);
+            if (nc) atomicAdd(a.sums + 6 * (size_t)p + 2, (unsigned long long)nc);
+            if (a.work && ev) {
+                unsigned long long *slot =
+                    a.work + kWorkSlotWords * ((blockIdx.x * kWaves + threadIdx.x / 64u) % kWorkSlots);
+                atomicAdd(slot, (unsigned long long)ev);
+                if (evi) atomicAdd(slot + 2, (unsigned long long)evi);
+            }
+        }
+    }
+    return 0u;
+}
+
+// Workgroup `block` of the launch: 16^3 blocks of part block / groups, a
+// particle a wave, so the workgroups in flight share a part of the target and,
+// the particles being clustered, a part of the source.
+template <typename A>
+__device__ __forceinline__ bool wave_unit(const A &a, uint32_t block, uint32_t &part, uint32_t &p) {
+    const uint32_t groups = (a.np + kWaves - 1u) / kWaves;
+    part = block / groups;
+    const uint32_t i = (block - part * groups) * kWaves +
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
+    p = a.p0 + i;
+    return i < a.np;
+}
+
+__global__ __launch_bounds__(kThreads) void k_score_dice(const Args a) {
+    __shared__ WaveLds q[kWaves];
+    uint32_t part, p;
+    if (blockIdx.x == 0u && threadIdx.x == 0u && a.work)
+        atomicAdd(a.work + 1, (unsigned long long)a.np * (unsigned long long)a.tn[0] * (unsigned long long)a.tn[1] *
+                                  (unsigned long long)a.tn[2]);
+    if (!wave_unit(a, blockIdx.x, part, p)) return;
+    dice_wave<false>(a, part, p, q[threadIdx.x / 64u]);
+}
+
+__global__ __launch_bounds__(kThreads) void k_probe_dice(const Args a, uint32_t key, uint32_t *out) {
+    __shared__ WaveLds q[kWaves];
+    uint32_t part, p;
+    if (!wave_unit(a, blockIdx.x, part, p)) return;
+    const uint32_t chk = dice_wave<true>(a, part, p, q[threadIdx.x / 64u]);
+    if (chk == key) out[0] = chk;
+}
+
+// The mask pairs of a batch: pair d owns workgroups offs[d] .. offs[d + 1) - 1.
+__global__ __launch_bounds__(kThreads) void k_batch_dice(const Args *pairs_g, const uint32_t *offs_g,
+                                                         const uint32_t *kmax_g, uint32_t n_pairs, uint32_t k) {
+    __shared__ WaveLds q[kWaves];
+    const auto *offs = as_const(offs_g);
+    uint32_t lo = 0, hi = n_pairs - 1;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (offs[mid] <= blockIdx.x) lo = mid;
+        else hi = mid - 1;
+    }
+    if (as_const(kmax_g)[lo] < k) return;  // pairs with fewer iterations are done
+    const Args a = as_const(pairs_g)[lo];
+    uint32_t part, p;
+    if (!wave_unit(a, blockIdx.x - offs[lo], part, p)) return;
+    dice_wave<false>(a, part, p, q[threadIdx.x / 64u]);
+}
+
+// ---------------------------------------------------------------- preparation
+
+// Source bitmap: bit 31 - x % 32 of dword y + ny (x / 32 + W z); pad bits
+// zero.  A thread makes one dword, neighbours of one row (the reads meet).
+__global__ __launch_bounds__(256) void k_pack_bits(const uint8_t *prep, int32_t nx, uint32_t ny, int64_t rows,
+                                                   uint32_t W, uint32_t *out) {
+    const int64_t n = (int64_t)W * rows;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+        const int64_t row = q / W, z = row / ny;
+        const uint32_t xw = (uint32_t)(q - row * W), y = (uint32_t)(row - z * ny);
+        const int32_t x0 = (int32_t)xw * 32;
+        const uint8_t *r = prep + row * (int64_t)nx;
+        uint32_t v = 0u;
+        for (int b = 0; b < 32 && x0 + b < nx; ++b) v |= ((uint32_t)(r[x0 + b] >> 1) & 1u) << (31 - b);
+        out[y + ny * (xw + W * z)] = v;
+    }
+}
+
+// The field, one axis at a time.  Gaps are whole voxels between two voxels'
+// boxes, 0 where they touch; kWindow and more read as kWindow, and squared
+// distances saturate at 255 (both lower bounds).  Voxels outside the source
+// are off.  Byte pairs hold the distances to the nearest on (low) and off
+// (high) voxel.
+//
+// x: gaps along the rows, four voxels a thread.
+__global__ __launch_bounds__(256) void k_field_x(const uint32_t *bits, int32_t nx, uint32_t ny, int64_t rows, uint32_t W,
+                                                 uint16_t *out) {
+    const int64_t quads = (nx + 3) / 4, n = quads * rows;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+        const int64_t row = q / quads, z = row / ny;
+        const int32_t xa = 4 * (int32_t)(q - row * quads), x0 = xa - kWindow;  // first voxel of the window
+        const uint32_t *r = bits + (row - z * ny) + (int64_t)ny * W * z;
+        const int32_t d = x0 >> 5, s = x0 & 31;
+        const auto word = [&](int32_t e) { return e >= 0 && e < (int32_t)W ? __brev(r[(int64_t)ny * e]) : 0u; };
+        uint64_t m = ((uint64_t)word(d) | ((uint64_t)word(d + 1) << 32)) >> s;
+        if (s) m |= (uint64_t)word(d + 2) << (64 - s);
+        // kWindow bits to the left of a voxel, its own, kWindow to the right
+        const auto gap = [&](uint64_t b) -> uint32_t {
+            if ((b >> kWindow) & 1u) return 0u;
+            const uint32_t l = (uint32_t)b & ((1u << kWindow) - 1u),
+                           rt = (uint32_t)(b >> (kWindow + 1)) & ((1u << kWindow) - 1u);
+            const uint32_t gl = l ? (uint32_t)__clz(l) - (32u - kWindow) : (uint32_t)kWindow;
+            const uint32_t gr = rt ? (uint32_t)__ffs(rt) - 1u : (uint32_t)kWindow;
+            return min(gl, gr);
+        };
+        for (int j = 0; j < 4 && xa + j < nx; ++j)
+            out[row * nx + xa + j] = (uint16_t)(gap(m >> j) | (gap(~m >> j) << 8));
+    }
+}
+
+// Lower envelopes of a strip of kStrip voxels along a line: v holds, from
+// kWindow before the strip on, the squared distances within the rows (planes)
+// crossed so far, on in the low and off in the high half; a voxel t steps away
+// adds the square of its gap.  Both halves move together in packed 16-bit
+// arithmetic.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 envelope(const u16x2 *v) {
+    u16x2 m = v[kWindow];
+#pragma unroll
+    for (int t = -kWindow; t <= kWindow; ++t) {
+        if (t == 0) continue;
+        const int g = (t < 0 ? -t : t) - 1;
+        m = __builtin_elementwise_min(m, (u16x2)(v[kWindow + t] + (uint16_t)(g * g)));
+    }
+    return m;
+}
+
+// y: squared distances within a slice.
+__global__ __launch_bounds__(256) void k_field_y(const uint16_t *gx, int32_t nx, int32_t ny, int32_t nz,
+                                                 uint16_t *out) {
+    const int64_t strips = (ny + kStrip - 1) / kStrip, n = (int64_t)nx * strips * nz;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+        const int64_t t = q / nx, z = t / strips;
+        const int32_t y0 = kStrip * (int32_t)(t - z * strips);
+        const uint16_t *line = gx + (q - t * nx) + (int64_t)nx * ny * z;
+        u16x2 v[kStrip + 2 * kWindow];
+#pragma unroll
+        for (int e = 0; e < kStrip + 2 * kWindow; ++e) {
+            const int32_t y = y0 + e - kWindow;
+            const uint32_t g = y >= 0 && y < ny ? line[(int64_t)nx * y] : (uint32_t)kWindow;  // outside: off
+            const u16x2 p = {(uint16_t)(g & 255u), (uint16_t)(g >> 8)};
+            v[e] = p * p;
+        }
+#pragma unroll
+        for (int j = 0; j < kStrip; ++j) {
+            if (y0 + j >= ny) break;
+            const u16x2 m = envelope(v + j);
+            out[(q - t * nx) + (int64_t)nx * ((y0 + j) + ny * z)] =
+                (uint16_t)(min((uint32_t)m.x, 255u) | (min((uint32_t)m.y, 255u) << 8));
+        }
+    }
+}
+
+// z, and the field byte: 0 where a voxel of the other state touches (always
+// sampled).
+__global__ __launch_bounds__(256) void k_field_z(const uint16_t *gy, int64_t plane, int32_t nz, uint8_t *out) {
+    const int64_t strips = (nz + kStrip - 1) / kStrip, n = plane * strips;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+        const int64_t t = q / plane;
+        const int32_t z0 = kStrip * (int32_t)t;
+        const uint16_t *line = gy + (q - t * plane);
+        u16x2 v[kStrip + 2 * kWindow];
+#pragma unroll
+        for (int e = 0; e < kStrip + 2 * kWindow; ++e) {
+            const int32_t z = z0 + e - kWindow;
+            const uint32_t g = z >= 0 && z < nz ? line[plane * z] : 255u;  // outside: off
+            v[e] = u16x2{(uint16_t)(g & 255u), (uint16_t)(g >> 8)};
+        }
+#pragma unroll
+        for (int j = 0; j < kStrip; ++j) {
+            if (z0 + j >= nz) break;
+            const u16x2 m = envelope(v + j);
+            // (one of the two is 0: the voxel's own state)
+            const uint32_t d2 = min((uint32_t)max(m.x, m.y), 255u);
+            const uint32_t dist = min(kFieldDist, (uint32_t)floorf(sqrtf((float)(64u * d2))));
+            out[(q - t * plane) + plane * (z0 + j)] = (uint8_t)(dist | (m.x == 0 && m.y != 0 ? kFieldOn : 0u));
+        }
+    }
+}
+
+// Target 4^3 blocks (layout: Args::t4).
+__global__ __launch_bounds__(256) void k_target4(const uint8_t *prep, int32_t nx, int32_t ny, int32_t nz, uint32_t gx,
+                                                 uint32_t gy, uint32_t gz, uint4 *out) {
+    const int64_t n = (int64_t)gx * gy * gz;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+        const int64_t t = q / gx;
+        const int32_t x0 = 4 * (int32_t)(q - t * gx), y0 = 4 * (int32_t)(t % gy), z0 = 4 * (int32_t)(t / gy);
+        uint32_t v[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int y = 0; y < 4; ++y)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    if (z0 + s >= nz || y0 + y >= ny || x0 + x >= nx) continue;
+                    const uint32_t b = prep[(int64_t)(x0 + x) + (int64_t)nx * ((y0 + y) + (int64_t)ny * (z0 + s))];
+                    v[y] |= ((b & 1u) | ((b & 2u) << 3)) << (8 * x + 3 - s);
+                }
+        out[q] = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+// Counts (FOV | on << 16) of the target blocks of side 4 c (c = 2, 4).
+__global__ __launch_bounds__(256) void k_target_counts(const uint4 *t4, uint32_t c, uint32_t g4x, uint32_t g4y,
+                                                       uint32_t g4z, uint32_t gx, uint32_t gy, uint32_t gz,
+                                                       uint32_t *out) {
+    const int64_t n = (int64_t)gx * gy * gz;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+        const int64_t t = q / gx;
+        const uint32_t x0 = c * (uint32_t)(q - t * gx), y0 = c * (uint32_t)(t % gy), z0 = c * (uint32_t)(t / gy);
+        uint32_t v = 0u;
+        for (uint32_t z = z0; z < min(z0 + c, g4z); ++z)
+            for (uint32_t y = y0; y < min(y0 + c, g4y); ++y)
+                for (uint32_t x = x0; x < min(x0 + c, g4x); ++x) {
+                    const uint4 b = t4[x + (int64_t)g4x * (y + (int64_t)g4y * z)];
+                    v += (uint32_t)(__popc(b.x & 0x0F0F0F0Fu) + __popc(b.y & 0x0F0F0F0Fu) +
+                                    __popc(b.z & 0x0F0F0F0Fu) + __popc(b.w & 0x0F0F0F0Fu)) +
+                         ((uint32_t)(__popc(b.x & 0xF0F0F0F0u) + __popc(b.y & 0xF0F0F0F0u) +
+                                     __popc(b.z & 0xF0F0F0F0u) + __popc(b.w & 0xF0F0F0F0u))
+                          << 16);
+                }
+        out[q] = v;
+    }
+}
+
+unsigned blocks_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192)); }
+
+uint32_t cells(int32_t n, int32_t side) { return (uint32_t)((n + side - 1) / side); }
+
+Args make_args(const ScoreLaunch &L) {
+    Args a;
+    a.bits = L.dice.bits;
+    a.field = L.dice.field;
+    a.t4 = (const uint4 *)L.dice.t4;
+    a.t8 = L.dice.t8;
+    a.t16 = L.dice.t16;
+    a.words = L.words;
+    a.sums = L.sums;
+    a.work = L.work;
+    for (int d = 0; d < 3; ++d) {
+        a.sn[d] = L.sn[d];
+        a.tn[d] = L.tn[d];
+        a.g4[d] = cells(L.tn[d], 4);
+        a.g8[d] = cells(L.tn[d], 8);
+        a.g16[d] = cells(L.tn[d], 16);
+    }
+    a.n16 = a.g16[0] * a.g16[1] * a.g16[2];
+    a.t4_bytes = 16u * a.g4[0] * a.g4[1] * a.g4[2];
+    a.ny = (uint32_t)L.sn[1];
+    a.WH = cells(L.sn[0], 32) * a.ny;
+    a.bwords = a.WH * (uint32_t)L.sn[2];
+    a.fx = (uint32_t)L.sn[0];
+    a.fxy = a.fx * a.ny;
+    a.fbytes = a.fxy * (uint32_t)L.sn[2];
+    a.p0 = L.p0;
+    a.np = L.np;
+    // blocks per wave: as many as keep about 32k waves (16 per SIMD slot of
+    // the 256 CUs), since a wave tests 64 blocks at the price of one
+    const uint64_t want = (uint64_t)a.n16 * L.np / 32768u;
+    a.blocks = (uint32_t)std::min<uint64_t>(64u, std::max<uint64_t>(4u, want));
+    a.parts = (a.n16 + a.blocks - 1) / a.blocks;
+    return a;
+}
+
+uint64_t groups_of(const Args &a) { return (uint64_t)a.parts * ((a.np + kWaves - 1) / kWaves); }
+
+}  // namespace
+
+DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]) {
+    DiceSizes s;
+    const uint64_t n = (uint64_t)sn[0] * sn[1] * sn[2];
+    s.bits = 4ull * cells(sn[0], 32) * (uint64_t)sn[1] * (uint64_t)sn[2];
+    s.field = n;
+    s.gap_x = s.gap_y = 2ull * n;
+    const auto grid = [&](int32_t side) {
+        return (uint64_t)cells(tn[0], side) * cells(tn[1], side) * cells(tn[2], side);
+    };
+    s.t4 = 16ull * grid(4);
+    s.t8 = 4ull * grid(8);
+    s.t16 = 4ull * grid(16);
+    return s;
+}
+
+hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
+                              uint16_t *gap_y, uint8_t *field, hipStream_t s) {
+    const int64_t rows = (int64_t)n[1] * n[2], plane = (int64_t)n[0] * n[1];
+    const uint32_t W = cells(n[0], 32);
+    hipLaunchKernelGGL(k_pack_bits, dim3(blocks_for(W * rows)), dim3(256), 0, s, prep, n[0], (uint32_t)n[1], rows, W,
+                       bits);
+    hipLaunchKernelGGL(k_field_x, dim3(blocks_for((n[0] + 3) / 4 * rows)), dim3(256), 0, s, (const uint32_t *)bits,
+                       n[0], (uint32_t)n[1], rows, W, gap_x);
+    hipLaunchKernelGGL(k_field_y, dim3(blocks_for(((int64_t)n[1] + kStrip - 1) / kStrip * n[0] * n[2])), dim3(256), 0, s,
+                       (const uint16_t *)gap_x, n[0], n[1], n[2], gap_y);
+    hipLaunchKernelGGL(k_field_z, dim3(blocks_for(((int64_t)n[2] + kStrip - 1) / kStrip * plane)), dim3(256), 0, s,
+                       (const uint16_t *)gap_y, plane, n[2], field);
+    return hipGetLastError();
+}
+
+hipError_t launch_dice_target(const uint8_t *prep, const int32_t n[3], void *t4, uint32_t *t8, uint32_t *t16,
+                              hipStream_t s) {
+    uint32_t g[3][3];
+    for (int l = 0; l < 3; ++l)
+        for (int d = 0; d < 3; ++d) g[l][d] = cells(n[d], 4 << l);
+    const auto count = [&](int l) { return (int64_t)g[l][0] * g[l][1] * g[l][2]; };
+    hipLaunchKernelGGL(k_target4, dim3(blocks_for(count(0))), dim3(256), 0, s, prep, n[0], n[1], n[2], g[0][0], g[0][1],
+                       g[0][2], (uint4 *)t4);
+    for (int l = 1; l < 3; ++l)
+        hipLaunchKernelGGL(k_target_counts, dim3(blocks_for(count(l))), dim3(256), 0, s, (const uint4 *)t4, 1u << l,
+                           g[0][0], g[0][1], g[0][2], g[l][0], g[l][1], g[l][2], l == 1 ? t8 : t16);
+    return hipGetLastError();
+}
+
+size_t dice_args_bytes() { return sizeof(Args); }
+
+uint64_t dice_args(const ScoreLaunch &L, void *out) {
+    const Args a = make_args(L);
+    memcpy(out, &a, sizeof a);
+    return groups_of(a);
+}
+
+hipError_t launch_dice(const ScoreLaunch &L, hipStream_t s) {
+    if (L.np == 0) return hipSuccess;
+    const Args a = make_args(L);
+    const uint64_t groups = groups_of(a);
+    if (groups > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_score_dice, dim3((unsigned)groups), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_dice_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s) {
+    if (L.np == 0) return hipSuccess;
+    const Args a = make_args(L);
+    const uint64_t groups = groups_of(a);
+    if (groups > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_probe_dice, dim3((unsigned)groups), dim3(kThreads), 0, s, a, key, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_dice(const void *pairs, const uint32_t *offs, const uint32_t *kmax, uint32_t n_pairs,
+                             uint32_t groups, uint32_t k, hipStream_t s) {
+    if (n_pairs == 0 || groups == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_batch_dice, dim3(groups), dim3(kThreads), 0, s, (const Args *)pairs, offs, kmax, n_pairs, k);
+    return hipGetLastError();
+}
+
+}  // namespace smc

@@ -54,17 +54,19 @@ struct ScoreLaunch {
     int layout;               // SourceLayout
     int pt;                   // particles per workgroup: 4, 8 or 16
     int zchunk;               // target z-extent of a tile (0 = up to 256)
-    // masks: cull to the source mask's bounding box (exact for a and c only;
-    // n and b_ov then count only the tiles that reach it)
-    bool cull_box;
-    int32_t box_lo[3], box_hi[3];
-    const uint32_t *src_bits = nullptr;  // mask: bitmap of the source's on bits (the filter's launches)
-    // mask, culled launches: summed-area table of the source's occupied cells
-    // (or nullptr: the bounding box alone)
-    const uint32_t *occ = nullptr;
-    // mask, culled item-list launches (or nullptr): kWorkSlots counter pairs,
+    // masks: only a and c are needed (the filter's launches), by blocks of the
+    // target on the source's distance field (dice.hip); false: all four counts
+    bool ac = false;
+    struct Dice {
+        const uint32_t *bits = nullptr;  // source bitmap
+        const uint8_t *field = nullptr;  // source distance field
+        const void *t4 = nullptr;        // target blocks of 4^3, 8^3 and 16^3 voxels
+        const uint32_t *t8 = nullptr, *t16 = nullptr;
+    } dice;
+    // masks, ac launches (or nullptr): kWorkSlots counter triples,
     // kWorkSlotWords apart; summed over the slots, word 0 counts the particle x
-    // voxel pairs evaluated, word 1 the pairs covered (the culled ones included)
+    // voxel pairs sampled, word 1 the pairs covered (the decided ones
+    // included), word 2 the sampled pairs of blocks inside the source
     unsigned long long *work = nullptr;
     const uint8_t *src_ok;    // image: corner-valid bytes (source FOV) or nullptr
     const uint8_t *tgt;       // mask: prepared bits; image: intensities
@@ -76,14 +78,7 @@ struct ScoreLaunch {
     // mutual information: the launch adds into kMiBins^2 counts per particle
     // (indexed like words) instead of the moments
     uint32_t *hist = nullptr;
-    // masks, the filter's launches: the culled item lists (capacity item_cap
-    // items of 8 bytes) and their counters (kItemCounterWords 32-bit words);
-    // launches with more items than item_cap use a grid of one workgroup per item
-    void *items = nullptr;
-    uint32_t *item_counters = nullptr;
-    uint64_t item_cap = 0;
 };
-constexpr uint32_t kItemCounterWords = 512;
 // Most work items (tiles x particle groups) one scoring launch takes: a grid
 // dimension of signed 32-bit size.
 constexpr uint64_t kMaxScoreItems = 0x7FFFFFFFull;
@@ -126,11 +121,6 @@ struct BatchPlan {
     // item queues: 8 counters (one per XCD list) per iteration, zero before
     // the run; iteration k uses counters[8 (k - 1) .. 8 k)
     uint32_t *counters;
-    // masks: per iteration a cull pre-pass appends the live items (item id,
-    // particle mask) of list x to live[list_off[x] ..), counted in
-    // live_counts[kItemCounterWords / 2 (k - 1) + 32 x] (zero before the run)
-    void *live = nullptr;
-    uint32_t *live_counts = nullptr;
 };
 size_t score_args_bytes();
 uint32_t score_items(const ScoreLaunch &L);
@@ -144,21 +134,26 @@ int score_vmode(const ScoreLaunch &L);
 
 // Preparation of inputs.
 hipError_t launch_prep_mask(const uint8_t *vol, const uint8_t *fov, uint8_t *out, int64_t n, hipStream_t s);
-// Bounding box of the voxels with bit 1 set (mask on): out = {min x, y, z, max x, y, z};
-// initialise out to {INT_MAX x3, -1 x3}.
-hipError_t launch_mask_bbox(const uint8_t *prep, const int32_t n[3], int32_t *out, hipStream_t s);
-// Bitmap of the prepared source mask's "on" bits (rows padded to 32 bits):
-// bytes of the bitmap of a volume of shape n, and the packing launch.
-uint64_t mask_bits_bytes(const int32_t n[3]);
-hipError_t launch_pack_mask_bits(const uint8_t *prep, const int32_t n[3], uint32_t *out, hipStream_t s);
-// Occupancy of the prepared source mask's "on" bits over cells of
-// 2^kOccShift voxels a side, as a summed-area table with a zero first row,
-// column and slice: words of the table, and the building launches.
-constexpr int kOccShift = 1;
-constexpr uint64_t kOccMaxWords = 16ull << 20;  // 64 MB
 constexpr uint32_t kWorkSlots = 64, kWorkSlotWords = 16;
-uint64_t mask_occ_words(const int32_t n[3]);
-hipError_t launch_mask_occupancy(const uint8_t *prep, const int32_t n[3], uint32_t *sat, hipStream_t s);
+// Device bytes of the structures of the filter's mask launches (dice.hip);
+// gap_x and gap_y are scratch of launch_dice_source.
+struct DiceSizes {
+    uint64_t bits, field, gap_x, gap_y, t4, t8, t16;
+};
+DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]);
+hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
+                              uint16_t *gap_y, uint8_t *field, hipStream_t s);
+hipError_t launch_dice_target(const uint8_t *prep, const int32_t n[3], void *t4, uint32_t *t8, uint32_t *t16,
+                              hipStream_t s);
+hipError_t launch_dice(const ScoreLaunch &L, hipStream_t s);
+hipError_t launch_dice_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s);
+// A batch's mask pairs: kernel arguments of a pair (its workgroups are
+// returned), and one launch over the workgroups of all pairs (offs, prefix
+// sums; pairs whose kmax is below k are done).
+size_t dice_args_bytes();
+uint64_t dice_args(const ScoreLaunch &L, void *out);
+hipError_t launch_batch_dice(const void *pairs, const uint32_t *offs, const uint32_t *kmax, uint32_t n_pairs,
+                             uint32_t groups, uint32_t k, hipStream_t s);
 hipError_t launch_corner_valid(const uint8_t *fov, uint8_t *out, const int32_t n[3], hipStream_t s);
 // out[0..3] += (fov count, nonzero count, sum v, sum v^2) over the FOV
 hipError_t launch_volume_sums(const uint8_t *vol, const uint8_t *fov, int64_t n, unsigned long long *out,

@@ -35,18 +35,6 @@ static_assert(kWX == 16, "a wave's four quarters are 4 x 4 squares side by side 
 constexpr int kWaves = kThreads / 64;
 constexpr int kZChunkMax = 256;  // keeps every per-thread 32-bit sum below 2^32
 constexpr int kSlab = 32;        // target slices staged in LDS at a time
-constexpr uint32_t kItemChunk = 4;  // items a persistent workgroup takes at a time
-// An item's second word: bit p for each live particle p (PT <= 16), and bit
-// kInteriorBit when every live particle's image of the tile lies inside the
-// source, so the scoring kernel can skip the per-sample inside test.
-constexpr uint32_t kInteriorBit = 16;
-// Bits 17..21 and 22..26: slices at the bottom and at the top of the item's
-// tile that no live particle's image can sample an occupied source cell
-// from (the pre-pass tests the tile's runs of kSpanSlices slices); the
-// scoring kernel skips them.  Zero: the whole tile.  Only tiles of at most
-// kSpanMaxDepth slices are trimmed.
-constexpr uint32_t kSpanLoBit = 17, kSpanHiBit = 22, kSpanMask = 31;
-constexpr int kSpanSlices = 4, kSpanMaxDepth = 32;
 
 struct KArgs {
     const uint8_t *src, *src_ok, *tgt, *tgt_fov;
@@ -59,12 +47,6 @@ struct KArgs {
     // exact culling: a particle can add to the sums of a tile only if the
     // tile's image reaches the source-coordinate box [cull_lo, cull_hi]
     float cull_lo[3], cull_hi[3];
-    // masks, culled launches: and only if a source voxel the image can sample
-    // is on: summed-area table of occupied cells (nullptr: not used), its row
-    // and slice strides, and the largest voxel index per axis
-    const uint32_t *occ;
-    uint32_t ocx, ocxy;
-    float occ_hi[3];
     // source FOV validity of a trilinear sample: 0 none, 1 gather src_ok,
     // 2 packed elements equal to `sentinel` mark samples outside the FOV
     int32_t vmode;
@@ -183,84 +165,18 @@ __device__ __forceinline__ void box_centre(const int lo[3], const int hi[3], flo
 }
 
 // Whether the image of the box (centre c, half extents h) under the recipe
-// words w can meet the cull box and, for masks with an occupancy table, can
-// sample an occupied cell: the image's voxel indices (the nearest-neighbour
-// words carry the +0.5, so a sample's index is the floor of its coordinate)
-// lie in [floor(uc - r), floor(uc + r)] per axis; clipped to the source and
-// taken to cells, the table's inclusion-exclusion count over that cell box is
-// the number of occupied cells it holds.  None occupied: every sample reads an
-// off bit and adds nothing to a or c.
+// words w can meet the cull box.
 template <typename P>
 __device__ __forceinline__ bool box_reaches(P w, const float c[3], const float h[3], const KArgs &a) {
     bool ok = true;
-    int32_t lo[3], hi[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const float uc = fmaf(w[4 * d + 2], c[2], fmaf(w[4 * d + 1], c[1], fmaf(w[4 * d], c[0], w[4 * d + 3])));
         const float r = fmaf(fabsf(w[4 * d + 2]), h[2], fmaf(fabsf(w[4 * d + 1]), h[1], fabsf(w[4 * d]) * h[0])) +
                         kCullMargin;
         ok = ok && uc + r >= a.cull_lo[d] && uc - r <= a.cull_hi[d];
-        lo[d] = (int32_t)floorf(fmaxf(uc - r, 0.0f));
-        hi[d] = (int32_t)floorf(fminf(uc + r, a.occ_hi[d]));
-    }
-    if (ok && a.occ) {
-        if (lo[0] > hi[0] || lo[1] > hi[1] || lo[2] > hi[2]) return false;
-        const uint32_t x0 = (uint32_t)lo[0] >> kOccShift, x1 = ((uint32_t)hi[0] >> kOccShift) + 1u;
-        const uint32_t y0 = ((uint32_t)lo[1] >> kOccShift) * a.ocx, y1 = (((uint32_t)hi[1] >> kOccShift) + 1u) * a.ocx;
-        const uint32_t z0 = ((uint32_t)lo[2] >> kOccShift) * a.ocxy,
-                       z1 = (((uint32_t)hi[2] >> kOccShift) + 1u) * a.ocxy;
-        const uint32_t *S = a.occ;
-        const uint32_t n = S[z1 + y1 + x1] - S[z0 + y1 + x1] - S[z1 + y0 + x1] - S[z1 + y1 + x0] +
-                           S[z0 + y0 + x1] + S[z0 + y1 + x0] + S[z1 + y0 + x0] - S[z0 + y0 + x0];
-        ok = n != 0u;
     }
     return ok;
-}
-
-// Whether every sample of the box's image under the nearest-neighbour words w
-// lies inside the source (0 <= u < n per axis), by the same bound.
-template <typename P>
-__device__ __forceinline__ bool box_inside(P w, const float c[3], const float h[3], const KArgs &a) {
-    const float n[3] = {(float)a.sn0, (float)a.sn1, (float)a.sn2};
-    bool in = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const float uc = fmaf(w[4 * d + 2], c[2], fmaf(w[4 * d + 1], c[1], fmaf(w[4 * d], c[0], w[4 * d + 3])));
-        const float r = fmaf(fabsf(w[4 * d + 2]), h[2], fmaf(fabsf(w[4 * d + 1]), h[1], fabsf(w[4 * d]) * h[0])) +
-                        kCullMargin;
-        in = in && uc - r >= 0.0f && uc + r < n[d];
-    }
-    return in;
-}
-
-// The slices of the bottom and top runs (kSpanSlices each) of the tile box
-// [lo, hi] that no live particle (bits of live; words w of particles 0 ..
-// npg - 1) can sample an occupied cell from, by box_reaches on each run's
-// box.  When no run is reached, live becomes 0.  Tiles deeper than
-// kSpanMaxDepth are left whole.
-template <typename P>
-__device__ __forceinline__ void trim_span(const KArgs &a, P w, uint32_t npg, const int lo[3], const int hi[3],
-                                          uint32_t &live, int &skip_lo, int &skip_hi) {
-    const int depth = hi[2] - lo[2] + 1;
-    skip_lo = skip_hi = 0;
-    if (!live || depth <= kSpanSlices || depth > kSpanMaxDepth) return;
-    const auto run_reaches = [&](int r0, int r1) {
-        const int rl[3] = {lo[0], lo[1], lo[2] + r0}, rh[3] = {hi[0], hi[1], lo[2] + r1};
-        float rc[3], rhh[3];
-        box_centre(rl, rh, rc, rhh);
-        bool any = false;
-        for (uint32_t p = 0; p < npg && !any; ++p) any = ((live >> p) & 1u) && box_reaches(w + 12 * p, rc, rhh, a);
-        return any;
-    };
-    while (skip_lo < depth && !run_reaches(skip_lo, min(skip_lo + kSpanSlices, depth) - 1)) skip_lo += kSpanSlices;
-    if (skip_lo >= depth) {
-        live = 0u;  // no run reaches an occupied cell: nothing of the tile can count
-        skip_lo = 0;
-        return;
-    }
-    int top = depth;  // runs from the top: [top - kSpanSlices, top)
-    while (top - kSpanSlices > skip_lo && !run_reaches(top - kSpanSlices, top - 1)) top -= kSpanSlices;
-    skip_hi = depth - top;
 }
 
 template <int PT>
@@ -324,39 +240,13 @@ __device__ __forceinline__ uint32_t mad_u24v(uint32_t a, uint32_t b, uint32_t c)
 // Target byte: bit 0 = inside the target FOV, bit 1 = mask on (and in FOV).
 // Per particle two packed counters: acc1 = n | a << 16, acc2 = b_ov | c << 16
 // (each half counts at most one voxel per z step, and a z-chunk < 2^16).
-// AC: only a and c (what Dice uses; the filter's launches), from the source
-// bitmap (one bit per voxel, the "on" bit; rows of ceil(nx / 32) dwords):
-// the sample is bit x % 32 of a dword, and one packed counter per particle
-// takes a + 2^16 c as bit * (in-FOV + 2^16 on) of the target voxel.  The
-// bitmap puts the rows of a slice 4 ceil(nx / 32) bytes apart, so the rotated
-// footprint of a wave's samples spans a few cache lines instead of one or two
-// per source row and slice as with a byte per voxel.
-// staged (or nullptr): the key of the tile whose target slab the LDS holds,
-// kept by a persistent workgroup across its items; an item whose tile has
-// that key (tile_key: unique per tile among the workgroup's items) and fits
-// one slab reuses the slab instead of staging it again.
-template <int PT, bool AC = false, bool GIVEN = false>
-__device__ __forceinline__ void mask_body(const KArgs &a, uint32_t bx, uint32_t by, uint32_t live_in = 0u,
-                                          uint32_t *staged = nullptr, uint32_t tile_key = 0u) {
+template <int PT>
+__device__ __forceinline__ void mask_body(const KArgs &a, uint32_t bx, uint32_t by) {
     const Tile t = tile_of<PT>(a, bx, by);
-    // GIVEN: the cull pre-pass already tested this item (live_in != 0)
-    const uint32_t live = GIVEN ? live_in : live_mask<PT>(a, t, bx);
-    if (live == 0u) return;  // nothing of this tile can reach the source region
+    const uint32_t live = live_mask<PT>(a, t, bx);
+    if (live == 0u) return;  // nothing of this tile can reach the source
     float mx[PT], my[PT], mz[PT], ax[PT], ay[PT], az[PT];
     column_terms<PT>(a, t, mx, my, mz, ax, ay, az);
-    // interior (bit kInteriorBit of a pre-pass item): every sample of the
-    // live particles lies inside the source, so the inside test is dropped;
-    // the other particle slots are pointed at slice n_z, whose offset
-    // (n_z times the slice stride) is the bitmap's end, where loads read zero
-    const bool interior = GIVEN && AC && ((live_in >> kInteriorBit) & 1u) != 0u;
-    if (interior) {
-#pragma unroll
-        for (int p = 0; p < PT; ++p)
-            if (!((live >> p) & 1u)) {
-                ax[p] = ay[p] = az[p] = mx[p] = my[p] = 0.0f;
-                mz[p] = (float)a.sn2;
-            }
-    }
     if constexpr (PT > 4) {
         // the per-particle slopes are uniform; with many particles they would
         // crowd the scalar registers out (and be spilled to vector lanes)
@@ -369,11 +259,10 @@ __device__ __forceinline__ void mask_body(const KArgs &a, uint32_t bx, uint32_t 
     {
         // prepared source bytes through a bounds-checked buffer with 32-bit
         // offsets: an outside sample may form any offset, its result is masked
-        const uint32_t sn0 = AC ? a.ysb : (uint32_t)a.sn0, sn01 = AC ? a.zsb : (uint32_t)a.sn0 * (uint32_t)a.sn1;
-        const int nbytes = AC ? (int)a.src_bytes : a.sn0 * a.sn1 * a.sn2;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            AC ? const_cast<void *>(a.src_packed) : (void *)const_cast<uint8_t *>(a.src), (short)0, nbytes,
-            kBufferWord3);
+        const uint32_t sn0 = (uint32_t)a.sn0, sn01 = (uint32_t)a.sn0 * (uint32_t)a.sn1;
+        const int nbytes = a.sn0 * a.sn1 * a.sn2;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void *)const_cast<uint8_t *>(a.src), (short)0, nbytes, kBufferWord3);
         // nearest (the words carry +0.5): inside iff 0 <= u < n, one unsigned
         // compare of bit patterns per axis (coordinates are never -0)
         const uint32_t nxb = __float_as_uint((float)a.sn0), nyb = __float_as_uint((float)a.sn1),
@@ -383,34 +272,19 @@ __device__ __forceinline__ void mask_body(const KArgs &a, uint32_t bx, uint32_t 
         __shared__ uint32_t tslab[kSlab * kThreads / 4];
         const uint8_t *tslab8 = (const uint8_t *)tslab;
         const uint32_t col = (uint32_t)(t.j - t.y0) * kTX + (uint32_t)(t.i - t.x0);
-        const bool one_slab = t.k1 - t.k0 <= kSlab;
-        // a pre-pass item's span: the slices of the tile some live particle
-        // can sample an occupied cell from (the whole tile otherwise)
-        const int kbeg = GIVEN ? t.k0 + (int)((live_in >> kSpanLoBit) & kSpanMask) : t.k0;
-        const int kend = GIVEN ? t.k1 - (int)((live_in >> kSpanHiBit) & kSpanMask) : t.k1;
         for (int kb = t.k0; kb < t.k1; kb += kSlab) {
             const int ke = min(kb + kSlab, t.k1);
-            if (!(staged && one_slab && *staged == tile_key)) {
-                __syncthreads();  // every thread is done with the previous slab
-                stage_target(a, t, kb, ke, rs_t, rs_t, false, tslab, tslab);
-                __syncthreads();
-                if (staged) *staged = one_slab ? tile_key : 0xFFFFFFFFu;
-            } else {
-                __syncthreads();  // the previous item's reduction slots are read
-            }
+            __syncthreads();  // every thread is done with the previous slab
+            stage_target(a, t, kb, ke, rs_t, rs_t, false, tslab, tslab);
+            __syncthreads();
             if (!t.ok) continue;
-            const auto slices = [&](auto interior_tag) {
-            constexpr bool INTERIOR = decltype(interior_tag)::value;
-            for (int k = max(kb, kbeg); k < min(ke, kend); ++k) {
+            for (int k = kb; k < ke; ++k) {
                 const uint32_t tb = tslab8[(uint32_t)(k - kb) * kThreads + col];
                 const uint32_t keep = (tb & 1u) ? 3u : 0u;
                 const bool ton = (tb & 2u) != 0u;
-                // AC: a source bit adds 1 to a where the target voxel is in its
-                // FOV and 2^16 to c where it is on (bit 1 implies bit 0)
-                const uint32_t tmul = (tb & 1u) + ((tb & 2u) << 15);
                 const float fk = (float)k;
                 // offsets of all PT samples first, then every load, then the sums
-                uint32_t off[PT], ix[PT];
+                uint32_t off[PT];
 #pragma unroll
                 for (int p = 0; p < PT; ++p) {
                     const float ux = fmaf(ax[p], fk, mx[p]);
@@ -420,54 +294,34 @@ __device__ __forceinline__ void mask_body(const KArgs &a, uint32_t bx, uint32_t 
                     // outside samples (and particles culled for this tile) load
                     // from the buffer's end: zero, no cache lines touched, so they
                     // count nothing
-                    if constexpr (AC) {
-                        // byte offset of dword x / 32 of the row; the bit index is
-                        // x % 32 (the low five bits of the offset operand)
-                        ix[p] = floor_u32(ux);
-                        off[p] = mad_u24(floor_u32(uz), sn01, mad_u24(floor_u32(uy), sn0, (ix[p] >> 3) & ~3u));
-                    } else {
-                        off[p] = mad_u24(floor_u32(uz), sn01, mad_u24(floor_u32(uy), sn0, floor_u32(ux)));
-                    }
-                    if constexpr (!INTERIOR) {
-                        const bool in = ((live >> p) & 1u) & (__float_as_uint(ux) < nxb) &
-                                        (__float_as_uint(uy) < nyb) & (__float_as_uint(uz) < nzb);
-                        off[p] = in ? off[p] : nbytes;
-                    }
+                    off[p] = mad_u24(floor_u32(uz), sn01, mad_u24(floor_u32(uy), sn0, floor_u32(ux)));
+                    const bool in = ((live >> p) & 1u) & (__float_as_uint(ux) < nxb) & (__float_as_uint(uy) < nyb) &
+                                    (__float_as_uint(uz) < nzb);
+                    off[p] = in ? off[p] : nbytes;
                 }
                 uint32_t val[PT];
 #pragma unroll
-                for (int p = 0; p < PT; ++p)
-                    val[p] = AC ? __builtin_amdgcn_raw_buffer_load_b32(rs, off[p], 0, 0)
-                                : __builtin_amdgcn_raw_buffer_load_b8(rs, off[p], 0, 0);
+                for (int p = 0; p < PT; ++p) val[p] = __builtin_amdgcn_raw_buffer_load_b8(rs, off[p], 0, 0);
 #pragma unroll
                 for (int p = 0; p < PT; ++p) {
-                    if constexpr (AC) {
-                        acc1[p] = mad_u24v(__builtin_amdgcn_ubfe(val[p], ix[p], 1u), tmul, acc1[p]);
-                    } else {
-                        // v in 0..3 (bit 0 in both FOVs, bit 1 also on); inc = (v & 1) +
-                        // (v >> 1) 2^16 = v + (v >> 1) (2^16 - 2)
-                        const uint32_t v = val[p] & keep;
-                        const uint32_t inc = mad_u24v(v >> 1, 65534u, v);
-                        acc1[p] += inc;
-                        acc2[p] += ton ? inc : 0u;
-                    }
+                    // v in 0..3 (bit 0 in both FOVs, bit 1 also on); inc = (v & 1) +
+                    // (v >> 1) 2^16 = v + (v >> 1) (2^16 - 2)
+                    const uint32_t v = val[p] & keep;
+                    const uint32_t inc = mad_u24v(v >> 1, 65534u, v);
+                    acc1[p] += inc;
+                    acc2[p] += ton ? inc : 0u;
                 }
             }
-            };
-            if (interior) slices(std::true_type{});
-            else slices(std::false_type{});
         }
     }
     __shared__ unsigned long long red[kWaves][PT][4];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
 #pragma unroll
     for (int p = 0; p < PT; ++p) {
-        // AC: a wave's halves stay below 64 x 256 < 2^16, so one sum serves both
-        const uint32_t ac = AC ? wave_sum(acc1[p]) : 0u;
-        const uint32_t n = AC ? 0u : wave_sum(acc1[p] & 0xFFFFu);
-        const uint32_t aa = AC ? ac & 0xFFFFu : wave_sum(acc1[p] >> 16);
-        const uint32_t b = AC ? 0u : wave_sum(acc2[p] & 0xFFFFu);
-        const uint32_t c = AC ? ac >> 16 : wave_sum(acc2[p] >> 16);
+        const uint32_t n = wave_sum(acc1[p] & 0xFFFFu);
+        const uint32_t aa = wave_sum(acc1[p] >> 16);
+        const uint32_t b = wave_sum(acc2[p] & 0xFFFFu);
+        const uint32_t c = wave_sum(acc2[p] >> 16);
         if (lane == 0) {
             red[wave][p][0] = n;
             red[wave][p][1] = aa;
@@ -1002,11 +856,11 @@ __device__ __forceinline__ void xcd_order(uint32_t b, uint32_t total, uint32_t g
     *by = w - *bx * groups;
 }
 
-template <int PT, bool AC>
+template <int PT>
 __global__ __launch_bounds__(kThreads) void k_score_mask(const KArgs a) {
     uint32_t bx, by;
     xcd_order(blockIdx.x, gridDim.x, (a.np + PT - 1) / PT, &bx, &by);
-    mask_body<PT, AC>(a, bx, by);
+    mask_body<PT>(a, bx, by);
 }
 
 // The octet variants with four particles per workgroup fit 72 VGPRs without
@@ -1023,133 +877,6 @@ void k_score_image(const KArgs a) {
     uint32_t bx, by;
     xcd_order(blockIdx.x, gridDim.x, (a.np + PT - 1) / PT, &bx, &by);
     image_body<PT, LAYOUT, TRI, VMODE, ACC>(a, bx, by);
-}
-
-// ---------------------------------------------------------------- culled item lists
-
-// Most (tile, particle group) items of a filter's mask launch cannot reach
-// the source mask's bounding box (a concentrated cloud maps most tiles
-// outside it).  Instead of a grid of one workgroup per item, most of which
-// would only run the cull test and leave, a pre-pass tests every item on its
-// own lane and appends the live ones, with their masks, to eight lists --
-// list x holds the live items of the x-th contiguous eighth of the item
-// sequence, the part the XCD-aware grid gives XCD x -- and a persistent grid
-// takes items from its XCD's list through an atomic counter, then helps the
-// other lists.  Sums are integer additions, so the result does not depend on
-// which workgroup takes which item.  An item whose live particles all map the
-// tile inside the source (by the cull's bound) is marked interior, and its
-// samples skip the inside test: three compares and a select per sample.  The
-// pre-pass also tests the tile's bottom and top runs of kSpanSlices slices
-// with the same bound and trims those no live particle reaches.
-constexpr uint32_t kListStride = 32;  // counter words 128 bytes apart
-
-__device__ __forceinline__ uint32_t list_begin(uint32_t total, uint32_t x) {
-    const uint32_t q = total / 8u, rem = total % 8u;
-    return x * q + min(x, rem);
-}
-
-// work (or nullptr): adds the particle x voxel pairs of the live particles of
-// the items (evaluated), of all their particles (covered) and of the live
-// particles of interior items (interior), one atomic per count and wave into
-// one of kWorkSlots counter triples (each on its own cache line, so the waves'
-// atomics do not queue on one address).
-template <int PT>
-__global__ __launch_bounds__(256) void k_cull_items(const KArgs a, uint32_t total, uint2 *items, uint32_t *counts,
-                                                    unsigned long long *work) {
-    static_assert(PT <= (int)kInteriorBit, "particle bits below the interior bit");
-    const uint32_t w = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t groups = (a.np + PT - 1) / PT;
-    uint32_t live = 0u, x = 0u;
-    unsigned long long evaluated = 0ull, covered = 0ull, interior = 0ull;
-    if (w < total) {
-        const uint32_t bx = w / groups, by = w - bx * groups;
-        const int tiles = a.tiles_x * a.tiles_y;
-        const int zc = (int)bx / tiles, b = (int)bx - zc * tiles;
-        const int ty = b / a.tiles_x, tx = b - ty * a.tiles_x;
-        const int k0 = zc * a.zchunk;
-        const int lo[3] = {tx * kTX, ty * kTY, k0};
-        const int hi[3] = {min(tx * kTX + kTX - 1, a.tn0 - 1), min(ty * kTY + kTY - 1, a.tn1 - 1),
-                           min(k0 + a.zchunk, a.tn2) - 1};
-        float c[3], h[3];
-        box_centre(lo, hi, c, h);
-        const uint32_t pbase = a.p0 + by * PT, npg = min((uint32_t)PT, a.p0 + a.np - pbase);
-        bool inside = true;
-        for (uint32_t p = 0; p < npg; ++p)
-            if (box_reaches(a.words + 12 * (size_t)(pbase + p), c, h, a)) {
-                live |= 1u << p;
-                inside = inside && box_inside(a.words + 12 * (size_t)(pbase + p), c, h, a);
-            }
-        while (x < 7u && w >= list_begin(total, x + 1u)) ++x;
-        const int depth = hi[2] - lo[2] + 1;
-        const unsigned long long area = (unsigned long long)(hi[0] - lo[0] + 1) * (unsigned long long)(hi[1] - lo[1] + 1);
-        covered = (unsigned long long)npg * area * depth;
-        int skip_lo = 0, skip_hi = 0;
-        trim_span(a, a.words + 12 * (size_t)pbase, npg, lo, hi, live, skip_lo, skip_hi);
-        evaluated = (unsigned long long)__popc(live) * area * (unsigned long long)(depth - skip_lo - skip_hi);
-        if (live && inside) {
-            live |= 1u << kInteriorBit;
-            interior = evaluated;
-        }
-        if (live) live |= ((uint32_t)skip_lo << kSpanLoBit) | ((uint32_t)skip_hi << kSpanHiBit);
-    }
-    const uint32_t lane = threadIdx.x % 64u;
-    if (work) {
-        evaluated = wave_sum(evaluated);
-        covered = wave_sum(covered);
-        interior = wave_sum(interior);
-        if (lane == 0u) {
-            unsigned long long *slot = work + kWorkSlotWords * ((blockIdx.x * 4u + threadIdx.x / 64u) % kWorkSlots);
-            atomicAdd(slot, evaluated);
-            atomicAdd(slot + 1, covered);
-            atomicAdd(slot + 2, interior);
-        }
-    }
-    // one atomic per wave when all its lanes fall in one list (the usual case)
-    const uint32_t x0 = __shfl(x, 0);
-    const bool one_list = __all(x == x0);
-    const uint64_t m = __ballot(live != 0u);
-    if (one_list) {
-        if (m == 0ull) return;
-        uint32_t base = 0u;
-        if (lane == 0u) base = atomicAdd(counts + x0 * kListStride, (uint32_t)__popcll(m));
-        base = __shfl(base, 0);
-        if (live) {
-            const uint32_t rank = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            items[list_begin(total, x0) + base + rank] = make_uint2(w, live);
-        }
-    } else if (live) {
-        const uint32_t pos = atomicAdd(counts + x * kListStride, 1u);
-        items[list_begin(total, x) + pos] = make_uint2(w, live);
-    }
-}
-
-template <int PT>
-__global__ __launch_bounds__(kThreads) void k_score_mask_items(const KArgs a, const uint2 *items,
-                                                               const uint32_t *counts, uint32_t *take,
-                                                               uint32_t total) {
-    __shared__ uint32_t next_item;
-    const uint32_t groups = (a.np + PT - 1) / PT;
-    uint32_t staged = 0xFFFFFFFFu;  // tile whose target slab the LDS holds (none yet)
-    for (uint32_t s = 0; s < 8; ++s) {
-        const uint32_t x = (blockIdx.x + s) % 8u;
-        const uint32_t begin = list_begin(total, x), n_items = counts[x * kListStride];
-        for (;;) {
-            // kItemChunk consecutive items at a time: the pre-pass appends a
-            // wave's items (mostly of one tile) together
-            if (threadIdx.x == 0) next_item = atomicAdd(take + x * kListStride, kItemChunk);
-            __syncthreads();
-            const uint32_t r0 = next_item;
-            if (r0 >= n_items) break;
-            const uint32_t r1 = min(r0 + kItemChunk, n_items);
-            for (uint32_t r = r0; r < r1; ++r) {
-                const uint2 it = items[begin + r];
-                const uint32_t bx = it.x / groups, by = it.x - bx * groups;
-                mask_body<PT, true, true>(a, bx, by, it.y, &staged, bx);
-            }
-            __syncthreads();  // next_item is read by all before thread 0 takes the next
-        }
-        __syncthreads();  // the same before the next list's first take
-    }
 }
 
 // ---------------------------------------------------------------- batches
@@ -1185,9 +912,8 @@ __device__ __forceinline__ uint32_t pair_of(const uint32_t *offs_g, uint32_t n, 
     return lo;
 }
 
-template <int PT, int MODE, int LAYOUT, int VMODE>
-__global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(MODE == kModeMask ? 1 : kImageWaves<PT, LAYOUT, VMODE, 0>)))
+template <int PT, int LAYOUT, int VMODE>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kImageWaves<PT, LAYOUT, VMODE, 0>)))
 void k_batch_score(const BatchArgs b) {
     const auto *lists = as_const(b.lists);
     const auto *kmax = as_const(b.kmax);
@@ -1211,102 +937,7 @@ void k_batch_score(const BatchArgs b) {
                 const uint32_t local = g - b.offs[d];
                 const uint32_t ng = (a.np + PT - 1) / PT;
                 const uint32_t bx = local / ng, by = local - bx * ng;
-                if (MODE == kModeMask) mask_body<PT, true>(a, bx, by);  // the filter's launches
-                else image_body<PT, LAYOUT, true, VMODE>(a, bx, by);
-            }
-            __syncthreads();  // next_item is read by all before thread 0 takes the next
-        }
-        __syncthreads();  // the same before the next list's first take
-    }
-}
-
-// Mask classes: the live items of an iteration.  One thread per entry of the
-// class's XCD lists tests its (tile, particle group) item against its pair's
-// source mask box and appends live items, with their particle masks, interior
-// bits and slice spans, to the same list's part of `live` (one atomic per wave where
-// all its lanes are in one list); pairs past their last iteration add nothing.
-template <int PT>
-__global__ __launch_bounds__(256) void k_batch_cull(const BatchArgs b, uint2 *live, uint32_t *counts) {
-    static_assert(PT <= (int)kInteriorBit, "particle bits below the interior bit");
-    const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t total = b.list_off[8];
-    uint32_t lm = 0u, x = 0u, g = 0u;
-    if (e < total) {
-        while (x < 7u && e >= b.list_off[x + 1]) ++x;
-        g = b.lists[e];
-        const uint32_t d = pair_of(b.offs, b.n_pairs, g);
-        if (b.kmax[d] >= b.k) {
-            const KArgs &a = b.pairs[d];
-            const uint32_t local = g - b.offs[d];
-            const uint32_t groups = (a.np + PT - 1) / PT;
-            const uint32_t bx = local / groups, by = local - bx * groups;
-            const int tiles = a.tiles_x * a.tiles_y;
-            const int zc = (int)bx / tiles, tb = (int)bx - zc * tiles;
-            const int ty = tb / a.tiles_x, tx = tb - ty * a.tiles_x;
-            const int k0 = zc * a.zchunk;
-            const int lo[3] = {tx * kTX, ty * kTY, k0};
-            const int hi[3] = {min(tx * kTX + kTX - 1, a.tn0 - 1), min(ty * kTY + kTY - 1, a.tn1 - 1),
-                               min(k0 + a.zchunk, a.tn2) - 1};
-            float c[3], h[3];
-            box_centre(lo, hi, c, h);
-            const uint32_t pbase = a.p0 + by * PT, npg = min((uint32_t)PT, a.p0 + a.np - pbase);
-            bool inside = true;
-            for (uint32_t p = 0; p < npg; ++p)
-                if (box_reaches(a.words + 12 * (size_t)(pbase + p), c, h, a)) {
-                    lm |= 1u << p;
-                    inside = inside && box_inside(a.words + 12 * (size_t)(pbase + p), c, h, a);
-                }
-            int skip_lo = 0, skip_hi = 0;
-            trim_span(a, a.words + 12 * (size_t)pbase, npg, lo, hi, lm, skip_lo, skip_hi);
-            if (lm && inside) lm |= 1u << kInteriorBit;
-            if (lm) lm |= ((uint32_t)skip_lo << kSpanLoBit) | ((uint32_t)skip_hi << kSpanHiBit);
-        }
-    }
-    const uint32_t lane = threadIdx.x % 64u;
-    const uint32_t x0 = __shfl(x, 0);
-    const bool one_list = __all(x == x0);
-    const uint64_t m = __ballot(lm != 0u);
-    if (one_list) {
-        if (m == 0ull) return;
-        uint32_t base = 0u;
-        if (lane == 0u) base = atomicAdd(counts + x0 * kListStride, (uint32_t)__popcll(m));
-        base = __shfl(base, 0);
-        if (lm) {
-            const uint32_t rank = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            live[b.list_off[x0] + base + rank] = make_uint2(g, lm);
-        }
-    } else if (lm) {
-        const uint32_t pos = atomicAdd(counts + x * kListStride, 1u);
-        live[b.list_off[x] + pos] = make_uint2(g, lm);
-    }
-}
-
-// The mask class's persistent warp-and-score over the live items of one
-// iteration: list x first (its XCD's), then the others, as k_batch_score.
-template <int PT>
-__global__ __launch_bounds__(kThreads) void k_batch_mask_items(const BatchArgs b, const uint2 *live,
-                                                               const uint32_t *counts) {
-    const auto *pairs = as_const(b.pairs);
-    __shared__ uint32_t next_item;
-    // key of the tile whose target slab the LDS holds: the batch-wide index of
-    // the tile's first item (none yet)
-    uint32_t staged = 0xFFFFFFFFu;
-    for (uint32_t s = 0; s < 8; ++s) {
-        const uint32_t x = (blockIdx.x + s) % 8;
-        const uint32_t begin = b.list_off[x], n_items = counts[x * kListStride];
-        for (;;) {
-            if (threadIdx.x == 0) next_item = atomicAdd(b.counters + x, kItemChunk);
-            __syncthreads();
-            const uint32_t r0 = next_item;
-            if (r0 >= n_items) break;
-            for (uint32_t r = r0; r < min(r0 + kItemChunk, n_items); ++r) {
-                const uint2 it = live[begin + r];
-                const uint32_t d = pair_of(b.offs, b.n_pairs, it.x);
-                const KArgs a = pairs[d];
-                const uint32_t local = it.x - b.offs[d];
-                const uint32_t ng = (a.np + PT - 1) / PT;
-                const uint32_t bx = local / ng, by = local - bx * ng;
-                mask_body<PT, true, true>(a, bx, by, it.y, &staged, it.x - by);
+                image_body<PT, LAYOUT, true, VMODE>(a, bx, by);
             }
             __syncthreads();  // next_item is read by all before thread 0 takes the next
         }
@@ -1334,12 +965,6 @@ KArgs make_args(const ScoreLaunch &L, int pt, int *nz_chunks) {
     a.tn2 = L.tn[2];
     a.p0 = L.p0;
     a.np = L.np;
-    // occupancy culling: masks' culled launches with a table
-    const bool occ = L.mode == kModeMask && L.cull_box && L.occ;
-    a.occ = occ ? L.occ : nullptr;
-    a.ocx = (uint32_t)((L.sn[0] + (1 << kOccShift) - 1) >> kOccShift) + 1u;
-    a.ocxy = a.ocx * ((uint32_t)((L.sn[1] + (1 << kOccShift) - 1) >> kOccShift) + 1u);
-    for (int d = 0; d < 3; ++d) a.occ_hi[d] = (float)(L.sn[d] - 1);
     a.tiles_x = (L.tn[0] + kTX - 1) / kTX;
     a.tiles_y = (L.tn[1] + kTY - 1) / kTY;
     const int zc = L.zchunk > 0 ? std::min(L.zchunk, kZChunkMax) : kZChunkMax;
@@ -1350,10 +975,6 @@ KArgs make_args(const ScoreLaunch &L, int pt, int *nz_chunks) {
             // inside iff 0 <= u <= n - 1
             a.cull_lo[d] = 0.0f;
             a.cull_hi[d] = (float)(L.sn[d] - 1);
-        } else if (L.mode == kModeMask && L.cull_box) {
-            // only samples landing in the source mask's bounding box add to a, c
-            a.cull_lo[d] = (float)L.box_lo[d];
-            a.cull_hi[d] = (float)(L.box_hi[d] + 1);
         } else {
             // nearest (words carry +0.5): inside iff 0 <= u < n
             a.cull_lo[d] = 0.0f;
@@ -1361,13 +982,7 @@ KArgs make_args(const ScoreLaunch &L, int pt, int *nz_chunks) {
         }
     }
     if (L.mode == kModeMask) {
-        // the filter's launches read the source bitmap: byte strides of its
-        // rows and slices (zero without a bitmap; those launches use bytes)
-        const uint32_t row = 4u * (uint32_t)((L.sn[0] + 31) / 32);
-        a.src_packed = L.src_bits;
-        a.src_bytes = L.src_bits ? (uint32_t)mask_bits_bytes(L.sn) : 0u;
-        a.ysb = row;
-        a.zsb = row * (uint32_t)L.sn[1];
+        a.src_bytes = a.ysb = a.zsb = 0u;
         *nz_chunks = chunks;
         return a;
     }
@@ -1409,7 +1024,7 @@ ScoreKernel pick_tri_layout(int layout, int vmode) {
 
 template <int PT>
 ScoreKernel pick(const ScoreLaunch &L) {
-    if (L.mode == kModeMask) return L.cull_box && L.src_bits ? k_score_mask<PT, true> : k_score_mask<PT, false>;
+    if (L.mode == kModeMask) return k_score_mask<PT>;
     const bool sok = L.src_ok != nullptr;
     if (L.mode == kModeImageNearest)
         return sok ? k_score_image<PT, kLayoutRaw, false, 1> : k_score_image<PT, kLayoutRaw, false, 0>;
@@ -1449,16 +1064,15 @@ ScoreKernel pick_batch_image(int vmode) {
     typedef void (*BK)(const BatchArgs);
     BK k;
     if constexpr (LAYOUT != kLayoutRaw) {
-        if (vmode == 2) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, kModeImageTrilinear, LAYOUT, 2>);
+        if (vmode == 2) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, LAYOUT, 2>);
     }
-    if (vmode != 0) k = k_batch_score<PT, kModeImageTrilinear, LAYOUT, 1>;
-    else k = k_batch_score<PT, kModeImageTrilinear, LAYOUT, 0>;
+    if (vmode != 0) k = k_batch_score<PT, LAYOUT, 1>;
+    else k = k_batch_score<PT, LAYOUT, 0>;
     return reinterpret_cast<ScoreKernel>(k);
 }
 
 template <int PT>
-ScoreKernel pick_batch(int mode, int layout, int vmode) {
-    if (mode == kModeMask) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, kModeMask, kLayoutRaw, 0>);
+ScoreKernel pick_batch(int layout, int vmode) {
     switch (layout) {
     case kLayoutPairX: return pick_batch_image<PT, kLayoutPairX>(vmode);
     case kLayoutQuadXY: return pick_batch_image<PT, kLayoutQuadXY>(vmode);
@@ -1471,12 +1085,13 @@ ScoreKernel pick_batch(int mode, int layout, int vmode) {
 
 template <int PT>
 ScoreKernel pick_batch_pt(const BatchPlan &P) {
-    return pick_batch<PT>(P.mode, P.layout, P.vmode);
+    return pick_batch<PT>(P.layout, P.vmode);
 }
 }  // namespace
 
 hipError_t launch_batch_score(const BatchPlan &P, uint32_t k, hipStream_t s) {
     if (P.n_pairs == 0) return hipSuccess;
+    if (P.mode == kModeMask) return launch_batch_dice(P.pairs, P.offs, P.kmax, P.n_pairs, P.grid, k, s);
     BatchArgs b;
     b.pairs = (const KArgs *)P.pairs;
     b.offs = P.offs;
@@ -1486,28 +1101,6 @@ hipError_t launch_batch_score(const BatchPlan &P, uint32_t k, hipStream_t s) {
     b.n_pairs = P.n_pairs;
     b.k = k;
     b.counters = P.counters + 8ull * (k - 1);
-    if (P.mode == kModeMask && P.live && P.live_counts) {
-        const int pt = score_pt_supported(P.pt) ? P.pt : 8;
-        uint32_t *counts = P.live_counts + (uint64_t)(kItemCounterWords / 2) * (k - 1);
-        const uint32_t total = P.list_off[8];
-        const dim3 cg((total + 255u) / 256u);
-        if (total == 0) return hipSuccess;
-        if (pt == 4) hipLaunchKernelGGL(k_batch_cull<4>, cg, dim3(256), 0, s, b, (uint2 *)P.live, counts);
-        else if (pt == 16) hipLaunchKernelGGL(k_batch_cull<16>, cg, dim3(256), 0, s, b, (uint2 *)P.live, counts);
-        else hipLaunchKernelGGL(k_batch_cull<8>, cg, dim3(256), 0, s, b, (uint2 *)P.live, counts);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        if (pt == 4)
-            hipLaunchKernelGGL(k_batch_mask_items<4>, dim3(P.grid), dim3(kThreads), 0, s, b, (const uint2 *)P.live,
-                               (const uint32_t *)counts);
-        else if (pt == 16)
-            hipLaunchKernelGGL(k_batch_mask_items<16>, dim3(P.grid), dim3(kThreads), 0, s, b, (const uint2 *)P.live,
-                               (const uint32_t *)counts);
-        else
-            hipLaunchKernelGGL(k_batch_mask_items<8>, dim3(P.grid), dim3(kThreads), 0, s, b, (const uint2 *)P.live,
-                               (const uint32_t *)counts);
-        return hipGetLastError();
-    }
     typedef void (*BK)(const BatchArgs);
     BK kern = reinterpret_cast<BK>(const_cast<void *>(batch_kernel(P)));
     hipLaunchKernelGGL(kern, dim3(P.grid), dim3(kThreads), 0, s, b);
@@ -1516,11 +1109,6 @@ hipError_t launch_batch_score(const BatchPlan &P, uint32_t k, hipStream_t s) {
 
 const void *batch_kernel(const BatchPlan &P) {
     const int pt = score_pt_supported(P.pt) ? P.pt : 8;
-    if (P.mode == kModeMask && P.live) {
-        if (pt == 4) return reinterpret_cast<const void *>(k_batch_mask_items<4>);
-        if (pt == 16) return reinterpret_cast<const void *>(k_batch_mask_items<16>);
-        return reinterpret_cast<const void *>(k_batch_mask_items<8>);
-    }
     if (pt == 4) return reinterpret_cast<const void *>(pick_batch_pt<4>(P));
     if (pt == 16) return reinterpret_cast<const void *>(pick_batch_pt<16>(P));
     return reinterpret_cast<const void *>(pick_batch_pt<8>(P));
@@ -1555,80 +1143,17 @@ void score_grid(const ScoreLaunch &L, dim3 *grid, dim3 *block) {
     *block = dim3(kThreads, 1, 1);
 }
 
-namespace {
-
-template <int PT>
-__global__ __launch_bounds__(kThreads) void k_probe_mask_items(const KArgs a, const uint2 *items,
-                                                               const uint32_t *counts, uint32_t *take,
-                                                               uint32_t total, uint32_t key, uint32_t *out);
-
-// Resident workgroups of a persistent kernel on the current device (cached
-// per device and kernel; the occupancy query is made once).
-int persistent_blocks(const void *kernel) {
-    static std::mutex mu;
-    static std::map<std::pair<int, const void *>, int> cache;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-    std::lock_guard<std::mutex> lk(mu);
-    const auto key = std::make_pair(dev, kernel);
-    const auto it = cache.find(key);
-    if (it != cache.end()) return it->second;
-    int cus = 0, per_cu = 0;
-    if (dev < 0 || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess || per_cu < 1)
-        per_cu = 4;
-    return cache[key] = cus * per_cu;
-}
-
-template <int PT>
-hipError_t launch_mask_items_pt(const KArgs &a, uint32_t total, const ScoreLaunch &L, bool probe, uint32_t key,
-                                uint32_t *out, hipStream_t s) {
-    static_assert(kItemCounterWords == 16 * kListStride, "counts and takes, eight each");
-    uint32_t *counts = L.item_counters, *take = L.item_counters + 8 * kListStride;
-    hipError_t e = launch_fill_u64((unsigned long long *)L.item_counters, kItemCounterWords / 2, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cull_items<PT>, dim3((total + 255u) / 256u), dim3(256), 0, s, a, total, (uint2 *)L.items,
-                       counts, probe ? nullptr : L.work);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (probe) {
-        const int blocks = persistent_blocks(reinterpret_cast<const void *>(k_probe_mask_items<PT>));
-        hipLaunchKernelGGL(k_probe_mask_items<PT>, dim3(blocks), dim3(kThreads), 0, s, a, (const uint2 *)L.items,
-                           (const uint32_t *)counts, take, total, key, out);
-    } else {
-        const int blocks = persistent_blocks(reinterpret_cast<const void *>(k_score_mask_items<PT>));
-        hipLaunchKernelGGL(k_score_mask_items<PT>, dim3(blocks), dim3(kThreads), 0, s, a, (const uint2 *)L.items,
-                           (const uint32_t *)counts, take, total);
-    }
-    return hipGetLastError();
-}
-
-// The filter's mask launches through the culled item lists, when the
-// context provides lists large enough for this launch.
-bool uses_item_lists(const ScoreLaunch &L, uint64_t total) {
-    return L.mode == kModeMask && L.cull_box && L.src_bits && L.items && L.item_counters && total <= L.item_cap;
-}
-
-hipError_t launch_mask_items(const ScoreLaunch &L, int pt, const KArgs &a, uint32_t total, bool probe, uint32_t key,
-                             uint32_t *out, hipStream_t s) {
-    if (pt == 4) return launch_mask_items_pt<4>(a, total, L, probe, key, out, s);
-    if (pt == 16) return launch_mask_items_pt<16>(a, total, L, probe, key, out, s);
-    return launch_mask_items_pt<8>(a, total, L, probe, key, out, s);
-}
-
-}  // namespace
-
 uint64_t score_items_for(const ScoreLaunch &L) { return score_items64(L); }
 
 hipError_t launch_score(const ScoreLaunch &L, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
+    if (L.mode == kModeMask && L.ac) return launch_dice(L, s);
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
     dim3 grid, block;
     score_grid(L, &grid, &block);
     if (grid.x == 0) return hipErrorInvalidConfiguration;
-    if (uses_item_lists(L, grid.x)) return launch_mask_items(L, pt, a, grid.x, false, 0u, nullptr, s);
     ScoreKernel k = pt == 4 ? pick<4>(L) : (pt == 16 ? pick<16>(L) : pick<8>(L));
     hipLaunchKernelGGL(k, grid, block, 0, s, a);
     return hipGetLastError();
@@ -1644,63 +1169,6 @@ hipError_t launch_score(const ScoreLaunch &L, hipStream_t s) {
 // gathers alone cost on that set.  The checksum is stored only if it equals a
 // key the host never passes, which keeps every load live.
 namespace {
-
-template <int PT, bool AC, bool GIVEN = false>
-__device__ __forceinline__ uint32_t probe_mask_body(const KArgs &a, uint32_t bx, uint32_t by, uint32_t live_in = 0u) {
-    const Tile t = tile_of<PT>(a, bx, by);
-    const uint32_t live = GIVEN ? live_in : live_mask<PT>(a, t, bx);
-    uint32_t chk = 0u;
-    if (live == 0u || !t.ok) return chk;
-    float mx[PT], my[PT], mz[PT], ax[PT], ay[PT], az[PT];
-    column_terms<PT>(a, t, mx, my, mz, ax, ay, az);
-    const uint32_t sn0 = AC ? a.ysb : (uint32_t)a.sn0, sn01 = AC ? a.zsb : (uint32_t)a.sn0 * (uint32_t)a.sn1;
-    const int nbytes = AC ? (int)a.src_bytes : a.sn0 * a.sn1 * a.sn2;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        AC ? const_cast<void *>(a.src_packed) : (void *)const_cast<uint8_t *>(a.src), (short)0, nbytes,
-        kBufferWord3);
-    const uint32_t nxb = __float_as_uint((float)a.sn0), nyb = __float_as_uint((float)a.sn1),
-                   nzb = __float_as_uint((float)a.sn2);
-    // the scoring kernel's interior items, as there
-    const bool interior = GIVEN && AC && ((live_in >> kInteriorBit) & 1u) != 0u;
-    if (interior) {
-#pragma unroll
-        for (int p = 0; p < PT; ++p)
-            if (!((live >> p) & 1u)) {
-                ax[p] = ay[p] = az[p] = mx[p] = my[p] = 0.0f;
-                mz[p] = (float)a.sn2;
-            }
-    }
-    // the scoring kernel's item spans, as there
-    const int kbeg = GIVEN ? t.k0 + (int)((live_in >> kSpanLoBit) & kSpanMask) : t.k0;
-    const int kend = GIVEN ? t.k1 - (int)((live_in >> kSpanHiBit) & kSpanMask) : t.k1;
-    const auto slices = [&](auto interior_tag) {
-        constexpr bool INTERIOR = decltype(interior_tag)::value;
-        for (int k = kbeg; k < kend; ++k) {
-            const float fk = (float)k;
-            uint32_t off[PT];
-#pragma unroll
-            for (int p = 0; p < PT; ++p) {
-                const float ux = fmaf(ax[p], fk, mx[p]);
-                const float uy = fmaf(ay[p], fk, my[p]);
-                const float uz = fmaf(az[p], fk, mz[p]);
-                const uint32_t xo = AC ? (floor_u32(ux) >> 3) & ~3u : floor_u32(ux);
-                off[p] = mad_u24(floor_u32(uz), sn01, mad_u24(floor_u32(uy), sn0, xo));
-                if constexpr (!INTERIOR) {
-                    const bool in = ((live >> p) & 1u) & (__float_as_uint(ux) < nxb) &
-                                    (__float_as_uint(uy) < nyb) & (__float_as_uint(uz) < nzb);
-                    off[p] = in ? off[p] : (uint32_t)nbytes;
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < PT; ++p)
-                chk ^= AC ? __builtin_amdgcn_raw_buffer_load_b32(rs, off[p], 0, 0)
-                          : __builtin_amdgcn_raw_buffer_load_b8(rs, off[p], 0, 0);
-        }
-    };
-    if (interior) slices(std::true_type{});
-    else slices(std::false_type{});
-    return chk;
-}
 
 // Trilinear images in the one-gather layouts (octets, tiled octets, lerp
 // elements), the layouts the filter's launches use.
@@ -1751,39 +1219,11 @@ __device__ __forceinline__ uint32_t probe_image_body(const KArgs &a, uint32_t bx
     return chk;
 }
 
-template <int PT, int MODE, int LAYOUT, bool AC = false>
+template <int PT, int LAYOUT>
 __global__ __launch_bounds__(kThreads) void k_gather_probe(const KArgs a, uint32_t key, uint32_t *out) {
     uint32_t bx, by;
     xcd_order(blockIdx.x, gridDim.x, (a.np + PT - 1) / PT, &bx, &by);
-    const uint32_t chk =
-        MODE == kModeMask ? probe_mask_body<PT, AC>(a, bx, by) : probe_image_body<PT, LAYOUT>(a, bx, by);
-    if (chk == key) out[0] = chk;
-}
-
-template <int PT>
-__global__ __launch_bounds__(kThreads) void k_probe_mask_items(const KArgs a, const uint2 *items,
-                                                               const uint32_t *counts, uint32_t *take,
-                                                               uint32_t total, uint32_t key, uint32_t *out) {
-    __shared__ uint32_t next_item;
-    const uint32_t groups = (a.np + PT - 1) / PT;
-    uint32_t chk = 0u;
-    for (uint32_t s = 0; s < 8; ++s) {
-        const uint32_t x = (blockIdx.x + s) % 8u;
-        const uint32_t begin = list_begin(total, x), n_items = counts[x * kListStride];
-        for (;;) {
-            if (threadIdx.x == 0) next_item = atomicAdd(take + x * kListStride, kItemChunk);
-            __syncthreads();
-            const uint32_t r0 = next_item;
-            if (r0 >= n_items) break;
-            for (uint32_t r = r0; r < min(r0 + kItemChunk, n_items); ++r) {
-                const uint2 it = items[begin + r];
-                const uint32_t bx = it.x / groups, by = it.x - bx * groups;
-                chk ^= probe_mask_body<PT, true, true>(a, bx, by, it.y);
-            }
-            __syncthreads();
-        }
-        __syncthreads();
-    }
+    const uint32_t chk = probe_image_body<PT, LAYOUT>(a, bx, by);
     if (chk == key) out[0] = chk;
 }
 
@@ -1791,15 +1231,9 @@ template <int PT>
 ScoreKernel probe_kernel(const ScoreLaunch &L) {
     typedef void (*PK)(const KArgs, uint32_t, uint32_t *);
     PK k = nullptr;
-    if (L.mode == kModeMask)
-        k = L.cull_box && L.src_bits ? k_gather_probe<PT, kModeMask, kLayoutRaw, true>
-                                     : k_gather_probe<PT, kModeMask, kLayoutRaw, false>;
-    else if (L.mode == kModeImageTrilinear && L.layout == kLayoutOct)
-        k = k_gather_probe<PT, kModeImageTrilinear, kLayoutOct>;
-    else if (L.mode == kModeImageTrilinear && L.layout == kLayoutOctTile)
-        k = k_gather_probe<PT, kModeImageTrilinear, kLayoutOctTile>;
-    else if (L.mode == kModeImageTrilinear && L.layout == kLayoutLerp)
-        k = k_gather_probe<PT, kModeImageTrilinear, kLayoutLerp>;
+    if (L.layout == kLayoutOct) k = k_gather_probe<PT, kLayoutOct>;
+    else if (L.layout == kLayoutOctTile) k = k_gather_probe<PT, kLayoutOctTile>;
+    else if (L.layout == kLayoutLerp) k = k_gather_probe<PT, kLayoutLerp>;
     return reinterpret_cast<ScoreKernel>(k);
 }
 
@@ -1807,7 +1241,7 @@ ScoreKernel probe_kernel(const ScoreLaunch &L) {
 
 bool gather_probe_supported(const ScoreLaunch &L) {
     if (L.tgt_fov != nullptr || L.hist != nullptr) return false;
-    if (L.mode == kModeMask) return true;
+    if (L.mode == kModeMask) return L.ac;
     return L.mode == kModeImageTrilinear &&
            (L.layout == kLayoutOct || L.layout == kLayoutOctTile || L.layout == kLayoutLerp);
 }
@@ -1815,14 +1249,13 @@ bool gather_probe_supported(const ScoreLaunch &L) {
 hipError_t launch_gather_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s) {
     if (!gather_probe_supported(L)) return hipErrorInvalidValue;
     if (L.np == 0) return hipSuccess;
+    if (L.mode == kModeMask) return launch_dice_probe(L, key, out, s);
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
     dim3 grid, block;
     score_grid(L, &grid, &block);
     if (grid.x == 0) return hipErrorInvalidConfiguration;
-    // the same schedule as the production launch (culled item lists or grid)
-    if (uses_item_lists(L, grid.x)) return launch_mask_items(L, pt, a, grid.x, true, key, out, s);
     ScoreKernel k = pt == 4 ? probe_kernel<4>(L) : (pt == 16 ? probe_kernel<16>(L) : probe_kernel<8>(L));
     typedef void (*PK)(const KArgs, uint32_t, uint32_t *);
     hipLaunchKernelGGL(reinterpret_cast<PK>(k), grid, block, 0, s, a, key, out);
