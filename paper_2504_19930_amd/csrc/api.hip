@@ -1685,27 +1685,25 @@ smc_status smc_cnn_create(smc_cnn **out, uint32_t max_batch, void *hip_stream) {
     };
     if ((st = n->alloc(&c.params, c.n_params)) != SMC_OK || (st = n->alloc(&c.grads, c.n_params)) != SMC_OK ||
         (st = n->alloc(&c.adam_m, c.n_params)) != SMC_OK || (st = n->alloc(&c.adam_v, c.n_params)) != SMC_OK ||
-        (st = n->alloc(&c.wbf16, cnn_param_offset(8))) != SMC_OK ||
         (st = n->alloc(&n->input, 2 * side3 * max_batch)) != SMC_OK ||
         (st = n->alloc(&n->out, 12ull * max_batch)) != SMC_OK ||
         (st = n->alloc(&n->target, 12ull * max_batch)) != SMC_OK || (st = n->alloc(&n->loss, 4)) != SMC_OK ||
-        (st = n->alloc(&c.dout, 12ull * max_batch)) != SMC_OK ||
-        (st = n->alloc(&c.partial, (size_t)cnn_partial_floats((int)max_batch))) != SMC_OK)
+        (st = n->alloc(&c.dout, 12ull * max_batch)) != SMC_OK)
         return bail(st);
-    c.partial_cap = cnn_partial_floats((int)max_batch);
-    for (int L = 0; L < 4; ++L) {
-        const size_t d = (size_t)(kCnnSide >> (L + 1));
-        const size_t elems = (size_t)max_batch * kCnnChannels[L + 1] * d * d * d;
-        if ((st = n->alloc(&c.act[L], elems)) != SMC_OK || (st = n->alloc(&c.dact[L], elems)) != SMC_OK)
+    const CnnSizes z = cnn_sizes((int)max_batch);
+    if ((st = n->alloc(&c.wpart, z.wpart)) != SMC_OK || (st = n->alloc(&c.bpart, z.bpart)) != SMC_OK) return bail(st);
+    for (int L = 0; L < 4; ++L)
+        if ((st = n->alloc(&c.wf[L], z.wf[L])) != SMC_OK || (st = n->alloc(&c.wd[L], z.wd[L])) != SMC_OK ||
+            (st = n->alloc(&c.act[L], z.act[L])) != SMC_OK || (st = n->alloc(&c.xs[L], z.xs[L])) != SMC_OK ||
+            (st = n->alloc(&c.dyf[L], z.dyf[L])) != SMC_OK || (st = n->alloc(&c.dyl[L], z.dyl[L])) != SMC_OK)
             return bail(st);
-    }
     std::vector<float> zeros((size_t)c.n_params, 0.0f);
     if (hipMemcpy(c.params, zeros.data(), 4 * c.n_params, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c.adam_m, zeros.data(), 4 * c.n_params, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c.adam_v, zeros.data(), 4 * c.n_params, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c.grads, zeros.data(), 4 * c.n_params, hipMemcpyHostToDevice) != hipSuccess)
         return bail(fail(SMC_EDEVICE, "parameter initialisation failed"));
-    if (cnn_refresh_bf16(c, n->stream) != hipSuccess || hipStreamSynchronize(n->stream) != hipSuccess)
+    if (cnn_prepare(c, (int)max_batch, n->stream) != hipSuccess || hipStreamSynchronize(n->stream) != hipSuccess)
         return bail(fail(SMC_EDEVICE, "parameter initialisation failed"));
     *out = n;
     return SMC_OK;
@@ -1743,8 +1741,7 @@ smc_status smc_cnn_input(smc_cnn *n, uint32_t slot, const smc_volume *src, const
     if ((st = check_volume(src, "src")) != SMC_OK || (st = check_volume(tgt, "tgt")) != SMC_OK) return st;
     const size_t side3 = (size_t)kCnnSide * kCnnSide * kCnnSide;
     const int32_t sn[3] = {src->nx, src->ny, src->nz}, tn[3] = {tgt->nx, tgt->ny, tgt->nz};
-    HIP_TRY(cnn_downsample(src->data, sn, scale, n->input + 2 * side3 * slot, n->stream));
-    HIP_TRY(cnn_downsample(tgt->data, tn, scale, n->input + 2 * side3 * slot + side3, n->stream));
+    HIP_TRY(cnn_downsample(src->data, sn, tgt->data, tn, scale, n->input + 2 * side3 * slot, n->stream));
     return SMC_OK;
 }
 
@@ -1760,7 +1757,7 @@ smc_status smc_cnn_read_input(smc_cnn *n, uint32_t slot, uint16_t *host) {
 smc_status smc_cnn_forward(smc_cnn *n, uint32_t B, float *out_host) {
     if (!n || !out_host) return fail(SMC_EINVAL, "net and out must not be NULL");
     if (B < 1 || B > n->max_batch) return fail(SMC_EINVAL, "batch %u outside 1..%u", B, n->max_batch);
-    HIP_TRY(cnn_forward(n->c, n->input, (int)B, n->out, n->stream));
+    HIP_TRY(cnn_forward(n->c, n->input, (int)B, n->out, false, n->stream));
     HIP_TRY(hipMemcpyAsync(out_host, n->out, 48ull * B, hipMemcpyDeviceToHost, n->stream));
     HIP_TRY(hipStreamSynchronize(n->stream));
     return SMC_OK;
@@ -1773,7 +1770,7 @@ smc_status smc_cnn_backward(smc_cnn *n, uint32_t B, const float *target_host, fl
         if (!isfinite(target_host[q]) || (q % 12 >= 6 && target_host[q] < 0.0f))
             return fail(SMC_EINVAL, "target %zu must be finite (variances non-negative)", q);
     HIP_TRY(hipMemcpyAsync(n->target, target_host, 48ull * B, hipMemcpyHostToDevice, n->stream));
-    HIP_TRY(cnn_forward(n->c, n->input, (int)B, n->out, n->stream));
+    HIP_TRY(cnn_forward(n->c, n->input, (int)B, n->out, true, n->stream));
     HIP_TRY(cnn_backward(n->c, n->input, (int)B, n->out, n->target, n->loss, n->stream));
     float l = 0.0f;
     HIP_TRY(hipMemcpyAsync(&l, n->loss, 4, hipMemcpyDeviceToHost, n->stream));

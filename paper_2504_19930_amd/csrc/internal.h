@@ -219,20 +219,29 @@ extern const int kCnnSide;
 extern const int kCnnFlat;
 struct CnnBuffers {
     float *params;       // FP32 master weights (flat; layout in smc.h)
-    uint16_t *wbf16;     // bfloat16 copy of the convolution part
     float *grads, *adam_m, *adam_v;
     int64_t n_params;
-    uint16_t *act[4];    // layer outputs after ReLU, bfloat16
-    float *dact[4];      // gradients w.r.t. layer pre-activations
-    float *dout;         // B x 12
-    float *partial;      // split-K partial tiles of the forward convolutions
-    int64_t partial_cap; // floats in partial
+    // bfloat16 copies of the convolution weights and tensors per layer, in the
+    // orders that cnn.hip describes
+    uint16_t *wf[4], *wd[4];    // weights of the forward and of the data gradient
+    uint16_t *act[4];           // outputs after ReLU: channels last; the last layer's channels first
+    uint16_t *xs[4];            // inputs, split (training)
+    uint16_t *dyf[4], *dyl[4];  // gradients of the pre-activations, channels first and last
+    float *dout;                // B x 12
+    float *wpart, *bpart;       // partial weight and bias gradients
 };
-// Floats of the forward split-K buffer a network of max_batch pairs needs.
-int64_t cnn_partial_floats(int max_batch);
+// Elements of the buffers of a network of up to max_batch pairs.
+struct CnnSizes {
+    size_t wf[4], wd[4], act[4], xs[4], dyf[4], dyl[4], wpart, bpart;
+};
+CnnSizes cnn_sizes(int max_batch);
+// Clear what stays zero and pack the weights of params.
+hipError_t cnn_prepare(const CnnBuffers &c, int max_batch, hipStream_t s);
 int64_t cnn_param_offset(int part);
-hipError_t cnn_downsample(const uint8_t *vol, const int32_t n[3], float scale, uint16_t *out, hipStream_t s);
-hipError_t cnn_forward(const CnnBuffers &c, const uint16_t *input, int B, float *out, hipStream_t s);
+hipError_t cnn_downsample(const uint8_t *src, const int32_t sn[3], const uint8_t *tgt, const int32_t tn[3], float scale,
+                          uint16_t *out, hipStream_t s);
+// train: also keep what cnn_backward reads
+hipError_t cnn_forward(const CnnBuffers &c, const uint16_t *input, int B, float *out, bool train, hipStream_t s);
 hipError_t cnn_backward(const CnnBuffers &c, const uint16_t *input, int B, const float *out, const float *target,
                         float *loss_dev, hipStream_t s);
 hipError_t cnn_adam(const CnnBuffers &c, float lr, int t, hipStream_t s);
