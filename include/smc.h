@@ -222,8 +222,8 @@ smc_status smc_set_frames(smc_ctx *ctx, uint32_t n_extra, const smc_volume *src_
  * slices per tile, 1 .. 256 (a tile is 32 x 8 x tile_depth voxels; shallower
  * tiles cull more exactly -- a tile whose image cannot reach the source is
  * skipped -- at the cost of more partial sums).  The filter's mask launches
- * use neither (they decide blocks of the target by the source's distance
- * field); smc_evaluate on masks does.  A negative value keeps the current setting.  Defaults
+ * and, on sources with a FOV, the layouts of one gather (3, 4 and 5) use
+ * neither: they decide blocks of the target by a distance field of the source.  A negative value keeps the current setting.  Defaults
  * come from measurements on MI355X: 4 particles per group; tile depth 16 for
  * masks and 256 for images.  A packed layout addresses its source
  * with 32-bit offsets: SMC_EINVAL if the packed source reaches 4 GiB or one

@@ -158,6 +158,7 @@ struct smc_ctx {
     const uint8_t *src = nullptr, *src_fov = nullptr, *tgt = nullptr, *tgt_fov = nullptr;
     uint8_t *src_prep = nullptr, *tgt_prep = nullptr, *src_ok = nullptr;
     ScoreLaunch::Dice dice;  // masks: structures of the filter's launches
+    ScoreLaunch::Tri tri;    // trilinear images with a source FOV: structures of the block launches
     int layout = kDefaultLayout, pt = kDefaultPT, zchunk = kDefaultZChunkMask;
     unsigned long long *work = nullptr;  // masks: pairs sampled and covered by the filter's launches
     void *packed[kLayouts] = {};
@@ -233,6 +234,7 @@ struct smc_ctx {
             L.tgt_fov = nullptr;
         } else {
             L.src = src;
+            L.tri = tri;
             L.src_ok = src_ok;
             L.tgt = tgt;
             L.tgt_fov = tgt_fov;
@@ -511,6 +513,28 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         } else {
             c->src_ok = const_cast<uint8_t *>(src->fov);
         }
+    }
+
+    if (c->src_ok && c->mode == kModeImageTrilinear) {
+        const TriSizes ts = tri_sizes(c->sn, c->tn);
+        uint8_t *may, *must, *gap_x, *gap_y, *field, *tz, *fz = nullptr, *t4, *t8, *t16;
+        if ((st = c->alloc(&may, ts.bits)) != SMC_OK || (st = c->alloc(&must, ts.bits)) != SMC_OK ||
+            (st = c->alloc(&gap_x, ts.gap)) != SMC_OK || (st = c->alloc(&gap_y, ts.gap)) != SMC_OK ||
+            (st = c->alloc(&field, ts.field)) != SMC_OK || (st = c->alloc(&tz, ts.tz)) != SMC_OK ||
+            (tgt->fov && (st = c->alloc(&fz, ts.tz)) != SMC_OK) || (st = c->alloc(&t4, ts.t4)) != SMC_OK ||
+            (st = c->alloc(&t8, ts.t8)) != SMC_OK || (st = c->alloc(&t16, ts.t16)) != SMC_OK)
+            return bail(st);
+        c->tri.field = field;
+        c->tri.tz = (const uint32_t *)tz;
+        c->tri.fz = (const uint32_t *)fz;
+        c->tri.t4 = t4;
+        c->tri.t8 = t8;
+        c->tri.t16 = t16;
+        if (launch_tri_source(c->src_ok, c->sn, (uint32_t *)may, (uint32_t *)must, (uint16_t *)gap_x, (uint16_t *)gap_y,
+                              field, c->stream) != hipSuccess ||
+            launch_tri_target(tgt->data, tgt->fov, c->tn, (uint32_t *)tz, (uint32_t *)fz, t4, t8, t16, c->stream) !=
+                hipSuccess)
+            return bail(fail(SMC_EDEVICE, "image preparation launch failed"));
     }
 
     if (!layout_fits(c->layout, c->sn)) c->layout = layout_fits(kLayoutOct, c->sn) ? kLayoutOct : kLayoutRaw;
@@ -1301,10 +1325,8 @@ int device_cus() {
 smc_status plan_class(smc_batch *b, smc_batch::Class &C, int vmode) {
     const uint32_t n = (uint32_t)C.members.size();
     C.has_first = false;
-    if (n == 0) {
-        C.plan = BatchPlan{};  // an empty class launches nothing (also after a re-plan)
-        return SMC_OK;
-    }
+    C.plan = BatchPlan{};
+    if (n == 0) return SMC_OK;  // an empty class launches nothing (also after a re-plan)
     const size_t ab = score_args_bytes();
     std::vector<uint8_t> args(ab * n);
     std::vector<uint32_t> offs(n + 1, 0), kmax(n);
@@ -1391,33 +1413,30 @@ smc_status plan_class(smc_batch *b, smc_batch::Class &C, int vmode) {
     return SMC_OK;
 }
 
-// The mask class: one launch over the workgroups of all pairs, the largest
-// pairs first.
-smc_status plan_masks(smc_batch *b, smc_batch::Class &C) {
+// A class of block kernels (masks; images in a one-gather layout): one launch
+// over the workgroups of all pairs, the largest pairs first.
+smc_status plan_blocks(smc_batch *b, smc_batch::Class &C, bool masks, int vmode) {
     C.plan = BatchPlan{};
+    C.has_first = false;
     const uint32_t n = (uint32_t)C.members.size();
     if (n == 0) return SMC_OK;
-    const size_t ab = dice_args_bytes();
-    std::vector<uint8_t> one(ab * n), args(ab * n);
-    std::vector<uint64_t> groups(n);
     std::vector<uint32_t> order(n), offs(n + 1, 0), kmax(n);
-    for (uint32_t q = 0; q < n; ++q) {
-        const smc_ctx *c = b->pairs[C.members[q]];
-        groups[q] = dice_args(c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true), one.data() + ab * q);
-        order[q] = q;
-    }
-    const auto voxels = [&](uint32_t q) {
+    for (uint32_t q = 0; q < n; ++q) order[q] = q;
+    const auto pairs = [&](uint32_t q) {
         const smc_ctx *c = b->pairs[C.members[q]];
         return (double)c->tn[0] * c->tn[1] * c->tn[2] * (double)c->f.n;
     };
-    std::sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return voxels(x) > voxels(y); });
+    std::sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return pairs(x) > pairs(y); });
+    const size_t ab = masks ? dice_args_bytes() : tri_args_bytes();
+    std::vector<uint8_t> args(ab * n);
     uint64_t total = 0;
     for (uint32_t q = 0; q < n; ++q) {
-        memcpy(args.data() + ab * q, one.data() + ab * order[q], ab);
-        kmax[q] = b->pairs[C.members[order[q]]]->f.n_iters;
-        total += groups[order[q]];
-        if (total > kMaxScoreItems) return fail(SMC_EINVAL, "the batch's mask pairs exceed one launch");
+        const smc_ctx *c = b->pairs[C.members[order[q]]];
+        const ScoreLaunch L = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true);
+        total += masks ? dice_args(L, args.data() + ab * q) : tri_args(L, args.data() + ab * q);
+        if (total > kMaxScoreItems) return fail(SMC_EINVAL, "the batch's pairs exceed one launch");
         offs[q + 1] = (uint32_t)total;
+        kmax[q] = c->f.n_iters;
     }
     smc_status st;
     if ((st = b->alloc((uint8_t **)&C.args, args.size())) != SMC_OK || (st = b->alloc(&C.offs, n + 1)) != SMC_OK ||
@@ -1426,12 +1445,35 @@ smc_status plan_masks(smc_batch *b, smc_batch::Class &C) {
     HIP_TRY(hipMemcpy(C.args, args.data(), args.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(C.offs, offs.data(), 4 * (n + 1), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(C.kmax, kmax.data(), 4 * n, hipMemcpyHostToDevice));
-    C.plan.mode = kModeMask;
+    C.plan.mode = masks ? kModeMask : kModeImageTrilinear;
+    C.plan.layout = b->pairs[C.members[0]]->layout;
+    C.plan.vmode = vmode;
+    C.plan.blocks = true;
     C.plan.pairs = C.args;
     C.plan.offs = C.offs;
     C.plan.kmax = C.kmax;
     C.plan.n_pairs = n;
     C.plan.grid = (uint32_t)total;
+    if (masks) return SMC_OK;
+    // a first-iteration plan when every pair scores its uniform prior from the
+    // same other layout with the same FOV mode (the same workgroups)
+    int flayout = -1;
+    bool ok = true;
+    for (uint32_t q = 0; q < n && ok; ++q) {
+        const smc_ctx *c = b->pairs[C.members[order[q]]];
+        const ScoreLaunch F = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true, true);
+        if (q == 0) flayout = F.layout;
+        ok = !c->f.has_proposal && F.layout == flayout && F.layout != C.plan.layout && score_vmode(F) == vmode &&
+             tri_supported(F);
+        if (ok) ok = tri_args(F, args.data() + ab * q) == offs[q + 1] - offs[q];
+    }
+    if (!ok) return SMC_OK;
+    if ((st = b->alloc((uint8_t **)&C.fargs, args.size())) != SMC_OK) return st;
+    HIP_TRY(hipMemcpy(C.fargs, args.data(), args.size(), hipMemcpyHostToDevice));
+    C.plan_first = C.plan;
+    C.plan_first.layout = flayout;
+    C.plan_first.pairs = C.fargs;
+    C.has_first = true;
     return SMC_OK;
 }
 
@@ -1460,9 +1502,17 @@ smc_status plan_all(smc_batch *b) {
         b->cls[1 + vm].members.push_back(i);
     }
     smc_status st;
-    if ((st = plan_masks(b, b->cls[0])) != SMC_OK) return st;
-    for (int q = 1; q < 4; ++q)
-        if ((st = plan_class(b, b->cls[q], q - 1)) != SMC_OK) return st;
+    if ((st = plan_blocks(b, b->cls[0], true, 0)) != SMC_OK) return st;
+    for (int q = 1; q < 4; ++q) {
+        // (all pairs of a class share a layout)
+        const auto &m = b->cls[q].members;
+        bool tri = !m.empty();
+        if (tri) {
+            const smc_ctx *c = b->pairs[m[0]];
+            tri = tri_supported(c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true));
+        }
+        if ((st = tri ? plan_blocks(b, b->cls[q], false, q - 1) : plan_class(b, b->cls[q], q - 1)) != SMC_OK) return st;
+    }
     return SMC_OK;
 }
 
@@ -1472,7 +1522,7 @@ smc_status record_run(smc_batch *b) {
     for (smc_ctx *c : b->pairs) HIP_TRY(launch_fill_u64(c->f.sums, 6ull * (c->f.n + 1), b->stream));
     // the item queues start empty on every run (a fill kernel, so graph replays clear them too)
     for (int q = 1; q < 4; ++q)
-        if (b->cls[q].plan.n_pairs)
+        if (b->cls[q].plan.n_pairs && !b->cls[q].plan.blocks)
             HIP_TRY(launch_fill_u64((unsigned long long *)b->cls[q].plan.counters, 4ull * std::max(1u, b->kmax_all),
                                     b->stream));
     for (uint32_t k = 1; k <= b->kmax_all; ++k) {

@@ -42,14 +42,6 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBufferWord3 = 0x00020000;
-// Bound on the partial sums of the recipe below which a sample's and a block
-// centre's FP32 coordinates are each within 0.023 voxel of the exact map, so
-// that kMargin covers both; beyond it every voxel is sampled.
-constexpr float kCoordLimit = 262144.0f;
-constexpr float kMargin = 0.0625f;
-// Field byte: distance in eighths of a voxel (below 16 voxels), state bit.
-constexpr uint32_t kFieldOn = 128u, kFieldDist = 127u;
-constexpr float kFieldUnit = 8.0f;
 constexpr int kWindow = 16;  // voxels searched on either side
 constexpr int kStrip = 16;   // voxels of a line a thread of the field's passes makes
 
@@ -128,36 +120,15 @@ __device__ __forceinline__ uint32_t dice_wave(const A &a, uint32_t part, uint32_
 #pragma unroll
     for (int e = 0; e < 12; ++e) w[e] = wp[e];
 
-    // ball radii: the farthest image of a corner of the unit half-cube
-    float rho2 = 0.0f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        float d2 = 0.0f;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const float v = w[4 * d] + (s & 1 ? w[4 * d + 1] : -w[4 * d + 1]) + (s & 2 ? w[4 * d + 2] : -w[4 * d + 2]);
-            d2 = fmaf(v, v, d2);
-        }
-        rho2 = fmaxf(rho2, d2);
-    }
-    const float rho = sqrtf(rho2);
-    bool bounded = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const float b = fabsf(w[4 * d]) * (float)(a.tn[0] + 16) + fabsf(w[4 * d + 1]) * (float)(a.tn[1] + 16) +
-                        fabsf(w[4 * d + 2]) * (float)(a.tn[2] + 16) + fabsf(w[4 * d + 3]);
-        bounded = bounded && b < kCoordLimit;
-    }
-    // least field distance (in its units) that decides a block of each size
-    const auto threshold = [&](float half) {
-        return bounded ? (uint32_t)fminf(ceilf(kFieldUnit * (half * rho + kMargin)), 255.0f) : 255u;
-    };
-    const uint32_t need16 = threshold(7.5f), need8 = threshold(3.5f), need4 = threshold(1.5f);
+    const float rho = ball_radius(w);
+    const bool bounded = coords_bounded(w, a.tn);
+    const uint32_t need16 = field_need(7.5f, rho, bounded), need8 = field_need(3.5f, rho, bounded),
+                   need4 = field_need(1.5f, rho, bounded);
     // half extents of the image's box of a 32 x 16 x 16 tile
     float rt[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d)
-        rt[d] = fmaf(15.5f, fabsf(w[4 * d]), fmaf(7.5f, fabsf(w[4 * d + 1]), 7.5f * fabsf(w[4 * d + 2]))) + kMargin;
+        rt[d] = fmaf(15.5f, fabsf(w[4 * d]), fmaf(7.5f, fabsf(w[4 * d + 1]), 7.5f * fabsf(w[4 * d + 2]))) + kFieldMargin;
 
     const __amdgpu_buffer_rsrc_t rs_f =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.field), (short)0, (int)a.fbytes, kBufferWord3);
@@ -441,21 +412,25 @@ __global__ __launch_bounds__(256) void k_pack_bits(const uint8_t *prep, int32_t 
 // The field, one axis at a time.  Gaps are whole voxels between two voxels'
 // boxes, 0 where they touch; kWindow and more read as kWindow, and squared
 // distances saturate at 255 (both lower bounds).  Voxels outside the source
-// are off.  Byte pairs hold the distances to the nearest on (low) and off
-// (high) voxel.
+// are off.  Byte pairs hold the distances to the nearest voxel that may be on
+// (low) and that may be off (high).
 //
 // x: gaps along the rows, four voxels a thread.
-__global__ __launch_bounds__(256) void k_field_x(const uint32_t *bits, int32_t nx, uint32_t ny, int64_t rows, uint32_t W,
-                                                 uint16_t *out) {
+__global__ __launch_bounds__(256) void k_field_x(const uint32_t *may, const uint32_t *must, int32_t nx, uint32_t ny,
+                                                 int64_t rows, uint32_t W, uint16_t *out) {
     const int64_t quads = (nx + 3) / 4, n = quads * rows;
     for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
         const int64_t row = q / quads, z = row / ny;
         const int32_t xa = 4 * (int32_t)(q - row * quads), x0 = xa - kWindow;  // first voxel of the window
-        const uint32_t *r = bits + (row - z * ny) + (int64_t)ny * W * z;
+        const int64_t r = (row - z * ny) + (int64_t)ny * W * z;
         const int32_t d = x0 >> 5, s = x0 & 31;
-        const auto word = [&](int32_t e) { return e >= 0 && e < (int32_t)W ? __brev(r[(int64_t)ny * e]) : 0u; };
-        uint64_t m = ((uint64_t)word(d) | ((uint64_t)word(d + 1) << 32)) >> s;
-        if (s) m |= (uint64_t)word(d + 2) << (64 - s);
+        const auto window = [&](const uint32_t *bits) {
+            const auto word = [&](int32_t e) { return e >= 0 && e < (int32_t)W ? __brev(bits[r + (int64_t)ny * e]) : 0u; };
+            uint64_t m = ((uint64_t)word(d) | ((uint64_t)word(d + 1) << 32)) >> s;
+            if (s) m |= (uint64_t)word(d + 2) << (64 - s);
+            return m;
+        };
+        const uint64_t on = window(may), off = ~window(must);
         // kWindow bits to the left of a voxel, its own, kWindow to the right
         const auto gap = [&](uint64_t b) -> uint32_t {
             if ((b >> kWindow) & 1u) return 0u;
@@ -466,7 +441,7 @@ __global__ __launch_bounds__(256) void k_field_x(const uint32_t *bits, int32_t n
             return min(gl, gr);
         };
         for (int j = 0; j < 4 && xa + j < nx; ++j)
-            out[row * nx + xa + j] = (uint16_t)(gap(m >> j) | (gap(~m >> j) << 8));
+            out[row * nx + xa + j] = (uint16_t)(gap(on >> j) | (gap(off >> j) << 8));
     }
 }
 
@@ -643,19 +618,25 @@ DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]) {
     return s;
 }
 
-hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
-                              uint16_t *gap_y, uint8_t *field, hipStream_t s) {
+hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint16_t *gap_x, uint16_t *gap_y,
+                        uint8_t *field, hipStream_t s) {
     const int64_t rows = (int64_t)n[1] * n[2], plane = (int64_t)n[0] * n[1];
-    const uint32_t W = cells(n[0], 32);
-    hipLaunchKernelGGL(k_pack_bits, dim3(blocks_for(W * rows)), dim3(256), 0, s, prep, n[0], (uint32_t)n[1], rows, W,
-                       bits);
-    hipLaunchKernelGGL(k_field_x, dim3(blocks_for((n[0] + 3) / 4 * rows)), dim3(256), 0, s, (const uint32_t *)bits,
-                       n[0], (uint32_t)n[1], rows, W, gap_x);
+    hipLaunchKernelGGL(k_field_x, dim3(blocks_for((n[0] + 3) / 4 * rows)), dim3(256), 0, s, may, must, n[0],
+                       (uint32_t)n[1], rows, cells(n[0], 32), gap_x);
     hipLaunchKernelGGL(k_field_y, dim3(blocks_for(((int64_t)n[1] + kStrip - 1) / kStrip * n[0] * n[2])), dim3(256), 0, s,
                        (const uint16_t *)gap_x, n[0], n[1], n[2], gap_y);
     hipLaunchKernelGGL(k_field_z, dim3(blocks_for(((int64_t)n[2] + kStrip - 1) / kStrip * plane)), dim3(256), 0, s,
                        (const uint16_t *)gap_y, plane, n[2], field);
     return hipGetLastError();
+}
+
+hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
+                              uint16_t *gap_y, uint8_t *field, hipStream_t s) {
+    const int64_t rows = (int64_t)n[1] * n[2];
+    const uint32_t W = cells(n[0], 32);
+    hipLaunchKernelGGL(k_pack_bits, dim3(blocks_for(W * rows)), dim3(256), 0, s, prep, n[0], (uint32_t)n[1], rows, W,
+                       bits);
+    return launch_field(bits, bits, n, gap_x, gap_y, field, s);
 }
 
 hipError_t launch_dice_target(const uint8_t *prep, const int32_t n[3], void *t4, uint32_t *t8, uint32_t *t16,

@@ -25,6 +25,51 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
     return r;
 }
 
+// ---- block tests on a source's distance field (dice.hip, tri.hip)
+//
+// Field byte of a voxel: its state, and the distance (eighths of a voxel, below
+// 16 voxels) from its box to the nearest box of a voxel of the other state; 0
+// where that touches.  The image of a cubic block of target voxels under the
+// recipe lies in a ball about the image of its centre, so a distance of at
+// least the ball's radius decides the block.
+constexpr uint32_t kFieldOn = 128u, kFieldDist = 127u;
+constexpr float kFieldUnit = 8.0f;
+// Bound on the partial sums of the recipe below which a sample's and a block
+// centre's FP32 coordinates are each within 0.023 voxel of the exact map, so
+// that the margin covers both; beyond it no block is decided.
+constexpr float kFieldCoordLimit = 262144.0f, kFieldMargin = 0.0625f;
+
+// Farthest image of a corner of the cube [-1, 1]^3 from its centre's, under
+// recipe words w.
+__device__ __forceinline__ float ball_radius(const float w[12]) {
+    float r2 = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        float d2 = 0.0f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float v = w[4 * d] + (s & 1 ? w[4 * d + 1] : -w[4 * d + 1]) + (s & 2 ? w[4 * d + 2] : -w[4 * d + 2]);
+            d2 = fmaf(v, v, d2);
+        }
+        r2 = fmaxf(r2, d2);
+    }
+    return sqrtf(r2);
+}
+__device__ __forceinline__ bool coords_bounded(const float w[12], const int32_t tn[3]) {
+    bool ok = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const float b = fabsf(w[4 * d]) * (float)(tn[0] + 16) + fabsf(w[4 * d + 1]) * (float)(tn[1] + 16) +
+                        fabsf(w[4 * d + 2]) * (float)(tn[2] + 16) + fabsf(w[4 * d + 3]);
+        ok = ok && b < kFieldCoordLimit;
+    }
+    return ok;
+}
+// Least field distance (in its units) that decides a block of half side `half`.
+__device__ __forceinline__ uint32_t field_need(float half, float radius, bool bounded) {
+    return bounded ? (uint32_t)fminf(ceilf(kFieldUnit * (half * radius + kFieldMargin)), 255.0f) : 255u;
+}
+
 // Warp-and-score launch: particle range [p0, p0 + np) of `words`, sums
 // accumulated (atomically, exactly) into sums[6 * p].
 enum ScoreMode : int { kModeMask = 0, kModeImageTrilinear = 1, kModeImageNearest = 2 };
@@ -63,6 +108,14 @@ struct ScoreLaunch {
         const void *t4 = nullptr;        // target blocks of 4^3, 8^3 and 16^3 voxels
         const uint32_t *t8 = nullptr, *t16 = nullptr;
     } dice;
+    // trilinear images with a source FOV in the one-gather layouts (tri.hip;
+    // nullptr without a FOV): field of the valid
+    // cells, target (and FOV) bytes of four slices as dwords, target blocks
+    struct Tri {
+        const uint8_t *field = nullptr;
+        const uint32_t *tz = nullptr, *fz = nullptr;
+        const void *t4 = nullptr, *t8 = nullptr, *t16 = nullptr;
+    } tri;
     // masks, ac launches (or nullptr): kWorkSlots counter triples,
     // kWorkSlotWords apart; summed over the slots, word 0 counts the particle x
     // voxel pairs sampled, word 1 the pairs covered (the decided ones
@@ -117,7 +170,10 @@ struct BatchPlan {
     const uint32_t *lists;    // item ids grouped by XCD
     uint32_t list_off[9];
     uint32_t n_pairs;
-    uint32_t grid;            // persistent workgroups
+    uint32_t grid;            // workgroups: persistent, or (blocks) offs[n_pairs]
+    // masks and one-gather images: block kernels, pairs holds their arguments
+    // and offs counts workgroups; no queues
+    bool blocks = false;
     // item queues: 8 counters (one per XCD list) per iteration, zero before
     // the run; iteration k uses counters[8 (k - 1) .. 8 k)
     uint32_t *counters;
@@ -141,6 +197,10 @@ struct DiceSizes {
     uint64_t bits, field, gap_x, gap_y, t4, t8, t16;
 };
 DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]);
+// Distance field of a source from bitmaps (dword y + ny (x / 32 + W z), bit
+// 31 - x % 32) of the voxels that may be on and that certainly are.
+hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint16_t *gap_x, uint16_t *gap_y,
+                        uint8_t *field, hipStream_t s);
 hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
                               uint16_t *gap_y, uint8_t *field, hipStream_t s);
 hipError_t launch_dice_target(const uint8_t *prep, const int32_t n[3], void *t4, uint32_t *t8, uint32_t *t16,
@@ -154,6 +214,23 @@ size_t dice_args_bytes();
 uint64_t dice_args(const ScoreLaunch &L, void *out);
 hipError_t launch_batch_dice(const void *pairs, const uint32_t *offs, const uint32_t *kmax, uint32_t n_pairs,
                              uint32_t groups, uint32_t k, hipStream_t s);
+// The same for trilinear images with a source FOV (tri.hip); may, must
+// (bits bytes each), gap_x and gap_y (gap bytes each) are scratch.
+struct TriSizes {
+    uint64_t bits, field, gap, tz, t4, t8, t16;
+};
+TriSizes tri_sizes(const int32_t sn[3], const int32_t tn[3]);
+hipError_t launch_tri_source(const uint8_t *ok, const int32_t n[3], uint32_t *may, uint32_t *must, uint16_t *gap_x,
+                             uint16_t *gap_y, uint8_t *field, hipStream_t s);
+hipError_t launch_tri_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint32_t *tz, uint32_t *fz,
+                             void *t4, void *t8, void *t16, hipStream_t s);
+bool tri_supported(const ScoreLaunch &L);
+hipError_t launch_tri(const ScoreLaunch &L, hipStream_t s);
+hipError_t launch_tri_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s);
+size_t tri_args_bytes();
+uint64_t tri_args(const ScoreLaunch &L, void *out);
+hipError_t launch_batch_tri(int layout, int vmode, const void *pairs, const uint32_t *offs, const uint32_t *kmax,
+                            uint32_t n_pairs, uint32_t groups, uint32_t k, hipStream_t s);
 hipError_t launch_corner_valid(const uint8_t *fov, uint8_t *out, const int32_t n[3], hipStream_t s);
 // out[0..3] += (fov count, nonzero count, sum v, sum v^2) over the FOV
 hipError_t launch_volume_sums(const uint8_t *vol, const uint8_t *fov, int64_t n, unsigned long long *out,

@@ -1002,8 +1002,14 @@ KArgs make_args(const ScoreLaunch &L, int pt, int *nz_chunks) {
 
 typedef void (*ScoreKernel)(const KArgs);
 
+// (the layouts of one gather come here without a source FOV only: tri_supported)
+constexpr bool one_gather(int layout) {
+    return layout == kLayoutOct || layout == kLayoutOctTile || layout == kLayoutLerp;
+}
+
 template <int PT, int LAYOUT, int ACC>
 ScoreKernel pick_tri(int vmode) {
+    if constexpr (one_gather(LAYOUT)) return k_score_image<PT, LAYOUT, true, 0, ACC>;
     if constexpr (LAYOUT != kLayoutRaw) {
         if (vmode == 2) return k_score_image<PT, LAYOUT, true, 2, ACC>;
     }
@@ -1063,6 +1069,7 @@ template <int PT, int LAYOUT>
 ScoreKernel pick_batch_image(int vmode) {
     typedef void (*BK)(const BatchArgs);
     BK k;
+    if constexpr (one_gather(LAYOUT)) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, LAYOUT, 0>);
     if constexpr (LAYOUT != kLayoutRaw) {
         if (vmode == 2) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, LAYOUT, 2>);
     }
@@ -1092,6 +1099,7 @@ ScoreKernel pick_batch_pt(const BatchPlan &P) {
 hipError_t launch_batch_score(const BatchPlan &P, uint32_t k, hipStream_t s) {
     if (P.n_pairs == 0) return hipSuccess;
     if (P.mode == kModeMask) return launch_batch_dice(P.pairs, P.offs, P.kmax, P.n_pairs, P.grid, k, s);
+    if (P.blocks) return launch_batch_tri(P.layout, P.vmode, P.pairs, P.offs, P.kmax, P.n_pairs, P.grid, k, s);
     BatchArgs b;
     b.pairs = (const KArgs *)P.pairs;
     b.offs = P.offs;
@@ -1148,6 +1156,7 @@ uint64_t score_items_for(const ScoreLaunch &L) { return score_items64(L); }
 hipError_t launch_score(const ScoreLaunch &L, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
     if (L.mode == kModeMask && L.ac) return launch_dice(L, s);
+    if (tri_supported(L)) return launch_tri(L, s);
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
@@ -1250,6 +1259,7 @@ hipError_t launch_gather_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out
     if (!gather_probe_supported(L)) return hipErrorInvalidValue;
     if (L.np == 0) return hipSuccess;
     if (L.mode == kModeMask) return launch_dice_probe(L, key, out, s);
+    if (tri_supported(L)) return launch_tri_probe(L, key, out, s);
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
