@@ -592,10 +592,14 @@ Args make_args(const ScoreLaunch &L) {
     a.p0 = L.p0;
     a.np = L.np;
     // blocks per wave: as many as keep about 32k waves (16 per SIMD slot of
-    // the 256 CUs), since a wave tests 64 blocks at the price of one
+    // the 256 CUs), since a wave tests 64 blocks at the price of one; at least
+    // two (a launch of 64^3 shells, N = 256: 17.4 us, 21.6 with four), and all
+    // parts of one size, so that no wave is left with a few (180 x 170 x 160,
+    // N = 2000: 256 us, 287 with a remainder; 224 x 208 x 176, N = 4096: 585, 612)
     const uint64_t want = (uint64_t)a.n16 * L.np / 32768u;
-    a.blocks = (uint32_t)std::min<uint64_t>(64u, std::max<uint64_t>(4u, want));
+    a.blocks = (uint32_t)std::min<uint64_t>(64u, std::max<uint64_t>(2u, want));
     a.parts = (a.n16 + a.blocks - 1) / a.blocks;
+    a.blocks = (a.n16 + a.parts - 1) / a.parts;
     return a;
 }
 
