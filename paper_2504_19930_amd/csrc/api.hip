@@ -149,6 +149,8 @@ float *scratch_of(int device) {
 
 }  // namespace
 
+constexpr int kPrepHits = 8, kPrepWords = kPrepHits + kLayouts;
+
 struct smc_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -164,6 +166,7 @@ struct smc_ctx {
     void *packed[kLayouts] = {};
     uint64_t sentinel[kLayouts] = {};  // per packed layout: value marking elements outside the source FOV
     bool has_sentinel[kLayouts] = {};
+    unsigned long long *prep = nullptr;  // volume sums (kPrepHits), hits of the packed layouts' sentinels
     FilterState f{};
     uint32_t k_done = 0;
     // the current particles are a draw from the uniform prior box (spread over
@@ -308,55 +311,107 @@ uint64_t splitmix64(uint64_t x) {
     return x ^ (x >> 31);
 }
 
+constexpr int kCandidates = 64;
+uint64_t candidate(int q) { return splitmix64((uint64_t)q + 1); }
+
 // Allocate and fill a packed trilinear layout of the source.  With a source
-// FOV, find a value no in-FOV element takes and store it in every element
-// that touches a voxel outside the FOV (then samples need no separate
-// validity gather); if none is free, pack plainly and keep the gather.
+// FOV, every element that touches a voxel outside it holds a value that no
+// in-FOV element takes (then samples need no separate validity gather); if none
+// is free, the layout is packed plainly and the gather kept.  Octets, which
+// hardly ever take a given 64-bit value, are packed with the first candidate
+// and counted against it in the same pass (c->prep[kPrepHits + layout]);
+// settle_layouts, once the counts are on the host, searches on for those
+// that met it.
+smc_status search_sentinel(smc_ctx *c, int layout, uint64_t *sent, bool *ok) {
+    const int n_cand = layout == kLayoutPairX ? 0 : kCandidates;
+    const size_t n_counts = layout == kLayoutPairX ? 65536 : kCandidates;
+    std::vector<uint64_t> cand(kCandidates);
+    for (int q = 0; q < kCandidates; ++q) cand[q] = candidate(q);
+    uint64_t *dcand = nullptr;
+    unsigned long long *dcounts = nullptr;
+    std::vector<unsigned long long> counts(n_counts);
+    hipError_t e = hipMalloc(&dcand, 8 * kCandidates);
+    if (e == hipSuccess) e = hipMalloc(&dcounts, 8 * n_counts);
+    if (e == hipSuccess) e = hipMemcpyAsync(dcand, cand.data(), 8 * kCandidates, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = launch_fill_u64(dcounts, n_counts, c->stream);
+    if (e == hipSuccess)
+        e = launch_count_elements(c->src, c->src_fov, c->sn, layout, dcand, n_cand, dcounts, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(counts.data(), dcounts, 8 * n_counts, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (dcand) (void)hipFree(dcand);
+    if (dcounts) (void)hipFree(dcounts);
+    if (e != hipSuccess) return fail(SMC_EDEVICE, "sentinel search failed: %s", hipGetErrorString(e));
+    *ok = false;
+    for (size_t q = 0; q < n_counts && !*ok; ++q)
+        if (counts[q] == 0) {
+            *sent = layout == kLayoutPairX ? (uint64_t)q : cand[q];
+            *ok = true;
+        }
+    return SMC_OK;
+}
+
 smc_status prepare_layout(smc_ctx *c, int layout) {
     if (c->mode != kModeImageTrilinear || layout == kLayoutRaw || c->packed[layout]) return SMC_OK;
-    if (layout == kLayoutLerp && layout_fits(kLayoutOctTile, c->sn)) {
-        // the tiled octets serve the first evaluation of a dispersed prior
-        const smc_status so = prepare_layout(c, kLayoutOctTile);
-        if (so != SMC_OK) return so;
-    }
     smc_status st;
-    if ((st = c->alloc((uint8_t **)&c->packed[layout], packed_bytes(layout, c->sn))) != SMC_OK) return st;
+    // the tiled octets serve the first evaluation of a dispersed prior
+    const bool lerp = layout == kLayoutLerp,
+               tiles = layout == kLayoutOctTile ||
+                       (lerp && !c->packed[kLayoutOctTile] && layout_fits(kLayoutOctTile, c->sn));
+    const auto take = [&](int l) { return c->alloc((uint8_t **)&c->packed[l], packed_bytes(l, c->sn)); };
+    if (tiles && (st = take(kLayoutOctTile)) != SMC_OK) return st;
+    if (layout != kLayoutOctTile && (st = take(layout)) != SMC_OK) return st;
     uint64_t sent = 0;
     bool ok = false;
-    if (c->src_fov && layout == kLayoutLerp) {
-        sent = kLerpSentinel;
-        ok = true;
-    } else if (c->src_fov) {
-        const int n_cand = layout == kLayoutPairX ? 0 : 64;
-        const size_t n_counts = layout == kLayoutPairX ? 65536 : 64;
-        std::vector<uint64_t> cand(64);
-        for (int q = 0; q < 64; ++q) cand[q] = splitmix64((uint64_t)q + 1);
-        uint64_t *dcand = nullptr;
-        unsigned long long *dcounts = nullptr;
-        std::vector<unsigned long long> counts(n_counts);
-        hipError_t e = hipMalloc(&dcand, 8 * 64);
-        if (e == hipSuccess) e = hipMalloc(&dcounts, 8 * n_counts);
-        if (e == hipSuccess) e = hipMemcpyAsync(dcand, cand.data(), 8 * 64, hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess) e = launch_fill_u64(dcounts, n_counts, c->stream);
-        if (e == hipSuccess)
-            e = launch_count_elements(c->src, c->src_fov, c->sn, layout, dcand, n_cand, dcounts, c->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(counts.data(), dcounts, 8 * n_counts, hipMemcpyDeviceToHost, c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (dcand) (void)hipFree(dcand);
-        if (dcounts) (void)hipFree(dcounts);
-        if (e != hipSuccess) return fail(SMC_EDEVICE, "sentinel search failed: %s", hipGetErrorString(e));
-        for (size_t q = 0; q < n_counts && !ok; ++q)
-            if (counts[q] == 0) {
-                sent = layout == kLayoutPairX ? (uint64_t)q : cand[q];
-                ok = true;
-            }
+    if (layout == kLayoutPairX || layout == kLayoutQuadXY) {
+        if (c->src_fov && (st = search_sentinel(c, layout, &sent, &ok)) != SMC_OK) return st;
+        HIP_TRY(launch_pack_rows(c->src, ok ? c->src_fov : nullptr, c->sn, layout, sent, c->packed[layout], c->stream));
+        c->sentinel[layout] = sent;
+        c->has_sentinel[layout] = ok;
+        return SMC_OK;
     }
-    HIP_TRY(launch_pack_source(c->src, ok ? c->src_fov : nullptr, c->sn, layout, sent, c->packed[layout],
-                               c->stream));
-    c->sentinel[layout] = sent;
-    c->has_sentinel[layout] = ok;
+    const int octets = tiles ? kLayoutOctTile : (lerp ? -1 : layout);
+    if (c->src_fov) sent = candidate(0);
+    HIP_TRY(launch_pack_cells(c->src, c->src_ok, c->sn, lerp ? c->packed[layout] : nullptr,
+                              octets >= 0 ? c->packed[octets] : nullptr, tiles, sent,
+                              octets >= 0 && c->src_fov ? c->prep + kPrepHits + octets : nullptr, c->stream));
+    if (octets >= 0) {
+        c->sentinel[octets] = sent;
+        c->has_sentinel[octets] = c->src_fov != nullptr;
+    }
+    if (lerp) {
+        c->sentinel[layout] = c->src_fov ? kLerpSentinel : 0;
+        c->has_sentinel[layout] = c->src_fov != nullptr;
+    }
     return SMC_OK;
+}
+
+// hits: the counts of c->prep per layout.
+smc_status settle_layouts(smc_ctx *c, const unsigned long long *hits) {
+    for (int layout : {kLayoutOct, kLayoutOctTile}) {
+        if (!hits[layout]) continue;
+        uint64_t sent = 0;
+        bool ok = false;
+        const smc_status st = search_sentinel(c, layout, &sent, &ok);
+        if (st != SMC_OK) return st;
+        HIP_TRY(launch_pack_cells(c->src, ok ? c->src_ok : nullptr, c->sn, nullptr, c->packed[layout],
+                                  layout == kLayoutOctTile, sent, nullptr, c->stream));
+        c->sentinel[layout] = sent;
+        c->has_sentinel[layout] = ok;
+    }
+    return SMC_OK;
+}
+
+// prepare_layout of a context in use.
+smc_status add_layout(smc_ctx *c, int layout) {
+    const bool search = c->mode == kModeImageTrilinear && layout != kLayoutRaw && !c->packed[layout] && c->src_fov;
+    if (!search) return prepare_layout(c, layout);
+    unsigned long long hits[kLayouts];
+    smc_status st;
+    HIP_TRY(launch_fill_u64(c->prep + kPrepHits, kLayouts, c->stream));
+    if ((st = prepare_layout(c, layout)) != SMC_OK) return st;
+    HIP_TRY(hipMemcpyAsync(hits, c->prep + kPrepHits, sizeof hits, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return settle_layouts(c, hits);
 }
 
 smc_status launch_prior(smc_ctx *c) {
@@ -498,24 +553,17 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         c->dice.t4 = t4;
         c->dice.t8 = (const uint32_t *)t8;
         c->dice.t16 = (const uint32_t *)t16;
-        if (launch_prep_mask(src->data, src->fov, c->src_prep, vs, c->stream) != hipSuccess ||
-            launch_prep_mask(tgt->data, tgt->fov, c->tgt_prep, vt, c->stream) != hipSuccess ||
-            launch_dice_source(c->src_prep, c->sn, (uint32_t *)bits, (uint16_t *)gap_x, (uint16_t *)gap_y, field,
+        if (launch_mask_source(src->data, src->fov, c->sn, c->src_prep, (uint32_t *)bits, c->stream) != hipSuccess ||
+            launch_field((const uint32_t *)bits, (const uint32_t *)bits, c->sn, (uint16_t *)gap_x, (uint16_t *)gap_y,
+                         field, c->stream) != hipSuccess ||
+            launch_dice_target(tgt->data, tgt->fov, c->tn, c->tgt_prep, t4, (uint32_t *)t8, (uint32_t *)t16,
                                c->stream) != hipSuccess ||
-            launch_dice_target(c->tgt_prep, c->tn, t4, (uint32_t *)t8, (uint32_t *)t16, c->stream) != hipSuccess ||
             launch_fill_u64(c->work, kWorkSlots * kWorkSlotWords, c->stream) != hipSuccess)
             return bail(fail(SMC_EDEVICE, "mask preparation launch failed"));
+    } else if (src->fov && c->mode == kModeImageNearest) {
+        c->src_ok = const_cast<uint8_t *>(src->fov);
     } else if (src->fov) {
-        if (c->mode == kModeImageTrilinear) {
-            if ((st = c->alloc(&c->src_ok, vs)) != SMC_OK) return bail(st);
-            if (launch_corner_valid(src->fov, c->src_ok, c->sn, c->stream) != hipSuccess)
-                return bail(fail(SMC_EDEVICE, "corner-validity launch failed"));
-        } else {
-            c->src_ok = const_cast<uint8_t *>(src->fov);
-        }
-    }
-
-    if (c->src_ok && c->mode == kModeImageTrilinear) {
+        if ((st = c->alloc(&c->src_ok, vs)) != SMC_OK) return bail(st);
         const TriSizes ts = tri_sizes(c->sn, c->tn);
         uint8_t *may, *must, *gap_x, *gap_y, *field, *tz, *fz = nullptr, *t4, *t8, *t16;
         if ((st = c->alloc(&may, ts.bits)) != SMC_OK || (st = c->alloc(&must, ts.bits)) != SMC_OK ||
@@ -530,27 +578,30 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         c->tri.t4 = t4;
         c->tri.t8 = t8;
         c->tri.t16 = t16;
-        if (launch_tri_source(c->src_ok, c->sn, (uint32_t *)may, (uint32_t *)must, (uint16_t *)gap_x, (uint16_t *)gap_y,
-                              field, c->stream) != hipSuccess ||
+        if (launch_corner_valid(src->fov, c->sn, c->src_ok, (uint32_t *)may, (uint32_t *)must, c->stream) != hipSuccess ||
+            launch_field((const uint32_t *)may, (const uint32_t *)must, c->sn, (uint16_t *)gap_x, (uint16_t *)gap_y,
+                         field, c->stream) != hipSuccess ||
             launch_tri_target(tgt->data, tgt->fov, c->tn, (uint32_t *)tz, (uint32_t *)fz, t4, t8, t16, c->stream) !=
                 hipSuccess)
             return bail(fail(SMC_EDEVICE, "image preparation launch failed"));
     }
 
+    // exact per-volume sums -> statistics, and the hits of the packed layouts
+    if ((st = c->alloc(&c->prep, kPrepWords)) != SMC_OK) return bail(st);
+    const uint8_t *const vols[2] = {tgt->data, src->data}, *const fovs[2] = {tgt->fov, src->fov};
+    const int64_t sizes[2] = {vt, vs};
+    if (launch_fill_u64(c->prep, kPrepWords, c->stream) != hipSuccess ||
+        launch_volume_sums(vols, fovs, sizes, c->prep, c->stream) != hipSuccess)
+        return bail(fail(SMC_EDEVICE, "volume statistics launch failed"));
+
     if (!layout_fits(c->layout, c->sn)) c->layout = layout_fits(kLayoutOct, c->sn) ? kLayoutOct : kLayoutRaw;
     if ((st = prepare_layout(c, c->layout)) != SMC_OK) return bail(st);
 
-    // exact per-volume sums -> statistics
-    unsigned long long *vsum = nullptr;
-    if ((st = c->alloc(&vsum, 8)) != SMC_OK) return bail(st);
-    unsigned long long hs[8];
-    if (launch_fill_u64(vsum, 8, c->stream) != hipSuccess ||
-        launch_volume_sums(tgt->data, tgt->fov, vt, vsum, c->stream) != hipSuccess ||
-        launch_volume_sums(src->data, src->fov, vs, vsum + 4, c->stream) != hipSuccess)
-        return bail(fail(SMC_EDEVICE, "volume statistics launch failed"));
-    if (hipMemcpyAsync(hs, vsum, sizeof hs, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+    unsigned long long hs[kPrepWords];
+    if (hipMemcpyAsync(hs, c->prep, sizeof hs, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
         return bail(fail(SMC_EDEVICE, "reading volume statistics failed: %s", hipGetErrorString(hipGetLastError())));
+    if ((st = settle_layouts(c, hs + kPrepHits)) != SMC_OK) return bail(st);
     const Stats ts = stats_from_sums(hs), ss = stats_from_sums(hs + 4);
     if (ts.count == 0) return bail(fail(SMC_EINVAL, "the target FOV is empty"));
     c->tgt_on = ts.on;
@@ -1021,7 +1072,7 @@ smc_status smc_set_tuning(smc_ctx *c, int32_t layout, int32_t pt, int32_t tile_d
         if (c->mode == kModeImageTrilinear && !layout_fits(layout, c->sn))
             return fail(SMC_EINVAL, "layout %d cannot address a %d x %d x %d source (packed size >= 4 GiB or "
                         "a packed slice >= 16 MiB); use layout 0", layout, c->sn[0], c->sn[1], c->sn[2]);
-        if ((st = prepare_layout(c, layout)) != SMC_OK) return c->mark(st);
+        if ((st = add_layout(c, layout)) != SMC_OK) return c->mark(st);
         c->layout = layout;
     }
     for (smc_ctx *fr : c->frames)

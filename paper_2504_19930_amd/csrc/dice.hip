@@ -393,22 +393,6 @@ __global__ __launch_bounds__(kThreads) void k_batch_dice(const Args *pairs_g, co
 
 // ---------------------------------------------------------------- preparation
 
-// Source bitmap: bit 31 - x % 32 of dword y + ny (x / 32 + W z); pad bits
-// zero.  A thread makes one dword, neighbours of one row (the reads meet).
-__global__ __launch_bounds__(256) void k_pack_bits(const uint8_t *prep, int32_t nx, uint32_t ny, int64_t rows,
-                                                   uint32_t W, uint32_t *out) {
-    const int64_t n = (int64_t)W * rows;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t row = q / W, z = row / ny;
-        const uint32_t xw = (uint32_t)(q - row * W), y = (uint32_t)(row - z * ny);
-        const int32_t x0 = (int32_t)xw * 32;
-        const uint8_t *r = prep + row * (int64_t)nx;
-        uint32_t v = 0u;
-        for (int b = 0; b < 32 && x0 + b < nx; ++b) v |= ((uint32_t)(r[x0 + b] >> 1) & 1u) << (31 - b);
-        out[y + ny * (xw + W * z)] = v;
-    }
-}
-
 // The field, one axis at a time.  Gaps are whole voxels between two voxels'
 // boxes, 0 where they touch; kWindow and more read as kWindow, and squared
 // distances saturate at 255 (both lower bounds).  Voxels outside the source
@@ -417,10 +401,10 @@ __global__ __launch_bounds__(256) void k_pack_bits(const uint8_t *prep, int32_t 
 //
 // x: gaps along the rows, four voxels a thread.
 __global__ __launch_bounds__(256) void k_field_x(const uint32_t *may, const uint32_t *must, int32_t nx, uint32_t ny,
-                                                 int64_t rows, uint32_t W, uint16_t *out) {
-    const int64_t quads = (nx + 3) / 4, n = quads * rows;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t row = q / quads, z = row / ny;
+                                                 uint32_t rows, uint32_t W, uint16_t *out) {
+    const uint32_t quads = (uint32_t)(nx + 3) / 4, n = quads * rows;
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
+        const uint32_t row = q / quads, z = row / ny;
         const int32_t xa = 4 * (int32_t)(q - row * quads), x0 = xa - kWindow;  // first voxel of the window
         const int64_t r = (row - z * ny) + (int64_t)ny * W * z;
         const int32_t d = x0 >> 5, s = x0 & 31;
@@ -441,7 +425,7 @@ __global__ __launch_bounds__(256) void k_field_x(const uint32_t *may, const uint
             return min(gl, gr);
         };
         for (int j = 0; j < 4 && xa + j < nx; ++j)
-            out[row * nx + xa + j] = (uint16_t)(gap(on >> j) | (gap(off >> j) << 8));
+            out[row * (uint32_t)nx + xa + j] = (uint16_t)(gap(on >> j) | (gap(off >> j) << 8));
     }
 }
 
@@ -465,16 +449,16 @@ __device__ __forceinline__ u16x2 envelope(const u16x2 *v) {
 // y: squared distances within a slice.
 __global__ __launch_bounds__(256) void k_field_y(const uint16_t *gx, int32_t nx, int32_t ny, int32_t nz,
                                                  uint16_t *out) {
-    const int64_t strips = (ny + kStrip - 1) / kStrip, n = (int64_t)nx * strips * nz;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t t = q / nx, z = t / strips;
+    const uint32_t strips = (uint32_t)(ny + kStrip - 1) / kStrip, n = (uint32_t)nx * strips * (uint32_t)nz;
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
+        const uint32_t t = q / (uint32_t)nx, z = t / strips;
         const int32_t y0 = kStrip * (int32_t)(t - z * strips);
-        const uint16_t *line = gx + (q - t * nx) + (int64_t)nx * ny * z;
+        const uint32_t line = (q - t * nx) + (uint32_t)nx * ((uint32_t)ny * z);
         u16x2 v[kStrip + 2 * kWindow];
 #pragma unroll
         for (int e = 0; e < kStrip + 2 * kWindow; ++e) {
             const int32_t y = y0 + e - kWindow;
-            const uint32_t g = y >= 0 && y < ny ? line[(int64_t)nx * y] : (uint32_t)kWindow;  // outside: off
+            const uint32_t g = y >= 0 && y < ny ? gx[line + (uint32_t)(nx * y)] : (uint32_t)kWindow;  // outside: off
             const u16x2 p = {(uint16_t)(g & 255u), (uint16_t)(g >> 8)};
             v[e] = p * p;
         }
@@ -482,7 +466,7 @@ __global__ __launch_bounds__(256) void k_field_y(const uint16_t *gx, int32_t nx,
         for (int j = 0; j < kStrip; ++j) {
             if (y0 + j >= ny) break;
             const u16x2 m = envelope(v + j);
-            out[(q - t * nx) + (int64_t)nx * ((y0 + j) + ny * z)] =
+            out[line + (uint32_t)(nx * (y0 + j))] =
                 (uint16_t)(min((uint32_t)m.x, 255u) | (min((uint32_t)m.y, 255u) << 8));
         }
     }
@@ -490,17 +474,17 @@ __global__ __launch_bounds__(256) void k_field_y(const uint16_t *gx, int32_t nx,
 
 // z, and the field byte: 0 where a voxel of the other state touches (always
 // sampled).
-__global__ __launch_bounds__(256) void k_field_z(const uint16_t *gy, int64_t plane, int32_t nz, uint8_t *out) {
-    const int64_t strips = (nz + kStrip - 1) / kStrip, n = plane * strips;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t t = q / plane;
+__global__ __launch_bounds__(256) void k_field_z(const uint16_t *gy, uint32_t plane, int32_t nz, uint8_t *out) {
+    const uint32_t strips = (uint32_t)(nz + kStrip - 1) / kStrip, n = plane * strips;
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
+        const uint32_t t = q / plane;
         const int32_t z0 = kStrip * (int32_t)t;
-        const uint16_t *line = gy + (q - t * plane);
+        const uint32_t line = q - t * plane;
         u16x2 v[kStrip + 2 * kWindow];
 #pragma unroll
         for (int e = 0; e < kStrip + 2 * kWindow; ++e) {
             const int32_t z = z0 + e - kWindow;
-            const uint32_t g = z >= 0 && z < nz ? line[plane * z] : 255u;  // outside: off
+            const uint32_t g = z >= 0 && z < nz ? gy[line + plane * (uint32_t)z] : 255u;  // outside: off
             v[e] = u16x2{(uint16_t)(g & 255u), (uint16_t)(g >> 8)};
         }
 #pragma unroll
@@ -510,53 +494,82 @@ __global__ __launch_bounds__(256) void k_field_z(const uint16_t *gy, int64_t pla
             // (one of the two is 0: the voxel's own state)
             const uint32_t d2 = min((uint32_t)max(m.x, m.y), 255u);
             const uint32_t dist = min(kFieldDist, (uint32_t)floorf(sqrtf((float)(64u * d2))));
-            out[(q - t * plane) + plane * (z0 + j)] = (uint8_t)(dist | (m.x == 0 && m.y != 0 ? kFieldOn : 0u));
+            out[line + plane * (uint32_t)(z0 + j)] = (uint8_t)(dist | (m.x == 0 && m.y != 0 ? kFieldOn : 0u));
         }
     }
 }
 
-// Target 4^3 blocks (layout: Args::t4).
-__global__ __launch_bounds__(256) void k_target4(const uint8_t *prep, int32_t nx, int32_t ny, int32_t nz, uint32_t gx,
-                                                 uint32_t gy, uint32_t gz, uint4 *out) {
-    const int64_t n = (int64_t)gx * gy * gz;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t t = q / gx;
-        const int32_t x0 = 4 * (int32_t)(q - t * gx), y0 = 4 * (int32_t)(t % gy), z0 = 4 * (int32_t)(t / gy);
+// Prepared bytes (bit 0: inside the FOV, no FOV = everywhere; bit 1: nonzero and
+// inside) and 4^3 blocks (layout: Args::t4) of the target, a block a thread, a
+// row of it a dword (bytes at the last columns and of an unaligned volume
+// all the same: a dword load takes any address).  8.2 M voxels: 10 us; a byte
+// a load and the bytes in a pass of their own 8 + 17.
+__global__ __launch_bounds__(256) void k_target4(const uint8_t *vol, const uint8_t *fov, uint8_t *prep, int32_t nx,
+                                                 int32_t ny, int32_t nz, uint32_t gx, uint32_t gy, uint32_t gz,
+                                                 uint4 *out) {
+    const uint32_t n = gx * gy * gz;
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
+        const uint32_t t = q / gx, tz = t / gy;
+        const int32_t x0 = 4 * (int32_t)(q - t * gx), y0 = 4 * (int32_t)(t - tz * gy), z0 = 4 * (int32_t)tz;
         uint32_t v[4] = {0u, 0u, 0u, 0u};
+        const int32_t wide = min(4, nx - x0);
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int y = 0; y < 4; ++y)
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    if (z0 + s >= nz || y0 + y >= ny || x0 + x >= nx) continue;
-                    const uint32_t b = prep[(int64_t)(x0 + x) + (int64_t)nx * ((y0 + y) + (int64_t)ny * (z0 + s))];
-                    v[y] |= ((b & 1u) | ((b & 2u) << 3)) << (8 * x + 3 - s);
+            for (int y = 0; y < 4; ++y) {
+                if (z0 + s >= nz || y0 + y >= ny) continue;
+                const int64_t o = (int64_t)x0 + (int64_t)nx * ((y0 + y) + (int64_t)ny * (z0 + s));
+                uint32_t a = 0u, f = 0x01010101u, keep = ~0u;
+                if (wide == 4) {
+                    __builtin_memcpy(&a, vol + o, 4);
+                    if (fov) __builtin_memcpy(&f, fov + o, 4);
+                } else {
+                    keep = 0u;
+                    for (int x = 0; x < wide; ++x) {
+                        a |= (uint32_t)vol[o + x] << (8 * x);
+                        if (fov) f = (f & ~(255u << (8 * x))) | ((uint32_t)fov[o + x] << (8 * x));
+                        keep |= 255u << (8 * x);
+                    }
                 }
+                const auto nonzero = [](uint32_t b) {  // 1 in each byte that is not zero
+                    return ((((b & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | b) >> 7) & 0x01010101u;
+                };
+                const uint32_t in = nonzero(f) & keep, on = nonzero(a) & in, bytes = in | (on << 1);
+                if (wide == 4)
+                    __builtin_memcpy(prep + o, &bytes, 4);
+                else
+                    for (int x = 0; x < wide; ++x) prep[o + x] = (uint8_t)(bytes >> (8 * x));
+                v[y] |= (in | (on << 4)) << (3 - s);
+            }
         out[q] = make_uint4(v[0], v[1], v[2], v[3]);
     }
 }
 
-// Counts (FOV | on << 16) of the target blocks of side 4 c (c = 2, 4).
-__global__ __launch_bounds__(256) void k_target_counts(const uint4 *t4, uint32_t c, uint32_t g4x, uint32_t g4y,
-                                                       uint32_t g4z, uint32_t gx, uint32_t gy, uint32_t gz,
-                                                       uint32_t *out) {
-    const int64_t n = (int64_t)gx * gy * gz;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t t = q / gx;
-        const uint32_t x0 = c * (uint32_t)(q - t * gx), y0 = c * (uint32_t)(t % gy), z0 = c * (uint32_t)(t / gy);
+// Counts (FOV | on << 16) of the target blocks of side 8 and 16: a wave makes one
+// of 16 from its 64 blocks of 4^3, a lane each (one thread over all 64 waited
+// on a chain of loads: 4 + 14 us for both sides, 5 us so).
+__global__ __launch_bounds__(256) void k_target_counts(const uint4 *t4, uint32_t g4x, uint32_t g4y, uint32_t g4z,
+                                                       uint32_t g8x, uint32_t g8y, uint32_t g8z, uint32_t gx,
+                                                       uint32_t gy, uint32_t gz, uint32_t *t8, uint32_t *t16) {
+    const uint32_t n = gx * gy * gz, lane = threadIdx.x % 64;
+    const uint32_t lx = lane & 3u, ly = (lane >> 2) & 3u, lz = lane >> 4;
+    for (uint32_t w = blockIdx.x * 4 + threadIdx.x / 64; w < n; w += gridDim.x * 4) {
+        const uint32_t t = w / gx, bz = t / gy, bx = w - t * gx, by = t - bz * gy;
+        const uint32_t x = 4 * bx + lx, y = 4 * by + ly, z = 4 * bz + lz;
         uint32_t v = 0u;
-        for (uint32_t z = z0; z < min(z0 + c, g4z); ++z)
-            for (uint32_t y = y0; y < min(y0 + c, g4y); ++y)
-                for (uint32_t x = x0; x < min(x0 + c, g4x); ++x) {
-                    const uint4 b = t4[x + (int64_t)g4x * (y + (int64_t)g4y * z)];
-                    v += (uint32_t)(__popc(b.x & 0x0F0F0F0Fu) + __popc(b.y & 0x0F0F0F0Fu) +
-                                    __popc(b.z & 0x0F0F0F0Fu) + __popc(b.w & 0x0F0F0F0Fu)) +
-                         ((uint32_t)(__popc(b.x & 0xF0F0F0F0u) + __popc(b.y & 0xF0F0F0F0u) +
-                                     __popc(b.z & 0xF0F0F0F0u) + __popc(b.w & 0xF0F0F0F0u))
-                          << 16);
-                }
-        out[q] = v;
+        if (x < g4x && y < g4y && z < g4z) {
+            const uint4 b = t4[x + (int64_t)g4x * (y + (int64_t)g4y * z)];
+            v = (uint32_t)(__popc(b.x & 0x0F0F0F0Fu) + __popc(b.y & 0x0F0F0F0Fu) + __popc(b.z & 0x0F0F0F0Fu) +
+                           __popc(b.w & 0x0F0F0F0Fu)) +
+                ((uint32_t)(__popc(b.x & 0xF0F0F0F0u) + __popc(b.y & 0xF0F0F0F0u) + __popc(b.z & 0xF0F0F0F0u) +
+                            __popc(b.w & 0xF0F0F0F0u))
+                 << 16);
+        }
+        for (int o = 1; o < 64; o <<= 2) v += __shfl_xor(v, o);
+        const uint32_t x8 = 2 * bx + lx / 2, y8 = 2 * by + ly / 2, z8 = 2 * bz + lz / 2;
+        if ((lane & 21u) == 0u && x8 < g8x && y8 < g8y && z8 < g8z) t8[x8 + (int64_t)g8x * (y8 + (int64_t)g8y * z8)] = v;
+        for (int o = 2; o < 64; o <<= 2) v += __shfl_xor(v, o);
+        if (lane == 0) t16[w] = v;
     }
 }
 
@@ -626,34 +639,24 @@ hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t
                         uint8_t *field, hipStream_t s) {
     const int64_t rows = (int64_t)n[1] * n[2], plane = (int64_t)n[0] * n[1];
     hipLaunchKernelGGL(k_field_x, dim3(blocks_for((n[0] + 3) / 4 * rows)), dim3(256), 0, s, may, must, n[0],
-                       (uint32_t)n[1], rows, cells(n[0], 32), gap_x);
+                       (uint32_t)n[1], (uint32_t)rows, cells(n[0], 32), gap_x);
     hipLaunchKernelGGL(k_field_y, dim3(blocks_for(((int64_t)n[1] + kStrip - 1) / kStrip * n[0] * n[2])), dim3(256), 0, s,
                        (const uint16_t *)gap_x, n[0], n[1], n[2], gap_y);
     hipLaunchKernelGGL(k_field_z, dim3(blocks_for(((int64_t)n[2] + kStrip - 1) / kStrip * plane)), dim3(256), 0, s,
-                       (const uint16_t *)gap_y, plane, n[2], field);
+                       (const uint16_t *)gap_y, (uint32_t)plane, n[2], field);
     return hipGetLastError();
 }
 
-hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
-                              uint16_t *gap_y, uint8_t *field, hipStream_t s) {
-    const int64_t rows = (int64_t)n[1] * n[2];
-    const uint32_t W = cells(n[0], 32);
-    hipLaunchKernelGGL(k_pack_bits, dim3(blocks_for(W * rows)), dim3(256), 0, s, prep, n[0], (uint32_t)n[1], rows, W,
-                       bits);
-    return launch_field(bits, bits, n, gap_x, gap_y, field, s);
-}
-
-hipError_t launch_dice_target(const uint8_t *prep, const int32_t n[3], void *t4, uint32_t *t8, uint32_t *t16,
-                              hipStream_t s) {
+hipError_t launch_dice_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint8_t *prep, void *t4,
+                              uint32_t *t8, uint32_t *t16, hipStream_t s) {
     uint32_t g[3][3];
     for (int l = 0; l < 3; ++l)
         for (int d = 0; d < 3; ++d) g[l][d] = cells(n[d], 4 << l);
     const auto count = [&](int l) { return (int64_t)g[l][0] * g[l][1] * g[l][2]; };
-    hipLaunchKernelGGL(k_target4, dim3(blocks_for(count(0))), dim3(256), 0, s, prep, n[0], n[1], n[2], g[0][0], g[0][1],
-                       g[0][2], (uint4 *)t4);
-    for (int l = 1; l < 3; ++l)
-        hipLaunchKernelGGL(k_target_counts, dim3(blocks_for(count(l))), dim3(256), 0, s, (const uint4 *)t4, 1u << l,
-                           g[0][0], g[0][1], g[0][2], g[l][0], g[l][1], g[l][2], l == 1 ? t8 : t16);
+    hipLaunchKernelGGL(k_target4, dim3(blocks_for(count(0))), dim3(256), 0, s, vol, fov, prep, n[0], n[1], n[2], g[0][0],
+                       g[0][1], g[0][2], (uint4 *)t4);
+    hipLaunchKernelGGL(k_target_counts, dim3(blocks_for(64 * count(2))), dim3(256), 0, s, (const uint4 *)t4, g[0][0],
+                       g[0][1], g[0][2], g[1][0], g[1][1], g[1][2], g[2][0], g[2][1], g[2][2], t8, t16);
     return hipGetLastError();
 }
 

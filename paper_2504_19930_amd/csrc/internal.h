@@ -147,10 +147,16 @@ void score_grid(const ScoreLaunch &L, dim3 *grid, dim3 *block);
 bool score_pt_supported(int pt);
 // whether a packed trilinear layout can address a source of this shape
 bool layout_fits(int layout, const int32_t sn[3]);
-// Pack a source volume into `layout` (edge corners repeat the last voxel).
-// With fov, elements touching a voxel outside it hold `sentinel` instead.
-hipError_t launch_pack_source(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], int layout,
-                              uint64_t sentinel, void *out, hipStream_t s);
+// Pack a source volume into the layouts pairx or quadxy (edge corners repeat the
+// last voxel).  With fov, elements touching a voxel outside it hold `sentinel`
+// instead.
+hipError_t launch_pack_rows(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], int layout, uint64_t sentinel,
+                            void *out, hipStream_t s);
+// The same into the x-lerps and the (tiled) octets, either of which may be
+// nullptr; ok: corner validity or nullptr, hits: += valid octets that equal the
+// sentinel, or nullptr.
+hipError_t launch_pack_cells(const uint8_t *vol, const uint8_t *ok, const int32_t n[3], void *lerp, void *oct,
+                             bool tiled, uint64_t sentinel, unsigned long long *hits, hipStream_t s);
 // Over the elements of `layout` that lie inside the fov, count those equal to
 // each candidate (truncated to the element width) -- or, for x-pairs with
 // n_cand == 0, a 65536-bin histogram of all element values.
@@ -189,22 +195,27 @@ int batch_blocks_per_cu(const BatchPlan &P);
 int score_vmode(const ScoreLaunch &L);
 
 // Preparation of inputs.
-hipError_t launch_prep_mask(const uint8_t *vol, const uint8_t *fov, uint8_t *out, int64_t n, hipStream_t s);
+// Bitmaps: dword y + ny (x / 32 + W z), bit 31 - x % 32.
+// A mask source: prepared bytes and the bitmap of the nonzero voxels in the FOV.
+hipError_t launch_mask_source(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint8_t *out, uint32_t *bits,
+                              hipStream_t s);
+// A trilinear source's FOV: corner-validity bytes, bitmaps of the cells a valid
+// sample may and must lie in.
+hipError_t launch_corner_valid(const uint8_t *fov, const int32_t n[3], uint8_t *out, uint32_t *may, uint32_t *must,
+                               hipStream_t s);
 constexpr uint32_t kWorkSlots = 64, kWorkSlotWords = 16;
 // Device bytes of the structures of the filter's mask launches (dice.hip);
-// gap_x and gap_y are scratch of launch_dice_source.
+// gap_x and gap_y are scratch of launch_field.
 struct DiceSizes {
     uint64_t bits, field, gap_x, gap_y, t4, t8, t16;
 };
 DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]);
-// Distance field of a source from bitmaps (dword y + ny (x / 32 + W z), bit
-// 31 - x % 32) of the voxels that may be on and that certainly are.
+// Distance field of a source from bitmaps of the voxels that may be on and that
+// certainly are.
 hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint16_t *gap_x, uint16_t *gap_y,
                         uint8_t *field, hipStream_t s);
-hipError_t launch_dice_source(const uint8_t *prep, const int32_t n[3], uint32_t *bits, uint16_t *gap_x,
-                              uint16_t *gap_y, uint8_t *field, hipStream_t s);
-hipError_t launch_dice_target(const uint8_t *prep, const int32_t n[3], void *t4, uint32_t *t8, uint32_t *t16,
-                              hipStream_t s);
+hipError_t launch_dice_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint8_t *prep, void *t4,
+                              uint32_t *t8, uint32_t *t16, hipStream_t s);
 hipError_t launch_dice(const ScoreLaunch &L, hipStream_t s);
 hipError_t launch_dice_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s);
 // A batch's mask pairs: kernel arguments of a pair (its workgroups are
@@ -220,8 +231,6 @@ struct TriSizes {
     uint64_t bits, field, gap, tz, t4, t8, t16;
 };
 TriSizes tri_sizes(const int32_t sn[3], const int32_t tn[3]);
-hipError_t launch_tri_source(const uint8_t *ok, const int32_t n[3], uint32_t *may, uint32_t *must, uint16_t *gap_x,
-                             uint16_t *gap_y, uint8_t *field, hipStream_t s);
 hipError_t launch_tri_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint32_t *tz, uint32_t *fz,
                              void *t4, void *t8, void *t16, hipStream_t s);
 bool tri_supported(const ScoreLaunch &L);
@@ -231,10 +240,9 @@ size_t tri_args_bytes();
 uint64_t tri_args(const ScoreLaunch &L, void *out);
 hipError_t launch_batch_tri(int layout, int vmode, const void *pairs, const uint32_t *offs, const uint32_t *kmax,
                             uint32_t n_pairs, uint32_t groups, uint32_t k, hipStream_t s);
-hipError_t launch_corner_valid(const uint8_t *fov, uint8_t *out, const int32_t n[3], hipStream_t s);
-// out[0..3] += (fov count, nonzero count, sum v, sum v^2) over the FOV
-hipError_t launch_volume_sums(const uint8_t *vol, const uint8_t *fov, int64_t n, unsigned long long *out,
-                              hipStream_t s);
+// out[4 v + 0..3] += (fov count, nonzero count, sum, sum of squares) of volume v over its FOV
+hipError_t launch_volume_sums(const uint8_t *const vol[2], const uint8_t *const fov[2], const int64_t n[2],
+                              unsigned long long *out, hipStream_t s);
 
 // Filter state of one registration pair.
 struct FilterState {

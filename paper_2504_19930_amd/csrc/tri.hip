@@ -660,37 +660,19 @@ __global__ __launch_bounds__(kThreads) void k_batch_tri(const Args *pairs_g, con
 
 // ---------------------------------------------------------------- preparation
 
-// Bitmaps of the source cells a valid sample may lie in (ok) and must lie in to
-// be certainly valid (those below the last index of every axis: at
-// the last index only the exact coordinate is inside).
-__global__ __launch_bounds__(256) void k_pack_valid(const uint8_t *ok, int32_t nx, uint32_t ny, int32_t nz, uint32_t W,
-                                                    uint32_t *may, uint32_t *must) {
-    const int64_t n = (int64_t)W * ny * nz;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t row = q / W, z = row / ny;
-        const uint32_t xw = (uint32_t)(q - row * W), y = (uint32_t)(row - z * ny);
-        const int32_t x0 = (int32_t)xw * 32;
-        uint32_t v = 0u, u = 0u;
-        for (int b = 0; b < 32 && x0 + b < nx; ++b) {
-            const uint32_t on = ok[row * nx + x0 + b] != 0;
-            v |= on << (31 - b);
-            if (x0 + b + 1 < nx && y + 1 < ny && z + 1 < nz) u |= on << (31 - b);
-        }
-        const int64_t o = y + ny * (xw + W * z);
-        may[o] = v;
-        must[o] = u;
-    }
-}
-
-// Bytes of four slices as dwords (slices past the end zero).
-__global__ __launch_bounds__(256) void k_slices4(const uint8_t *vol, int64_t plane, int32_t nz, uint32_t *out) {
-    const int64_t n = plane * ((nz + 3) / 4);
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t zq = q / plane, xy = q - zq * plane;
+// Bytes of four slices as dwords (slices past the end zero); blockIdx.y 1: of
+// the FOV.
+__global__ __launch_bounds__(256) void k_slices4(const uint8_t *vol, const uint8_t *fov, uint32_t plane, int32_t nz,
+                                                 uint32_t *tz, uint32_t *fz) {
+    const uint8_t *in = blockIdx.y ? fov : vol;
+    uint32_t *out = blockIdx.y ? fz : tz;
+    const uint32_t n = plane * ((uint32_t)(nz + 3) / 4);
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
+        const uint32_t zq = q / plane, xy = q - zq * plane;
         uint32_t v = 0u;
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-            if (4 * zq + s < nz) v |= (uint32_t)vol[xy + plane * (4 * zq + s)] << (8 * s);
+            if ((int32_t)(4 * zq) + s < nz) v |= (uint32_t)in[xy + (int64_t)plane * (4 * zq + s)] << (8 * s);
         out[q] = v;
     }
 }
@@ -699,10 +681,10 @@ __global__ __launch_bounds__(256) void k_slices4(const uint8_t *vol, int64_t pla
 // of four dwords each.
 __global__ __launch_bounds__(256) void k_blocks4(const uint32_t *tz, const uint32_t *fz, int32_t nx, int32_t ny,
                                                  int32_t nz, uint32_t gx, uint32_t gy, uint32_t gz, uint2 *out) {
-    const int64_t n = (int64_t)gx * gy * gz;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < 4 * n; q += (int64_t)gridDim.x * 256) {
-        const int64_t blk = q / 4, r = blk / gx;
-        const int32_t x = 4 * (int32_t)(blk - r * gx) + (int32_t)(q % 4), y0 = 4 * (int32_t)(r % gy), zq = (int32_t)(r / gy);
+    const uint32_t n = gx * gy * gz;
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < 4 * n; q += gridDim.x * 256u) {
+        const uint32_t blk = q / 4, r = blk / gx, zb = r / gy;
+        const int32_t x = 4 * (int32_t)(blk - r * gx) + (int32_t)(q % 4), y0 = 4 * (int32_t)(r - zb * gy), zq = (int32_t)zb;
         uint32_t c = 0u, s = 0u, s2 = 0u;
         for (int32_t y = y0; y < min(y0 + 4, ny) && x < nx; ++y) {
             const int64_t o = ((int64_t)zq * ny + y) * nx + x;
@@ -726,23 +708,39 @@ __global__ __launch_bounds__(256) void k_blocks4(const uint32_t *tz, const uint3
     }
 }
 
-// Sums over blocks of c^3 of the 4^3 ones (c = 2, 4).
-__global__ __launch_bounds__(256) void k_blocks(const uint2 *t4, uint32_t c, uint32_t g4x, uint32_t g4y, uint32_t g4z,
-                                                uint32_t gx, uint32_t gy, uint32_t gz, uint4 *out) {
-    const int64_t n = (int64_t)gx * gy * gz;
-    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
-        const int64_t r = q / gx;
-        const uint32_t x0 = c * (uint32_t)(q - r * gx), y0 = c * (uint32_t)(r % gy), z0 = c * (uint32_t)(r / gy);
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        for (uint32_t z = z0; z < min(z0 + c, g4z); ++z)
-            for (uint32_t y = y0; y < min(y0 + c, g4y); ++y)
-                for (uint32_t x = x0; x < min(x0 + c, g4x); ++x) {
-                    const uint2 b = t4[x + (int64_t)g4x * (y + (int64_t)g4y * z)];
-                    v.x += b.x & 255u;
-                    v.y += b.x >> 8;
-                    v.z += b.y;
-                }
-        out[q] = v;
+// Sums over the blocks of side 8 and 16: a wave makes one of 16 from its 64
+// blocks of 4^3, a lane each (one thread over all 64 waited on a chain of
+// loads: 4 + 12 us for both sides, 4 us so).
+__global__ __launch_bounds__(256) void k_blocks(const uint2 *t4, uint32_t g4x, uint32_t g4y, uint32_t g4z, uint32_t g8x,
+                                                uint32_t g8y, uint32_t g8z, uint32_t gx, uint32_t gy, uint32_t gz,
+                                                uint4 *t8, uint4 *t16) {
+    const uint32_t n = gx * gy * gz, lane = threadIdx.x % 64;
+    const uint32_t lx = lane & 3u, ly = (lane >> 2) & 3u, lz = lane >> 4;
+    for (uint32_t w = blockIdx.x * 4 + threadIdx.x / 64; w < n; w += gridDim.x * 4) {
+        const uint32_t t = w / gx, bz = t / gy, bx = w - t * gx, by = t - bz * gy;
+        const uint32_t x = 4 * bx + lx, y = 4 * by + ly, z = 4 * bz + lz;
+        uint32_t c = 0u, s = 0u, s2 = 0u;
+        if (x < g4x && y < g4y && z < g4z) {
+            const uint2 b = t4[x + (int64_t)g4x * (y + (int64_t)g4y * z)];
+            c = b.x & 255u;
+            s = b.x >> 8;
+            s2 = b.y;
+        }
+        const auto add = [&](int o) {
+            c += __shfl_xor(c, o);
+            s += __shfl_xor(s, o);
+            s2 += __shfl_xor(s2, o);
+        };
+        add(1);
+        add(4);
+        add(16);
+        const uint32_t x8 = 2 * bx + lx / 2, y8 = 2 * by + ly / 2, z8 = 2 * bz + lz / 2;
+        if ((lane & 21u) == 0u && x8 < g8x && y8 < g8y && z8 < g8z)
+            t8[x8 + (int64_t)g8x * (y8 + (int64_t)g8y * z8)] = make_uint4(c, s, s2, 0u);
+        add(2);
+        add(8);
+        add(32);
+        if (lane == 0) t16[w] = make_uint4(c, s, s2, 0u);
     }
 }
 
@@ -825,29 +823,19 @@ TriSizes tri_sizes(const int32_t sn[3], const int32_t tn[3]) {
     return s;
 }
 
-hipError_t launch_tri_source(const uint8_t *ok, const int32_t n[3], uint32_t *may, uint32_t *must, uint16_t *gap_x,
-                             uint16_t *gap_y, uint8_t *field, hipStream_t s) {
-    const uint32_t W = cells(n[0], 32);
-    hipLaunchKernelGGL(k_pack_valid, dim3(blocks_for((int64_t)W * n[1] * n[2])), dim3(256), 0, s, ok, n[0],
-                       (uint32_t)n[1], n[2], W, may, must);
-    return launch_field(may, must, n, gap_x, gap_y, field, s);
-}
-
 hipError_t launch_tri_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint32_t *tz, uint32_t *fz,
                              void *t4, void *t8, void *t16, hipStream_t s) {
     const int64_t plane = (int64_t)n[0] * n[1];
-    const unsigned b = blocks_for(plane * ((n[2] + 3) / 4));
-    hipLaunchKernelGGL(k_slices4, dim3(b), dim3(256), 0, s, vol, plane, n[2], tz);
-    if (fov) hipLaunchKernelGGL(k_slices4, dim3(b), dim3(256), 0, s, fov, plane, n[2], fz);
+    hipLaunchKernelGGL(k_slices4, dim3(blocks_for(plane * ((n[2] + 3) / 4)), fov ? 2 : 1), dim3(256), 0, s, vol, fov,
+                       (uint32_t)plane, n[2], tz, fz);
     uint32_t g[3][3];
     for (int l = 0; l < 3; ++l)
         for (int d = 0; d < 3; ++d) g[l][d] = cells(n[d], 4 << l);
     const auto count = [&](int l) { return (int64_t)g[l][0] * g[l][1] * g[l][2]; };
     hipLaunchKernelGGL(k_blocks4, dim3(blocks_for(4 * count(0))), dim3(256), 0, s, (const uint32_t *)tz,
                        (const uint32_t *)(fov ? fz : nullptr), n[0], n[1], n[2], g[0][0], g[0][1], g[0][2], (uint2 *)t4);
-    for (int l = 1; l < 3; ++l)
-        hipLaunchKernelGGL(k_blocks, dim3(blocks_for(count(l))), dim3(256), 0, s, (const uint2 *)t4, 1u << l, g[0][0],
-                           g[0][1], g[0][2], g[l][0], g[l][1], g[l][2], (uint4 *)(l == 1 ? t8 : t16));
+    hipLaunchKernelGGL(k_blocks, dim3(blocks_for(64 * count(2))), dim3(256), 0, s, (const uint2 *)t4, g[0][0], g[0][1],
+                       g[0][2], g[1][0], g[1][1], g[1][2], g[2][0], g[2][1], g[2][2], (uint4 *)t8, (uint4 *)t16);
     return hipGetLastError();
 }
 
