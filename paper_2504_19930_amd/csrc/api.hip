@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -213,6 +214,32 @@ struct smc_ctx {
         return SMC_OK;
     }
 
+    // A set of arrays in one allocation, in the order they were reserved, each
+    // aligned to 256 bytes or (packed) right behind the one before; *out is set by
+    // take_reserved.  A context has some twenty arrays, and an allocation of its
+    // own and its release cost each of them 5 to 80 us.
+    struct Reserved {
+        void **out;
+        size_t at;
+    };
+    std::vector<Reserved> reserved;
+    size_t reserved_bytes = 0;
+    template <typename T>
+    void reserve(T **out, size_t count, bool packed_behind = false) {
+        if (!packed_behind) reserved_bytes = (reserved_bytes + 255) & ~(size_t)255;
+        reserved.push_back({(void **)out, reserved_bytes});
+        reserved_bytes += count * sizeof(T);
+    }
+    smc_status take_reserved() {
+        char *block = nullptr;
+        const smc_status st = alloc(&block, reserved_bytes);
+        if (st == SMC_OK)
+            for (const Reserved &r : reserved) *r.out = block + r.at;
+        reserved.clear();
+        reserved_bytes = 0;
+        return st;
+    }
+
     // layout of a launch over a dispersed cloud (see prior_dispersed)
     int dispersed_layout() const {
         return mode == kModeImageTrilinear && layout == kLayoutLerp && packed[kLayoutOctTile] ? kLayoutOctTile
@@ -350,7 +377,9 @@ smc_status search_sentinel(smc_ctx *c, int layout, uint64_t *sent, bool *ok) {
     return SMC_OK;
 }
 
-smc_status prepare_layout(smc_ctx *c, int layout) {
+//
+// buffer: where the layout goes, if it has been allocated already.
+smc_status prepare_layout(smc_ctx *c, int layout, void *buffer = nullptr) {
     if (c->mode != kModeImageTrilinear || layout == kLayoutRaw || c->packed[layout]) return SMC_OK;
     smc_status st;
     // the tiled octets serve the first evaluation of a dispersed prior
@@ -358,8 +387,9 @@ smc_status prepare_layout(smc_ctx *c, int layout) {
                tiles = layout == kLayoutOctTile ||
                        (lerp && !c->packed[kLayoutOctTile] && layout_fits(kLayoutOctTile, c->sn));
     const auto take = [&](int l) { return c->alloc((uint8_t **)&c->packed[l], packed_bytes(l, c->sn)); };
-    if (tiles && (st = take(kLayoutOctTile)) != SMC_OK) return st;
-    if (layout != kLayoutOctTile && (st = take(layout)) != SMC_OK) return st;
+    if (buffer) c->packed[layout] = buffer;
+    else if ((st = take(layout)) != SMC_OK) return st;
+    if (lerp && tiles && (st = take(kLayoutOctTile)) != SMC_OK) return st;
     uint64_t sent = 0;
     bool ok = false;
     if (layout == kLayoutPairX || layout == kLayoutQuadXY) {
@@ -415,7 +445,6 @@ smc_status add_layout(smc_ctx *c, int layout) {
 }
 
 smc_status launch_prior(smc_ctx *c) {
-    HIP_TRY(launch_fill_u64(c->f.sums, 6ull * (c->f.n + 1), c->stream));
     HIP_TRY(launch_init_particles(c->f, c->stream));
     c->k_done = 0;
     c->prior_dispersed = !c->f.has_proposal;
@@ -435,15 +464,14 @@ smc_status ensure_eval(smc_ctx *c, uint32_t n) {
     if (n <= c->eval_cap) return SMC_OK;
     // grow: old buffers stay in c->allocs until destroy (small)
     smc_status st;
-    if ((st = c->alloc(&c->x_eval, 6ull * n)) != SMC_OK) return st;
-    if ((st = c->alloc(&c->w_eval, 12ull * n)) != SMC_OK) return st;
-    if ((st = c->alloc(&c->s_eval, 6ull * n)) != SMC_OK) return st;
-    if ((st = c->alloc(&c->z_eval, n)) != SMC_OK) return st;
-    if (c->p.score == SMC_SCORE_MI) {
-        const uint64_t words = (uint64_t)kMiBins * kMiBins * n;
-        if ((st = c->alloc(&c->hist_eval, words)) != SMC_OK) return st;
-        HIP_TRY(launch_fill_u64((unsigned long long *)c->hist_eval, words / 2, c->stream));
-    }
+    const uint64_t words = c->p.score == SMC_SCORE_MI ? (uint64_t)kMiBins * kMiBins * n : 0;
+    c->reserve(&c->x_eval, 6ull * n);
+    c->reserve(&c->w_eval, 12ull * n);
+    c->reserve(&c->s_eval, 6ull * n);
+    c->reserve(&c->z_eval, n);
+    if (words) c->reserve(&c->hist_eval, words);
+    if ((st = c->take_reserved()) != SMC_OK) return st;
+    if (words) HIP_TRY(launch_fill_u64((unsigned long long *)c->hist_eval, words / 2, c->stream));
     c->eval_cap = n;
     return SMC_OK;
 }
@@ -537,77 +565,113 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         return s;
     };
 
+    // every array of the context but the packed layouts, in one allocation; what
+    // the host reads together lies together (read_run, smc_get_particles)
+    FilterState &f = c->f;
+    const bool images = c->mode != kModeMask, corners = c->mode == kModeImageTrilinear && src->fov;
+    c->reserve(&f.x, 6ull * n);
+    c->reserve(&f.lw, n, true);
+    c->reserve(&f.anc, n, true);
+    c->reserve(&f.est, 6);
+    c->reserve(&f.flags, 4, true);
+    c->reserve(&f.trace_ess, K, true);
+    c->reserve(&f.trace_score, K + 1ull, true);
+    c->reserve(&f.trace_est, 6ull * K, true);
+    c->reserve(&f.x_next, 6ull * n);
+    c->reserve(&f.words, 12ull * (n + 1));
+    c->reserve(&f.sums, 6ull * (n + 1));
+    c->reserve(&f.w, n);
+    c->reserve(&f.cdf, n);
+    c->reserve(&c->prep, kPrepWords);
+    const uint64_t hist_words = p->score == SMC_SCORE_MI ? (uint64_t)kMiBins * kMiBins * (n + 1ull) : 0;
+    if (hist_words) c->reserve(&c->hist, hist_words);
+    uint8_t *field = nullptr, *t4 = nullptr, *t8 = nullptr, *t16 = nullptr, *bits = nullptr, *scratch = nullptr;
+    uint8_t *tz = nullptr, *fz = nullptr, *layout_buf = nullptr;
+    const DiceSizes ds = dice_sizes(c->sn, c->tn);
+    const TriSizes ts = tri_sizes(c->sn, c->tn);
+    // (scratch of the field's passes: gap_x, gap_y, and an image's two bitmaps)
+    const uint64_t scratch_bytes = images ? 2 * ts.gap + 2 * ts.bits : ds.gap_x + ds.gap_y;
+    if (!layout_fits(c->layout, c->sn)) c->layout = layout_fits(kLayoutOct, c->sn) ? kLayoutOct : kLayoutRaw;
+    if (!images) {
+        c->reserve(&c->src_prep, vs);
+        c->reserve(&c->tgt_prep, vt);
+        c->reserve(&bits, ds.bits);
+        c->reserve(&field, ds.field);
+        c->reserve(&t4, ds.t4);
+        c->reserve(&t8, ds.t8);
+        c->reserve(&t16, ds.t16);
+        c->reserve(&c->work, kWorkSlots * kWorkSlotWords);
+        c->reserve(&scratch, scratch_bytes);
+    } else if (corners) {
+        c->reserve(&c->src_ok, vs);
+        c->reserve(&field, ts.field);
+        c->reserve(&tz, ts.tz);
+        if (tgt->fov) c->reserve(&fz, ts.tz);
+        c->reserve(&t4, ts.t4);
+        c->reserve(&t8, ts.t8);
+        c->reserve(&t16, ts.t16);
+        // the field is done before the layout is packed: it borrows its memory
+        if (c->layout != kLayoutRaw && packed_bytes(c->layout, c->sn) >= scratch_bytes) {
+            if ((st = c->alloc(&layout_buf, packed_bytes(c->layout, c->sn))) != SMC_OK) return bail(st);
+            scratch = layout_buf;
+        } else {
+            c->reserve(&scratch, scratch_bytes);
+        }
+    } else if (src->fov) {
+        c->src_ok = const_cast<uint8_t *>(src->fov);
+    }
+    if ((st = c->take_reserved()) != SMC_OK) return bail(st);
+
     // prepared inputs
-    if (c->mode == kModeMask) {
-        if ((st = c->alloc(&c->src_prep, vs)) != SMC_OK) return bail(st);
-        if ((st = c->alloc(&c->tgt_prep, vt)) != SMC_OK) return bail(st);
-        const DiceSizes ds = dice_sizes(c->sn, c->tn);
-        uint8_t *bits, *gap_x, *gap_y, *field, *t4, *t8, *t16;
-        if ((st = c->alloc(&bits, ds.bits)) != SMC_OK || (st = c->alloc(&gap_x, ds.gap_x)) != SMC_OK ||
-            (st = c->alloc(&gap_y, ds.gap_y)) != SMC_OK || (st = c->alloc(&field, ds.field)) != SMC_OK ||
-            (st = c->alloc(&t4, ds.t4)) != SMC_OK || (st = c->alloc(&t8, ds.t8)) != SMC_OK ||
-            (st = c->alloc(&t16, ds.t16)) != SMC_OK || (st = c->alloc(&c->work, kWorkSlots * kWorkSlotWords)) != SMC_OK)
-            return bail(st);
+    if (!images) {
+        uint16_t *gap_x = (uint16_t *)scratch, *gap_y = (uint16_t *)(scratch + ds.gap_x);
         c->dice.bits = (const uint32_t *)bits;
         c->dice.field = field;
         c->dice.t4 = t4;
         c->dice.t8 = (const uint32_t *)t8;
         c->dice.t16 = (const uint32_t *)t16;
         if (launch_mask_source(src->data, src->fov, c->sn, c->src_prep, (uint32_t *)bits, c->stream) != hipSuccess ||
-            launch_field((const uint32_t *)bits, (const uint32_t *)bits, c->sn, (uint16_t *)gap_x, (uint16_t *)gap_y,
-                         field, c->stream) != hipSuccess ||
+            launch_field((const uint32_t *)bits, (const uint32_t *)bits, c->sn, gap_x, gap_y, field, c->stream) !=
+                hipSuccess ||
             launch_dice_target(tgt->data, tgt->fov, c->tn, c->tgt_prep, t4, (uint32_t *)t8, (uint32_t *)t16,
                                c->stream) != hipSuccess ||
             launch_fill_u64(c->work, kWorkSlots * kWorkSlotWords, c->stream) != hipSuccess)
             return bail(fail(SMC_EDEVICE, "mask preparation launch failed"));
-    } else if (src->fov && c->mode == kModeImageNearest) {
-        c->src_ok = const_cast<uint8_t *>(src->fov);
-    } else if (src->fov) {
-        if ((st = c->alloc(&c->src_ok, vs)) != SMC_OK) return bail(st);
-        const TriSizes ts = tri_sizes(c->sn, c->tn);
-        uint8_t *may, *must, *gap_x, *gap_y, *field, *tz, *fz = nullptr, *t4, *t8, *t16;
-        if ((st = c->alloc(&may, ts.bits)) != SMC_OK || (st = c->alloc(&must, ts.bits)) != SMC_OK ||
-            (st = c->alloc(&gap_x, ts.gap)) != SMC_OK || (st = c->alloc(&gap_y, ts.gap)) != SMC_OK ||
-            (st = c->alloc(&field, ts.field)) != SMC_OK || (st = c->alloc(&tz, ts.tz)) != SMC_OK ||
-            (tgt->fov && (st = c->alloc(&fz, ts.tz)) != SMC_OK) || (st = c->alloc(&t4, ts.t4)) != SMC_OK ||
-            (st = c->alloc(&t8, ts.t8)) != SMC_OK || (st = c->alloc(&t16, ts.t16)) != SMC_OK)
-            return bail(st);
+    } else if (corners) {
+        uint32_t *may = (uint32_t *)scratch, *must = (uint32_t *)(scratch + ts.bits);
+        uint16_t *gap_x = (uint16_t *)(scratch + 2 * ts.bits), *gap_y = (uint16_t *)(scratch + 2 * ts.bits + ts.gap);
         c->tri.field = field;
         c->tri.tz = (const uint32_t *)tz;
         c->tri.fz = (const uint32_t *)fz;
         c->tri.t4 = t4;
         c->tri.t8 = t8;
         c->tri.t16 = t16;
-        if (launch_corner_valid(src->fov, c->sn, c->src_ok, (uint32_t *)may, (uint32_t *)must, c->stream) != hipSuccess ||
-            launch_field((const uint32_t *)may, (const uint32_t *)must, c->sn, (uint16_t *)gap_x, (uint16_t *)gap_y,
-                         field, c->stream) != hipSuccess ||
+        if (launch_corner_valid(src->fov, c->sn, c->src_ok, may, must, c->stream) != hipSuccess ||
+            launch_field(may, must, c->sn, gap_x, gap_y, field, c->stream) != hipSuccess ||
             launch_tri_target(tgt->data, tgt->fov, c->tn, (uint32_t *)tz, (uint32_t *)fz, t4, t8, t16, c->stream) !=
                 hipSuccess)
             return bail(fail(SMC_EDEVICE, "image preparation launch failed"));
     }
 
     // exact per-volume sums -> statistics, and the hits of the packed layouts
-    if ((st = c->alloc(&c->prep, kPrepWords)) != SMC_OK) return bail(st);
     const uint8_t *const vols[2] = {tgt->data, src->data}, *const fovs[2] = {tgt->fov, src->fov};
     const int64_t sizes[2] = {vt, vs};
     if (launch_fill_u64(c->prep, kPrepWords, c->stream) != hipSuccess ||
         launch_volume_sums(vols, fovs, sizes, c->prep, c->stream) != hipSuccess)
         return bail(fail(SMC_EDEVICE, "volume statistics launch failed"));
 
-    if (!layout_fits(c->layout, c->sn)) c->layout = layout_fits(kLayoutOct, c->sn) ? kLayoutOct : kLayoutRaw;
-    if ((st = prepare_layout(c, c->layout)) != SMC_OK) return bail(st);
+    if ((st = prepare_layout(c, c->layout, layout_buf)) != SMC_OK) return bail(st);
 
     unsigned long long hs[kPrepWords];
     if (hipMemcpyAsync(hs, c->prep, sizeof hs, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
         return bail(fail(SMC_EDEVICE, "reading volume statistics failed: %s", hipGetErrorString(hipGetLastError())));
     if ((st = settle_layouts(c, hs + kPrepHits)) != SMC_OK) return bail(st);
-    const Stats ts = stats_from_sums(hs), ss = stats_from_sums(hs + 4);
-    if (ts.count == 0) return bail(fail(SMC_EINVAL, "the target FOV is empty"));
-    c->tgt_on = ts.on;
-    c->tgt_count = ts.count;
+    const Stats tstat = stats_from_sums(hs), sstat = stats_from_sums(hs + 4);
+    if (tstat.count == 0) return bail(fail(SMC_EINVAL, "the target FOV is empty"));
+    c->tgt_on = tstat.on;
+    c->tgt_count = tstat.count;
 
-    FilterState &f = c->f;
     f.n = n;
     f.n_iters = K;
     f.seed = p->seed;
@@ -617,12 +681,12 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     f.geom.ss[0] = src->sx; f.geom.ss[1] = src->sy; f.geom.ss[2] = src->sz;
     f.nearest = c->mode != kModeImageTrilinear;
     f.sc.kind = p->score;
-    f.sc.t_on = ts.on;
-    f.sc.min_n = (uint64_t)ceil(p->min_overlap_frac * (double)ts.count);
-    f.sc.mu_s = ss.mu;
-    f.sc.sd_s = ss.sd;
-    f.sc.mu_t = ts.mu;
-    f.sc.sd_t = ts.sd;
+    f.sc.t_on = tstat.on;
+    f.sc.min_n = (uint64_t)ceil(p->min_overlap_frac * (double)tstat.count);
+    f.sc.mu_s = sstat.mu;
+    f.sc.sd_s = sstat.sd;
+    f.sc.mu_t = tstat.mu;
+    f.sc.sd_t = tstat.sd;
     f.sc.sigma = p->sigma_score;
     for (int d = 0; d < 6; ++d) {
         f.x0[d] = p->x0[d];
@@ -633,22 +697,8 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     }
     f.anneal = p->anneal;
     f.wide = p->rotation_mode == SMC_ROTATION_WIDE ? 1 : 0;
-    if ((st = c->alloc(&f.x, 6ull * n)) != SMC_OK ||
-        (st = c->alloc(&f.x_next, 6ull * n)) != SMC_OK ||
-        (st = c->alloc(&f.words, 12ull * (n + 1))) != SMC_OK ||
-        (st = c->alloc(&f.sums, 6ull * (n + 1))) != SMC_OK ||
-        (st = c->alloc(&f.lw, n)) != SMC_OK || (st = c->alloc(&f.w, n)) != SMC_OK ||
-        (st = c->alloc(&f.cdf, n)) != SMC_OK || (st = c->alloc(&f.anc, n)) != SMC_OK ||
-        (st = c->alloc(&f.est, 6)) != SMC_OK || (st = c->alloc(&f.trace_score, K + 1ull)) != SMC_OK ||
-        (st = c->alloc(&f.trace_ess, K)) != SMC_OK || (st = c->alloc(&f.trace_est, 6ull * K)) != SMC_OK ||
-        (st = c->alloc(&f.flags, 4)) != SMC_OK)
-        return bail(st);
-    if (p->score == SMC_SCORE_MI) {
-        const uint64_t words = (uint64_t)kMiBins * kMiBins * (n + 1ull);
-        if ((st = c->alloc(&c->hist, words)) != SMC_OK) return bail(st);
-        if (launch_fill_u64((unsigned long long *)c->hist, words / 2, c->stream) != hipSuccess)
-            return bail(fail(SMC_EDEVICE, "histogram clear failed"));
-    }
+    if (hist_words && launch_fill_u64((unsigned long long *)c->hist, hist_words / 2, c->stream) != hipSuccess)
+        return bail(fail(SMC_EDEVICE, "histogram clear failed"));
     if ((st = check_items(c)) != SMC_OK) return bail(st);
     if ((st = launch_prior(c)) != SMC_OK) return bail(st);
     *out = c;
@@ -862,6 +912,41 @@ smc_status smc_exhaustive(smc_ctx *c, const double lo[6], const double step[6], 
     return SMC_OK;
 }
 
+namespace {
+// A device block on the host.  A copy into pageable memory costs some 9 us
+// whatever its size up to a few tens of KB, so up to kWholeBlock bytes what
+// lies together is copied together and handed out from here.
+constexpr size_t kWholeBlock = 64 << 10;
+smc_status read_block(smc_ctx *c, const void *dev, size_t bytes, std::unique_ptr<char[]> *host) {
+    host->reset(new (std::nothrow) char[bytes]);
+    if (!*host) return fail(SMC_ENOMEM, "host allocation failed");
+    HIP_TRY(hipMemcpyAsync(host->get(), dev, bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return SMC_OK;
+}
+
+// The run's record: estimate, flags, then ESS, scores and estimates of the
+// iterations (the order of the reservations in smc_init).
+size_t record_bytes(const smc_ctx *c) { return 48 + 16 + 8 * (8ull * c->f.n_iters + 1); }
+struct RunRecord {
+    std::unique_ptr<char[]> host;
+    const double *est;
+    const int32_t *flags;
+    const double *ess, *score, *est_k;
+};
+smc_status read_run(smc_ctx *c, RunRecord *r) {
+    const smc_status st = read_block(c, c->f.est, record_bytes(c), &r->host);
+    if (st != SMC_OK) return st;
+    const auto at = [&](const void *dev) { return r->host.get() + ((const char *)dev - (const char *)c->f.est); };
+    r->est = (const double *)at(c->f.est);
+    r->flags = (const int32_t *)at(c->f.flags);
+    r->ess = (const double *)at(c->f.trace_ess);
+    r->score = (const double *)at(c->f.trace_score);
+    r->est_k = (const double *)at(c->f.trace_est);
+    return SMC_OK;
+}
+}  // namespace
+
 smc_status smc_estimate(smc_ctx *c, double params[6], double mat3x4[12], double *score, double *ess) {
     if (!c) return fail(SMC_EINVAL, "ctx is NULL");
     smc_status st;
@@ -869,13 +954,22 @@ smc_status smc_estimate(smc_ctx *c, double params[6], double mat3x4[12], double 
     if ((st = set_device(c)) != SMC_OK) return c->mark(st);
     double est[6], sc = NAN, e = NAN;
     int32_t flags[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(est, c->f.est, sizeof est, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(flags, c->f.flags, sizeof flags, hipMemcpyDeviceToHost, c->stream));
-    if (c->k_done >= 1)
-        HIP_TRY(hipMemcpyAsync(&e, c->f.trace_ess + (c->k_done - 1), sizeof e, hipMemcpyDeviceToHost, c->stream));
-    if (c->k_done == c->f.n_iters)
-        HIP_TRY(hipMemcpyAsync(&sc, c->f.trace_score + c->f.n_iters, sizeof sc, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (record_bytes(c) <= kWholeBlock) {
+        RunRecord r;
+        if ((st = read_run(c, &r)) != SMC_OK) return st;
+        memcpy(est, r.est, sizeof est);
+        memcpy(flags, r.flags, sizeof flags);
+        if (c->k_done >= 1) e = r.ess[c->k_done - 1];
+        if (c->k_done == c->f.n_iters) sc = r.score[c->f.n_iters];
+    } else {
+        HIP_TRY(hipMemcpyAsync(est, c->f.est, sizeof est, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(hipMemcpyAsync(flags, c->f.flags, sizeof flags, hipMemcpyDeviceToHost, c->stream));
+        if (c->k_done >= 1)
+            HIP_TRY(hipMemcpyAsync(&e, c->f.trace_ess + (c->k_done - 1), sizeof e, hipMemcpyDeviceToHost, c->stream));
+        if (c->k_done == c->f.n_iters)
+            HIP_TRY(hipMemcpyAsync(&sc, c->f.trace_score + c->f.n_iters, sizeof sc, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+    }
     if (score && c->k_done < c->f.n_iters) {
         int64_t m[6];
         if ((st = smc_evaluate(c, est, 1, m)) != SMC_OK) return st;
@@ -896,6 +990,14 @@ smc_status smc_get_particles(smc_ctx *c, double *states, double *logw, int32_t *
     if ((st = c->check_sticky()) != SMC_OK) return st;
     if ((st = set_device(c)) != SMC_OK) return c->mark(st);
     const size_t n = c->f.n;
+    if (60 * n <= kWholeBlock) {
+        std::unique_ptr<char[]> host;
+        if ((st = read_block(c, c->f.x, 60 * n, &host)) != SMC_OK) return st;
+        if (states) memcpy(states, host.get(), 48 * n);
+        if (logw) memcpy(logw, host.get() + 48 * n, 8 * n);
+        if (anc) memcpy(anc, host.get() + 56 * n, 4 * n);
+        return SMC_OK;
+    }
     if (states) HIP_TRY(hipMemcpyAsync(states, c->f.x, 48 * n, hipMemcpyDeviceToHost, c->stream));
     if (logw) HIP_TRY(hipMemcpyAsync(logw, c->f.lw, 8 * n, hipMemcpyDeviceToHost, c->stream));
     if (anc) HIP_TRY(hipMemcpyAsync(anc, c->f.anc, 4 * n, hipMemcpyDeviceToHost, c->stream));
@@ -909,6 +1011,14 @@ smc_status smc_trace(smc_ctx *c, double *score_k1, double *ess_k, double *est_6k
     if ((st = c->check_sticky()) != SMC_OK) return st;
     if ((st = set_device(c)) != SMC_OK) return c->mark(st);
     const size_t K = c->f.n_iters;
+    if (record_bytes(c) <= kWholeBlock) {
+        RunRecord r;
+        if ((st = read_run(c, &r)) != SMC_OK) return st;
+        if (score_k1) memcpy(score_k1, r.score, 8 * (K + 1));
+        if (ess_k) memcpy(ess_k, r.ess, 8 * K);
+        if (est_6k) memcpy(est_6k, r.est_k, 48 * K);
+        return SMC_OK;
+    }
     if (score_k1) HIP_TRY(hipMemcpyAsync(score_k1, c->f.trace_score, 8 * (K + 1), hipMemcpyDeviceToHost, c->stream));
     if (ess_k) HIP_TRY(hipMemcpyAsync(ess_k, c->f.trace_ess, 8 * K, hipMemcpyDeviceToHost, c->stream));
     if (est_6k) HIP_TRY(hipMemcpyAsync(est_6k, c->f.trace_est, 48 * K, hipMemcpyDeviceToHost, c->stream));
@@ -1570,7 +1680,6 @@ smc_status plan_all(smc_batch *b) {
 // The whole batched run, recorded on b->stream (captured into the graph).
 smc_status record_run(smc_batch *b) {
     HIP_TRY(launch_init_batch(b->states_dev, (uint32_t)b->pairs.size(), b->max_threads, b->stream));
-    for (smc_ctx *c : b->pairs) HIP_TRY(launch_fill_u64(c->f.sums, 6ull * (c->f.n + 1), b->stream));
     // the item queues start empty on every run (a fill kernel, so graph replays clear them too)
     for (int q = 1; q < 4; ++q)
         if (b->cls[q].plan.n_pairs && !b->cls[q].plan.blocks)

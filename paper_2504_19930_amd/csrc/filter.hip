@@ -117,6 +117,7 @@ __device__ __forceinline__ void init_body(const FilterState &f, uint32_t i, uint
         f.flags[1] = 0;
         f.flags[2] = f.has_proposal ? 1 : 0;
     }
+    for (uint64_t q = i; q < 6ull * (f.n + 1ull); q += stride) f.sums[q] = 0ull;
     const uint32_t nt = f.n_iters + 1;
     for (uint32_t q = i; q < nt; q += stride) {
         f.trace_score[q] = __builtin_nan("");
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(256) void k_init(const FilterState f) {
 __global__ __launch_bounds__(256) void k_init_batch(const FilterState *fs) {
     const FilterState &f = fs[blockIdx.y];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < f.n || i < f.n_iters + 1) init_body(f, i, gridDim.x * blockDim.x);
+    init_body(f, i, gridDim.x * blockDim.x);
 }
 
 __device__ __forceinline__ bool pointer_passed(unsigned long long c, unsigned __int128 scale,

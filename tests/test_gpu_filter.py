@@ -34,3 +34,24 @@ def test_filter_sizes_match_the_oracle(orc, n):
         assert np.allclose(t["est"], o["trace_est"], rtol=0, atol=1e-12)
         assert np.allclose(t["score"], o["trace_score"], rtol=1e-12, atol=1e-15)
     r.close()
+
+
+@pytest.mark.parametrize("n, k", [(1092, 2), (1093, 2), (4, 1023), (4, 1024)])
+def test_reads_of_whole_records_and_of_their_parts(orc, n, k):
+    """Particles and traces are read in one copy up to 64 KiB, piece by piece above."""
+    import torch
+    from paper_2504_19930_amd import binding
+    pair = synth.shell_pair(seed=3, side=8)
+    prm = config.default_params("dice", n, k, 10.0, 1.0, seed=4)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    r = binding.Registration(dev(pair["src"]), dev(pair["tgt"]), prm)
+    o = orc.smc_run(orc.Volume(pair["src"]), orc.Volume(pair["tgt"]), prm)
+    e = r.run()
+    p, t = r.particles(), r.trace()
+    assert np.array_equal(p["ancestors"], o["ancestors"])
+    assert np.allclose(p["states"], o["states"], rtol=0, atol=1e-12)
+    assert np.allclose(p["logw"], o["logw"], rtol=1e-12, atol=1e-12)
+    assert np.allclose(t["score"], o["trace_score"], rtol=1e-12, atol=1e-15)
+    assert np.allclose(t["est"], o["trace_est"], rtol=0, atol=1e-12)
+    assert e["score"] == t["score"][-1] and e["ess"] == t["ess"][-1]
+    r.close()
