@@ -507,12 +507,17 @@ void pool_frame_constants(smc_ctx *c) {
     c->f.sc.min_n = (uint64_t)ceil(c->p.min_overlap_frac * (double)count);
 }
 
-// Score a device particle set with the context's kernel; sums into s_eval.
-smc_status evaluate_device(smc_ctx *c, const double *x_dev, uint32_t n) {
+// Score n states on the host with the context's kernel; sums into s_eval.
+smc_status evaluate_states(smc_ctx *c, const double *states, uint32_t n) {
     smc_status st = ensure_eval(c, n);
     if (st != SMC_OK) return st;
-    HIP_TRY(launch_words(x_dev, n, c->f.geom, c->f.nearest, c->w_eval, c->stream));
-    HIP_TRY(launch_fill_u64(c->s_eval, 6ull * n, c->stream));
+    if (n <= kFewStates) {
+        HIP_TRY(launch_words_few(states, n, c->f.geom, c->f.nearest, c->w_eval, c->s_eval, c->stream));
+    } else {
+        if (hipMemcpyAsync(c->x_eval, states, 48ull * n, hipMemcpyHostToDevice, c->stream) != hipSuccess)
+            return fail(SMC_EDEVICE, "upload of states failed");
+        HIP_TRY(launch_words(c->x_eval, n, c->f.geom, c->f.nearest, c->w_eval, c->s_eval, c->stream));
+    }
     HIP_TRY(launch_score_frames(c, c->w_eval, c->s_eval, c->hist_eval, 0, n, false));
     return SMC_OK;
 }
@@ -584,7 +589,15 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     c->reserve(&f.cdf, n);
     c->reserve(&c->prep, kPrepWords);
     const uint64_t hist_words = p->score == SMC_SCORE_MI ? (uint64_t)kMiBins * kMiBins * (n + 1ull) : 0;
-    if (hist_words) c->reserve(&c->hist, hist_words);
+    if (hist_words) {
+        c->reserve(&c->hist, hist_words);
+    } else {
+        // room for the first evaluations of a few states
+        c->reserve(&c->x_eval, 6ull * kFewStates);
+        c->reserve(&c->w_eval, 12ull * kFewStates);
+        c->reserve(&c->s_eval, 6ull * kFewStates);
+        c->reserve(&c->z_eval, kFewStates);
+    }
     uint8_t *field = nullptr, *t4 = nullptr, *t8 = nullptr, *t16 = nullptr, *bits = nullptr, *scratch = nullptr;
     uint8_t *tz = nullptr, *fz = nullptr, *layout_buf = nullptr;
     const DiceSizes ds = dice_sizes(c->sn, c->tn);
@@ -621,6 +634,7 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         c->src_ok = const_cast<uint8_t *>(src->fov);
     }
     if ((st = c->take_reserved()) != SMC_OK) return bail(st);
+    if (!hist_words) c->eval_cap = kFewStates;
 
     // prepared inputs
     if (!images) {
@@ -749,10 +763,7 @@ smc_status smc_evaluate(smc_ctx *c, const double *states, uint32_t n, int64_t *m
     smc_status st;
     if ((st = c->check_sticky()) != SMC_OK) return st;
     if ((st = set_device(c)) != SMC_OK) return c->mark(st);
-    if ((st = ensure_eval(c, n)) != SMC_OK) return c->mark(st);
-    if (hipMemcpyAsync(c->x_eval, states, 48ull * n, hipMemcpyHostToDevice, c->stream) != hipSuccess)
-        return c->mark(fail(SMC_EDEVICE, "upload of states failed"));
-    if ((st = evaluate_device(c, c->x_eval, n)) != SMC_OK) return c->mark(st);
+    if ((st = evaluate_states(c, states, n)) != SMC_OK) return c->mark(st);
     if (hipMemcpyAsync(moments, c->s_eval, 48ull * n, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
         return c->mark(fail(SMC_EDEVICE, "evaluation failed: %s", hipGetErrorString(hipGetLastError())));
@@ -774,8 +785,7 @@ smc_status smc_evaluate_noalloc(smc_ctx *c, const double *states_dev, uint32_t n
     if (!words) return fail(SMC_EDEVICE, "no evaluation scratch resolved for device %d", c->device);
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(moments_dev);
     // every word of particles 0 .. n-1 is rewritten; the sums start from zero
-    HIP_TRY(launch_words(states_dev, n, c->f.geom, c->f.nearest, words, c->stream));
-    HIP_TRY(launch_fill_u64(sums, 6ull * n, c->stream));
+    HIP_TRY(launch_words(states_dev, n, c->f.geom, c->f.nearest, words, sums, c->stream));
     HIP_TRY(launch_score_frames(c, words, sums, nullptr, 0, n, false));
     return SMC_OK;
 }
@@ -838,10 +848,7 @@ smc_status smc_score_particles(smc_ctx *c, const double *states, uint32_t n, dou
     smc_status st;
     if ((st = c->check_sticky()) != SMC_OK) return st;
     if ((st = set_device(c)) != SMC_OK) return c->mark(st);
-    if ((st = ensure_eval(c, n)) != SMC_OK) return c->mark(st);
-    if (hipMemcpyAsync(c->x_eval, states, 48ull * n, hipMemcpyHostToDevice, c->stream) != hipSuccess)
-        return c->mark(fail(SMC_EDEVICE, "upload of states failed"));
-    if ((st = evaluate_device(c, c->x_eval, n)) != SMC_OK) return c->mark(st);
+    if ((st = evaluate_states(c, states, n)) != SMC_OK) return c->mark(st);
     if (launch_scores_from_sums(c->s_eval, n, c->f.sc, c->z_eval, c->stream) != hipSuccess ||
         hipMemcpyAsync(scores, c->z_eval, 8ull * n, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
@@ -1038,7 +1045,7 @@ smc_status smc_set_particles(smc_ctx *c, const double *states, uint32_t k_done) 
     HIP_TRY(hipMemcpyAsync(c->f.x, states, 48ull * c->f.n, hipMemcpyHostToDevice, c->stream));
     // a caller's set is not a proposal draw: no importance correction
     HIP_TRY(hipMemcpyAsync(c->f.flags + 2, &kZeroFlag, sizeof kZeroFlag, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(launch_words(c->f.x, c->f.n, c->f.geom, c->f.nearest, c->f.words, c->stream));
+    HIP_TRY(launch_words(c->f.x, c->f.n, c->f.geom, c->f.nearest, c->f.words, nullptr, c->stream));
     HIP_TRY(launch_fill_u64(c->f.sums, 6ull * (c->f.n + 1), c->stream));
     // the host copy must outlive the upload
     HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1104,8 +1111,8 @@ smc_status smc_set_state(smc_ctx *c, const void *buf, size_t len) {
     }
     // the state holds no proposal densities: a restored set gets no importance correction
     HIP_TRY(hipMemcpyAsync(c->f.flags + 2, &kZeroFlag, sizeof kZeroFlag, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(launch_words(c->f.x, c->f.n, c->f.geom, c->f.nearest, c->f.words, c->stream));
-    HIP_TRY(launch_words(c->f.est, 1, c->f.geom, c->f.nearest, c->f.words + 12 * n, c->stream));
+    HIP_TRY(launch_words(c->f.x, c->f.n, c->f.geom, c->f.nearest, c->f.words, nullptr, c->stream));
+    HIP_TRY(launch_words(c->f.est, 1, c->f.geom, c->f.nearest, c->f.words + 12 * n, nullptr, c->stream));
     HIP_TRY(launch_fill_u64(c->f.sums, 6ull * (n + 1), c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->k_done = (uint32_t)h.k_done;
@@ -1259,7 +1266,7 @@ smc_status smc_autotune(smc_ctx *c, uint32_t reps, double *best_ms) {
                 xs[6ull * i + d] = c->p.x0[d] + 0.05 * c->p.limit[d] * (2.0 * (h - floor(h)) - 1.0);
             }
         if (hipMemcpyAsync(c->x_eval, xs.data(), 48ull * np, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-            launch_words(c->x_eval, np, c->f.geom, c->f.nearest, c->w_eval, c->stream) != hipSuccess ||
+            launch_words(c->x_eval, np, c->f.geom, c->f.nearest, c->w_eval, nullptr, c->stream) != hipSuccess ||
             hipStreamSynchronize(c->stream) != hipSuccess)
             return c->mark(fail(SMC_EDEVICE, "autotune particle set failed"));
     }

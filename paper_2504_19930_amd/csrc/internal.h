@@ -98,7 +98,7 @@ struct ScoreLaunch {
     uint64_t sentinel;
     int layout;               // SourceLayout
     int pt;                   // particles per workgroup: 4, 8 or 16
-    int zchunk;               // target z-extent of a tile (0 = up to 256)
+    int zchunk;               // target z-extent of a tile, less in launches of few items (0 = up to 256)
     // masks: only a and c are needed (the filter's launches), by blocks of the
     // target on the source's distance field (dice.hip); false: all four counts
     bool ac = false;
@@ -288,7 +288,12 @@ hipError_t launch_ghost_final(const FilterState &f, hipStream_t s);
 // Weighted mean (out[0..5]) and per-axis weighted variance (out[6..11]) of the
 // particle set under the normalised weights of the last evaluation.
 hipError_t launch_cloud_moments(const FilterState &f, double *out, hipStream_t s);
-hipError_t launch_words(const double *x, uint32_t n, const Geom &g, bool nearest, float *words, hipStream_t s);
+// recipe words of n device states; sums (or nullptr): 6 n words, cleared
+hipError_t launch_words(const double *x, uint32_t n, const Geom &g, bool nearest, float *words,
+                        unsigned long long *sums, hipStream_t s);
+constexpr uint32_t kFewStates = 32;
+hipError_t launch_words_few(const double *host, uint32_t n, const Geom &g, bool nearest, float *words,
+                            unsigned long long *sums, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, hipStream_t s);
 // Mutual information: scores of particles p0 .. p0 + np - 1 from their joint
 // histograms into their sums (overlap count, score bits), clearing the
