@@ -20,11 +20,22 @@
 // one-voxel margin; the workgroup copies that box of each frame into LDS with
 // 16-byte loads, and the eight taps are LDS reads instead of byte gathers
 // through the texture path (a cycle per distinct cache line a quarter-wave
-// touches, four to eight lines under rotation).  Trilinear, direct: one
-// workgroup per tile and frame, every tap a byte gather; the host takes it
-// when the box would not fit the LDS budget, source rows are not 4-byte
-// aligned, or coordinates reach 2^20 (where the margin would no longer cover
+// touches, four to eight lines under rotation).  Tiles are 16 slices deep, or 8
+// or 4 where the box of a deeper one is too large (rotations by more than some
+// 20 and 35 degrees).  Trilinear, direct: one workgroup per tile and frame, every
+// tap a byte gather; the host takes it when no box fits (strong magnification of
+// the target) or coordinates reach 2^20 (where the margin would no longer cover
 // FP32 rounding).
+//
+// The 16-byte accesses take any address, so odd sizes and views go the same way:
+// trilinear 7 frames of 97 x 150 x 203, 20 degrees, 148 us with byte gathers,
+// 48 staged; 12 frames of 200 x 91 x 77, 38 degrees, 107 -> 40 us (tiles of 8
+// slices); 20 frames of 224 x 208 x 176, 40 degrees, 1030 -> 315 us, 8 degrees
+// 203 -> 194 us; nearest, 97 x 150 x 203, stores byte by byte 110 us, 32 now.
+// What bounds the staged kernel then is the box's chunks (three to four bytes
+// staged per byte written at 8 degrees) and the eight LDS taps.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace smc {
@@ -35,15 +46,17 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Word 3 of a raw buffer resource on gfx9-family GPUs (32-bit data format,
 // untyped loads; out-of-range offsets read zero and writes are dropped).
 constexpr int kBufferWord3 = 0x00020000;
-// LDS bytes of a staged workgroup's source box: with its output tile (4 or 2
+// LDS bytes of a staged workgroup's source box: with its output tile (4, 2 or 1
 // KB) three workgroups per CU for 16-slice tiles (whose registers allow
-// three), four for 8-slice tiles.
+// three), four for 8- and 4-slice tiles.
 constexpr uint32_t kStageBudget16 = 48u * 1024u, kStageBudget8 = 36u * 1024u;
-// Source-box rows of at most four 16-byte chunks; row passes a thread keeps
-// in flight while staging.
+// Source-box rows of at most four 16-byte chunks; chunks a thread keeps in
+// flight while staging.
 constexpr uint32_t kChunks = 4;
 constexpr int kStagePasses = 8;
-// Frames per workgroup of the frame-looping kernels.
+// Frames per workgroup of the frame-looping kernels, at most: the per-tile work
+// shared by four (8, 10 or 20 frames of 224 x 208 x 176 at 40 degrees: 530, 516,
+// 613 us, 312 with four, whose boxes are still in the L2).
 constexpr uint32_t kFrameGroup = 4;
 // Zero bytes at the start of the staged LDS.
 constexpr uint32_t kZeroBytes = 16;
@@ -102,23 +115,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const uint8_t *p, ui
 
 // Write one frame's output tile, assembled in LDS as ZC slices x kWY rows x
 // kWX bytes, with 16-byte stores: thread t takes half t % 2 of row t / 2
-// (rows past the target, and the tail of a row past its end, are skipped; a
-// row whose 16 bytes do not all lie inside, or outputs whose rows are not
-// 4-byte aligned, are written byte by byte).
+// (rows past the target, and the tail of a row past its end, are skipped; 16
+// bytes that do not all lie inside a row are written byte by byte).  The stores
+// take any address.
 template <int ZC>
 __device__ __forceinline__ void store_tile(const uint8_t *tile, const WArgs &a, const WTile &t, int f) {
     static_assert(kWX == 32, "two 16-byte halves per tile row");
     const uint32_t plane = (uint32_t)a.tn0 * (uint32_t)a.tn1;
     const __amdgpu_buffer_rsrc_t rd = buffer_of(a.dst + a.dst_stride * f, plane * (uint32_t)a.tn2);
     const int x = t.x0 + 16 * (int)(threadIdx.x % 2u);
-    const bool vec = a.tn0 % 4 == 0;
 #pragma unroll
     for (int r = (int)(threadIdx.x / 2u); r < ZC * kWY; r += 128) {
         const int k = t.k0 + r / kWY, j = t.y0 + r % kWY;
         if (k >= t.k1 || j >= a.tn1 || x >= a.tn0) continue;
         const u32x4 v = *(const u32x4 *)(tile + r * kWX + (x - t.x0));
         const uint32_t o = (uint32_t)x + (uint32_t)a.tn0 * (uint32_t)j + plane * (uint32_t)k;
-        if (vec && x + 16 <= a.tn0) {
+        if (x + 16 <= a.tn0) {
             __builtin_amdgcn_raw_buffer_store_b128(v, rd, o, 0, 0);
         } else {
             for (int b = 0; b < 16 && x + b < a.tn0; ++b)
@@ -159,27 +171,33 @@ void k_warp_trilinear_lds(const WArgs a) {
         hi[d] = min((int)floorf(m + a.span[d]) + 2, sn[d] - 1);
     }
     const bool any = lo[0] <= hi[0] && lo[1] <= hi[1] && lo[2] <= hi[2];
-    const uint32_t xa = (uint32_t)lo[0] & ~15u;
+    const uint32_t xa = (uint32_t)lo[0] & ~3u;
 
-    // staging list: thread -> (row slot t / 4 + 64 u, 16-byte chunk t % 4);
-    // source offset and LDS index per pass (LDS index 0 = nothing to copy)
-    uint32_t go[kStagePasses], gl[kStagePasses], tail = 0u;
+    // staging list: 16-byte chunk t + 256 u of the box, chunks along x, then y,
+    // then z; source offset and LDS index (0 = nothing to copy).  Chunks that run
+    // past the source's end are copied by bytes.
+    const uint32_t nq = any ? ((uint32_t)hi[0] - xa) / 16u + 1u : 1u;
+    const uint32_t ny = any ? (uint32_t)(hi[1] - lo[1] + 1) : 1u;
+    const uint32_t nitems = any ? nq * ny * (uint32_t)(hi[2] - lo[2] + 1) : 0u;
+    uint32_t go[kStagePasses], gl[kStagePasses];
+    bool tail = false;
     {
-        const uint32_t nq = any ? ((uint32_t)hi[0] - xa) / 16u + 1u : 0u;
-        const uint32_t ny = any ? (uint32_t)(hi[1] - lo[1] + 1) : 1u;
-        const uint32_t nrows = any ? ny * (uint32_t)(hi[2] - lo[2] + 1) : 0u;
-        const uint32_t c = threadIdx.x % 4u, dz = 64u / ny, dy = 64u - dz * ny;
-        uint32_t r = threadIdx.x / 4u, zz = r / ny, yy = r - zz * ny;
+        const uint32_t dr = 256u / nq, dc = 256u - dr * nq, dz = dr / ny, dy = dr - dz * ny;  // a pass further
+        uint32_t e = threadIdx.x, r = e / nq, c = e - r * nq, zz = r / ny, yy = r - zz * ny;
 #pragma unroll
         for (int u = 0; u < kStagePasses; ++u) {
-            const bool ok = r < nrows && c < nq;
             go[u] = mad_u24((uint32_t)lo[2] + zz, sn01, mad_u24((uint32_t)lo[1] + yy, sn0, xa)) + 16u * c;
-            gl[u] = ok ? kZeroBytes + mad_u24(zz, a.Pz, mad_u24(yy, a.P, 16u * c)) : 0u;
-            // chunks that run past the source's end (handled by a shifted load)
-            tail |= (ok && go[u] + 16u > nbytes) ? (1u << u) : 0u;
-            r += 64u;
-            zz += dy + yy >= ny ? dz + 1u : dz;
-            yy = dy + yy >= ny ? dy + yy - ny : dy + yy;
+            gl[u] = e < nitems ? kZeroBytes + mad_u24(zz, a.Pz, mad_u24(yy, a.P, 16u * c)) : 0u;
+            if (gl[u] != 0u && go[u] + 16u > nbytes) {
+                gl[u] = 0u;
+                tail = true;
+            }
+            e += 256u;
+            c += dc;
+            yy += dy + (c >= nq ? 1u : 0u);
+            c -= c >= nq ? nq : 0u;
+            zz += dz + (yy >= ny ? 1u : 0u);
+            yy -= yy >= ny ? ny : 0u;
         }
     }
 
@@ -224,19 +242,7 @@ void k_warp_trilinear_lds(const WArgs a) {
 #pragma unroll
         for (int u = 0; u < kStagePasses; ++u) {
             v[u] = u32x4{0u, 0u, 0u, 0u};
-            if (gl[u] != 0u) {
-                if (!((tail >> u) & 1u)) {
-                    v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, go[u], 0, 0);
-                } else if (go[u] < nbytes) {
-                    // k dwords past the end: load the last 16 bytes and shift
-                    // them down (bytes past the end are never used: left 0)
-                    const uint32_t k = (go[u] + 16u - nbytes) / 4u;
-                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, nbytes - 16u, 0, 0);
-                    v[u].x = w[k];
-                    v[u].y = k < 3u ? w[k + 1u] : 0u;
-                    v[u].z = k < 2u ? w[k + 2u] : 0u;
-                }
-            }
+            if (gl[u] != 0u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, go[u], 0, 0);  // (any address)
         }
     };
     const int f0 = t.frame * (int)a.fg, f1 = min(f0 + (int)a.fg, (int)a.frames);
@@ -246,19 +252,34 @@ void k_warp_trilinear_lds(const WArgs a) {
 #pragma unroll
         for (int u = 0; u < kStagePasses; ++u)
             if (gl[u] != 0u) *(u32x4 *)(lds + gl[u]) = v[u];
+        if (tail) {
+            const uint8_t *S = a.src + a.src_stride * f;
+            for (uint32_t e = threadIdx.x; e < nitems; e += 256u) {
+                const uint32_t r = e / nq, c = e - r * nq, zz = r / ny, yy = r - zz * ny;
+                const uint32_t from = ((uint32_t)lo[2] + zz) * sn01 + ((uint32_t)lo[1] + yy) * sn0 + xa + 16u * c;
+                const uint32_t to = kZeroBytes + zz * a.Pz + yy * a.P + 16u * c;
+                if (from + 16u > nbytes)
+                    for (uint32_t b = 0; b < 16u && from + b < nbytes; ++b) lds[to + b] = S[from + b];
+            }
+        }
         __syncthreads();
         if (f + 1 < f1) load_box(f + 1);
 #pragma unroll
         for (int q = 0; q < ZC; ++q) {
             // byte taps (2-byte LDS reads at odd addresses are far slower)
             const uint8_t *b0 = lds + li[q], *b1 = b0 + P, *b2 = b0 + Pz, *b3 = b2 + P;
-            const float v0 = (float)b0[0], v1 = (float)b0[1], v2 = (float)b1[0], v3 = (float)b1[1],
-                        v4 = (float)b2[0], v5 = (float)b2[1], v6 = (float)b3[0], v7 = (float)b3[1];
-            const float x00 = fmaf(fx[q], v1 - v0, v0), x10 = fmaf(fx[q], v3 - v2, v2);
-            const float x01 = fmaf(fx[q], v5 - v4, v4), x11 = fmaf(fx[q], v7 - v6, v6);
+            // a byte's bits, read as a half, are the denormal v 2^-24: differences of
+            // two are exact halves and go into the x-lerps (v_fma_mix_f32) without a
+            // conversion; every later value is the lerp of bytes times 2^-24
+            const auto tap = [](const uint8_t *q8) { return __builtin_bit_cast(_Float16, (uint16_t)*q8); };
+            const _Float16 v0 = tap(b0), v2 = tap(b1), v4 = tap(b2), v6 = tap(b3);
+            const _Float16 d0 = tap(b0 + 1) - v0, d2 = tap(b1 + 1) - v2, d4 = tap(b2 + 1) - v4, d6 = tap(b3 + 1) - v6;
+            const float x00 = fmaf(fx[q], (float)d0, (float)v0), x10 = fmaf(fx[q], (float)d2, (float)v2);
+            const float x01 = fmaf(fx[q], (float)d4, (float)v4), x11 = fmaf(fx[q], (float)d6, (float)v6);
             const float y0 = fmaf(fy[q], x10 - x00, x00), y1 = fmaf(fy[q], x11 - x01, x01);
-            // lerps of bytes stay within [0, 255]: no upper clamp needed
-            tile[q * kWY * kWX + tl] = (uint8_t)floor_u32(fmaf(fz[q], y1 - y0, y0) + 0.5f);
+            // lerps of bytes stay within [0, 255]: no upper clamp needed (2^24 z is
+            // exact, so this rounds z + 0.5 once)
+            tile[q * kWY * kWX + tl] = (uint8_t)floor_u32(fmaf(fmaf(fz[q], y1 - y0, y0), 16777216.0f, 0.5f));
         }
         __syncthreads();
         store_tile<ZC>(tile, a, t, f);
@@ -398,10 +419,10 @@ bool stage_geometry(WArgs &a, int zc, uint32_t &bytes) {
         // <= span + 5 voxels (plus rounding well below 0.1)
         ext[d] = (uint32_t)floor(s + 0.5) + 6u;
     }
-    // rows hold the 16-byte chunks from the box's x-start rounded down to 16;
-    // at most kChunks chunks a row and 64 rows per staging pass
-    const uint32_t nq = (ext[0] + 14u) / 16u + 1u;
-    if (nq > kChunks || (uint64_t)ext[1] * ext[2] > 64u * (uint64_t)kStagePasses) return false;
+    // rows hold the 16-byte chunks from the box's x-start rounded down to 4; at
+    // most 256 chunks per staging pass
+    const uint32_t nq = (ext[0] + 2u) / 16u + 1u;
+    if (nq > kChunks || (uint64_t)nq * ext[1] * ext[2] > 256u * (uint64_t)kStagePasses) return false;
     // row and slice pitches odd multiples of 16 bytes, so the rows and slices
     // a wave's taps span fall on different LDS banks; one more row and slice
     // hold the +1 taps of the box's last ones
@@ -412,6 +433,18 @@ bool stage_geometry(WArgs &a, int zc, uint32_t &bytes) {
     const uint64_t b = kZeroBytes + (uint64_t)a.Pz * (uint64_t)(ext[2] + 1u) + 16u;
     bytes = (uint32_t)(b > 0xFFFFFFFFull ? 0xFFFFFFFFull : b);
     return b <= (zc == 16 ? kStageBudget16 : kStageBudget8);
+}
+
+// Fewer frames and slices per workgroup while the launch has under two workgroups
+// a CU (3 trilinear frames of 61 x 70 x 80, 90 workgroups: 15.4 -> 14.7 us a call).
+constexpr uint64_t kFillGroups = 512;
+void spread(WArgs &a) {
+    const auto groups = [&] {
+        return (uint64_t)a.bxy * (uint64_t)((a.tn2 + a.zc - 1) / a.zc) * ((a.frames + a.fg - 1) / a.fg);
+    };
+    a.fg = std::min(a.fg, a.frames);
+    while (a.fg > 1 && groups() < kFillGroups) a.fg /= 2;
+    while (a.zc > 4 && groups() < kFillGroups) a.zc /= 2;
 }
 
 }  // namespace
@@ -436,24 +469,23 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
     a.bxy = a.xblocks * ((tn[1] + kWY - 1) / kWY);
     const dim3 block(256);
 
-    // frame-looping kernels: groups of kFrameGroup frames per workgroup (enough
-    // workgroups to fill the GPU evenly; the per-tile work shared by four)
-    const uint32_t groups = (frames + kFrameGroup - 1) / kFrameGroup;
     if (!trilinear) {
         a.zc = 16;
         a.fg = kFrameGroup;
+        spread(a);
         a.zchunks = (tn[2] + a.zc - 1) / a.zc;
-        const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * groups;
+        const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
         if (total > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
         a.total = (uint32_t)total;
-        hipLaunchKernelGGL(k_warp_nearest<16>, dim3(a.total), block, 0, s, a);
+        if (a.zc == 16) hipLaunchKernelGGL(k_warp_nearest<16>, dim3(a.total), block, 0, s, a);
+        else if (a.zc == 8) hipLaunchKernelGGL(k_warp_nearest<8>, dim3(a.total), block, 0, s, a);
+        else hipLaunchKernelGGL(k_warp_nearest<4>, dim3(a.total), block, 0, s, a);
         return hipGetLastError();
     }
 
-    // staged trilinear: source rows 4-byte aligned (16-byte chunks at dword
-    // offsets) and at least 16 bytes of source, every partial sum of the
+    // staged trilinear: at least 16 bytes of source, every partial sum of the
     // recipe below 2^20, box within budget
-    bool staged = sn[0] % 4 == 0 && (int64_t)sn[0] * sn[1] * sn[2] >= 16;
+    bool staged = (int64_t)sn[0] * sn[1] * sn[2] >= 16;
     for (int d = 0; d < 3 && staged; ++d) {
         double b = fabs((double)w[4 * d + 3]);
         for (int e = 0; e < 3; ++e) b += fabs((double)w[4 * d + e]) * (double)(tn[e] + 64);
@@ -461,9 +493,9 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
     }
     uint32_t bytes = 0;
     if (staged) {
-        // four registers a slice (index, fractions): tiles of 16 or 8 slices
+        // four registers a slice (index, fractions): tiles of 16, 8 or 4 slices
         staged = false;
-        for (int z : {16, 8})
+        for (int z : {16, 8, 4})
             if (stage_geometry(a, z, bytes)) {
                 a.zc = z;
                 staged = true;
@@ -471,16 +503,21 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
             }
     }
     if (!staged) a.zc = 16;
-    a.zchunks = (tn[2] + a.zc - 1) / a.zc;
     // staged: one workgroup per tile and group of frames; direct: one per tile
     // and frame
     a.fg = staged ? kFrameGroup : 1u;
-    const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * (staged ? groups : frames);
+    if (staged) {
+        spread(a);
+        if (!stage_geometry(a, a.zc, bytes)) return hipErrorInvalidConfiguration;
+    }
+    a.zchunks = (tn[2] + a.zc - 1) / a.zc;
+    const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
     if (total > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
     a.total = (uint32_t)total;
     if (!staged) hipLaunchKernelGGL(k_warp_trilinear, dim3(a.total), block, 0, s, a);
     else if (a.zc == 16) hipLaunchKernelGGL(k_warp_trilinear_lds<16>, dim3(a.total), block, bytes, s, a);
-    else hipLaunchKernelGGL(k_warp_trilinear_lds<8>, dim3(a.total), block, bytes, s, a);
+    else if (a.zc == 8) hipLaunchKernelGGL(k_warp_trilinear_lds<8>, dim3(a.total), block, bytes, s, a);
+    else hipLaunchKernelGGL(k_warp_trilinear_lds<4>, dim3(a.total), block, bytes, s, a);
     return hipGetLastError();
 }
 
