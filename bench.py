@@ -14,8 +14,8 @@ second, V the nominal target grid).  The JSON line also carries
 
 * roofline: the dominant kernel (mask warp-and-score), timed live with HIP
   events on the library's stream, against the published FP32 vector peak,
-  on the particle x voxel pairs it evaluates (tile culling skips the pairs
-  it proves add nothing; the library counts both);
+  on the particle x voxel pairs it samples (blocks of the target that the
+  source's distance field settles are counted whole; the library counts both);
   its gather probe (the same grid, coordinates and source loads and nothing
   else) timed on the particle sets of a real registration;
 * cpu_baseline: the CPU oracle on a bounded sample of the same workload;
@@ -55,10 +55,11 @@ GATHER_BYTES_MASK, GATHER_BYTES_IMAGE = 1.0, 8.0
 # image launch configuration timed for speckle160 (layout, particles per
 # workgroup, tile depth): the autotuner's choice on that workload
 DEFAULT_IMAGE_TUNING = "5,4,256"
-KERNEL_SOURCES = ["paper_2504_19930_amd/csrc/score.hip", "paper_2504_19930_amd/csrc/internal.h",
+KERNEL_SOURCES = ["paper_2504_19930_amd/csrc/score.hip", "paper_2504_19930_amd/csrc/dice.hip",
+                  "paper_2504_19930_amd/csrc/tri.hip", "paper_2504_19930_amd/csrc/internal.h",
                   "paper_2504_19930_amd/csrc/common.h"]
-PMC_MASK = os.path.join(ROOT, "profiles", "k_score_mask_lv224_pmc.md")
-PMC_IMAGE = os.path.join(ROOT, "profiles", "k_score_image_speckle160_pmc.md")
+PMC_MASK = os.path.join(ROOT, "profiles", "k_score_dice_lv224_pmc.md")
+PMC_IMAGE = os.path.join(ROOT, "profiles", "k_score_tri_speckle160_pmc.md")
 GOLDEN = os.path.join(ROOT, "tests", "golden", "full_runs.json")
 LV_FRAMES = 20
 
@@ -136,23 +137,22 @@ def roofline(kernel, ops_per_eval, evals_per_launch, launch_ms, launches, gather
 
 
 def mask_roofline(launch_ms, launches, work, N, V, probe):
-    """The mask kernel's roofline on the work its launches did: tile culling
-    proves that a particle adds nothing to a tile whose image reaches no
-    occupied source cell and skips it, so `achieved` counts the evaluated
-    particle x voxel pairs only (the headline value counts every pair of the
-    target grid, as the sums do)."""
+    """The mask kernel's roofline on the work its launches did: the source's
+    distance field settles most blocks of the target whole, so `achieved`
+    counts the particle x voxel pairs that were sampled only (the headline value
+    counts every pair of the target grid, as the sums do)."""
     # the counters also cover the final estimate's own one-particle scoring:
     # per launch, the evaluated fraction of the launch's N + 1 particles
     grid = float(N + 1) * V
     frac_eval = work["evaluated"] / work["covered"] if work["covered"] else 1.0
     evaluated, covered = frac_eval * grid, grid
-    r = roofline("k_score_mask (warp-and-score, nearest, Dice counts)", OPS_PER_EVAL_MASK, evaluated, launch_ms,
+    r = roofline("k_score_dice (warp-and-score, nearest, Dice counts)", OPS_PER_EVAL_MASK, evaluated, launch_ms,
                  launches, GATHER_BYTES_MASK, PMC_MASK, probe)
     frac_int = work.get("interior", 0) / work["evaluated"] if work["evaluated"] else 0.0
     r.update({"evals_per_launch_covered": covered, "evaluated_fraction": frac_eval,
               "interior_fraction_of_evaluated": frac_int,
-              "evals_note": "evals_per_launch = particle x voxel pairs evaluated per launch (the culled ones "
-                            "excluded): the fraction the cull pre-pass counted over the timed registrations times "
+              "evals_note": "evals_per_launch = particle x voxel pairs sampled per launch (those of decided "
+                            "blocks excluded): the fraction the kernel counted over the timed registrations times "
                             "the launch's (N + 1) x V pairs"})
     return r
 
@@ -246,9 +246,21 @@ def gather_probe_run(reg, K, seed):
         reg.step(1)
     return {"gather_probe_ms_per_launch": tp / K, "gather_probe_score_ms_per_launch": ts / K,
             "gather_frac": tp / ts,
-            "gather_probe_note": "probe = the warp-and-score grid, culling, coordinates, offsets and source loads "
+            "gather_probe_note": "probe = the warp-and-score grid, block tests, coordinates, offsets and source loads "
                                  "only (smc_gather_probe), timed with the production kernel on each particle set of "
                                  f"one {K}-iteration registration; gather_frac = probe time / production time"}
+
+
+def valid_fraction(reg, K, V, seed):
+    """Mean fraction of the target grid that has a valid sample (inside both
+    FOVs and the source: the n of the moments), over the particle sets of one
+    registration."""
+    reg.reset(seed)
+    total = 0.0
+    for _ in range(K):
+        total += float(reg.evaluate(reg.particles()["states"])[:, 0].mean()) / V
+        reg.step(1)
+    return total / K
 
 
 def exhaustive_run(reg, prm, V, smc_ms, smc_score, g=7):
@@ -363,15 +375,23 @@ def speckle160(inp, args):
     reg.profile(False)
     launch_ms = prof["score_ms"] / max(1, prof["score_launches"])
     probe = None if args.no_gather_probe else gather_probe_run(reg, K, 78)
+    # the sums need the valid samples only; blocks without one are skipped
+    valid = valid_fraction(reg, K, V, 78)
+    covered = float(N + 1) * V
     tuning = reg.tuning()
     reg.close()
     evals = float(N) * V * K * steps
+    roof = roofline("k_score_tri (warp-and-score, trilinear, source FOV)", OPS_PER_EVAL_IMAGE, valid * covered,
+                    launch_ms, prof["score_launches"], GATHER_BYTES_IMAGE, PMC_IMAGE, probe)
+    roof.update({"evals_per_launch_covered": covered, "evaluated_fraction": valid,
+                 "evals_note": "evals_per_launch = valid samples per launch (the n of the moments over one "
+                               "registration's particle sets); blocks without one are skipped, samples that turn "
+                               "out invalid are not credited"})
     return {"value": evals / wall, "unit": "evals/s", "steps": steps, "warmup": 1, "ms_per_step": wall * 1e3 / steps,
             "workload": f"speckle160: 160^3 u8 speckle images, 60 deg apical-cone source FOV, N={N}, K={K}, NCC, "
                         "trilinear; one step = one registration + warp_apply",
             "tuning": tuning, "final_score": est["score"],
-            "roofline": roofline("k_score_image (warp-and-score, trilinear)", OPS_PER_EVAL_IMAGE, float(N + 1) * V,
-                                 launch_ms, prof["score_launches"], GATHER_BYTES_IMAGE, PMC_IMAGE, probe)}
+            "roofline": roof}
 
 
 def batch64(inp, args):
