@@ -1912,7 +1912,7 @@ smc_status smc_cnn_create(smc_cnn **out, uint32_t max_batch, void *hip_stream) {
     for (int L = 0; L < 4; ++L)
         if ((st = n->alloc(&c.wf[L], z.wf[L])) != SMC_OK || (st = n->alloc(&c.wd[L], z.wd[L])) != SMC_OK ||
             (st = n->alloc(&c.act[L], z.act[L])) != SMC_OK || (st = n->alloc(&c.xs[L], z.xs[L])) != SMC_OK ||
-            (st = n->alloc(&c.dyf[L], z.dyf[L])) != SMC_OK || (st = n->alloc(&c.dyl[L], z.dyl[L])) != SMC_OK)
+            (st = n->alloc(&c.dy[L], z.dy[L])) != SMC_OK || (st = n->alloc(&c.reach[L], z.reach[L])) != SMC_OK)
             return bail(st);
     std::vector<float> zeros((size_t)c.n_params, 0.0f);
     if (hipMemcpy(c.params, zeros.data(), 4 * c.n_params, hipMemcpyHostToDevice) != hipSuccess ||

@@ -314,18 +314,19 @@ struct CnnBuffers {
     // bfloat16 copies of the convolution weights and tensors per layer, in the
     // orders that cnn.hip describes
     uint16_t *wf[4], *wd[4];    // weights of the forward and of the data gradient
-    uint16_t *act[4];           // outputs after ReLU: channels last; the last layer's channels first
+    uint16_t *act[4];           // outputs after ReLU, channels first
     uint16_t *xs[4];            // inputs, split (training)
-    uint16_t *dyf[4], *dyl[4];  // gradients of the pre-activations, channels first and last
+    uint16_t *dy[4];            // gradients of the pre-activations, channels first
+    uint64_t *reach[4];         // offsets that the data gradient gathers by
     float *dout;                // B x 12
     float *wpart, *bpart;       // partial weight and bias gradients
 };
 // Elements of the buffers of a network of up to max_batch pairs.
 struct CnnSizes {
-    size_t wf[4], wd[4], act[4], xs[4], dyf[4], dyl[4], wpart, bpart;
+    size_t wf[4], wd[4], act[4], xs[4], dy[4], reach[4], wpart, bpart;
 };
 CnnSizes cnn_sizes(int max_batch);
-// Clear what stays zero and pack the weights of params.
+// Clear what stays zero, make the tables and pack the weights of params.
 hipError_t cnn_prepare(const CnnBuffers &c, int max_batch, hipStream_t s);
 int64_t cnn_param_offset(int part);
 hipError_t cnn_downsample(const uint8_t *src, const int32_t sn[3], const uint8_t *tgt, const int32_t tn[3], float scale,
