@@ -437,14 +437,18 @@ bool stage_geometry(WArgs &a, int zc, uint32_t &bytes) {
 
 // Fewer frames and slices per workgroup while the launch has under two workgroups
 // a CU (3 trilinear frames of 61 x 70 x 80, 90 workgroups: 15.4 -> 14.7 us a call).
+// fits: whether the kernel takes tiles of a depth (a box hardly shrinks with the
+// depth where the target's x axis falls on the source's z axis, and shallow
+// tiles have the smaller LDS budget).
 constexpr uint64_t kFillGroups = 512;
-void spread(WArgs &a) {
+template <typename F>
+void spread(WArgs &a, F fits) {
     const auto groups = [&] {
         return (uint64_t)a.bxy * (uint64_t)((a.tn2 + a.zc - 1) / a.zc) * ((a.frames + a.fg - 1) / a.fg);
     };
     a.fg = std::min(a.fg, a.frames);
     while (a.fg > 1 && groups() < kFillGroups) a.fg /= 2;
-    while (a.zc > 4 && groups() < kFillGroups) a.zc /= 2;
+    while (a.zc > 4 && groups() < kFillGroups && fits(a.zc / 2)) a.zc /= 2;
 }
 
 }  // namespace
@@ -472,7 +476,7 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
     if (!trilinear) {
         a.zc = 16;
         a.fg = kFrameGroup;
-        spread(a);
+        spread(a, [](int) { return true; });
         a.zchunks = (tn[2] + a.zc - 1) / a.zc;
         const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
         if (total > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
@@ -507,8 +511,12 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
     // and frame
     a.fg = staged ? kFrameGroup : 1u;
     if (staged) {
-        spread(a);
-        if (!stage_geometry(a, a.zc, bytes)) return hipErrorInvalidConfiguration;
+        spread(a, [&](int zc) {
+            WArgs b = a;
+            uint32_t unused;
+            return stage_geometry(b, zc, unused);
+        });
+        (void)stage_geometry(a, a.zc, bytes);  // (a depth that fits)
     }
     a.zchunks = (tn[2] + a.zc - 1) / a.zc;
     const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
