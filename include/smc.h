@@ -233,7 +233,8 @@ smc_status smc_set_tuning(smc_ctx *ctx, int32_t layout, int32_t particles_per_gr
 smc_status smc_get_tuning(smc_ctx *ctx, int32_t *layout, int32_t *particles_per_group, int32_t *tile_depth);
 
 /* Autotuner: time every candidate tuning (layouts for trilinear images;
- * particles per group 4 / 8; tile depths) on this context's own volumes with
+ * particles per group 4 / 8 and tile depths 32 / 256 of the launches that use
+ * them: see smc_set_tuning; others leave both as they are) on this context's own volumes with
  * HIP events (the fastest of reps launches each, on a scratch sum buffer) over two particle
  * sets -- the current particles (after smc_init, the prior) and a cloud
  * concentrated within 5 % of the limits around x0, standing in for the

@@ -1211,7 +1211,7 @@ struct TuneKey {
     }
 };
 struct TuneVal {
-    int layout, pt, zchunk;
+    int layout, pt, zchunk;  // pt, zchunk: -1 where the launches of the layout use neither
     double ms;
 };
 std::map<TuneKey, TuneVal> &tune_cache() {
@@ -1271,42 +1271,53 @@ smc_status smc_autotune(smc_ctx *c, uint32_t reps, double *best_ms) {
             return c->mark(fail(SMC_EDEVICE, "autotune particle set failed"));
     }
     const double w_conc = c->f.n_iters > 1 ? (double)(c->f.n_iters - 1) : 0.0;
-    std::vector<int> layouts = {kLayoutRaw};
-    if (c->mode == kModeImageTrilinear)
-        layouts = {kLayoutRaw, kLayoutPairX, kLayoutQuadXY, kLayoutOct, kLayoutOctTile, kLayoutLerp};
-    const int depths_img[] = {32, 256}, depths_mask[] = {16, 32, 256};
-    const int *depths = c->mode == kModeMask ? depths_mask : depths_img;
-    const int nd = c->mode == kModeMask ? 3 : 2;
+    // block launches (masks; the one-gather layouts of a source with a FOV) have no
+    // particles per group and no tiles: one candidate, which keeps what is set
+    const TuneVal own{c->layout, c->pt, c->zchunk, 0.0};
+    std::vector<TuneVal> candidates;
+    for (int lay = kLayoutRaw; lay < (c->mode == kModeImageTrilinear ? kLayouts : 1); ++lay) {
+        if (!layout_fits(lay, c->sn)) continue;
+        ScoreLaunch L = c->score_launch(c->f.words, c->s_eval, 0, np, true);
+        L.layout = lay;
+        if (L.ac || tri_supported(L)) {
+            candidates.push_back({lay, -1, -1, 0.0});
+            continue;
+        }
+        for (int pt : {4, 8})
+            for (int depth : {32, 256}) candidates.push_back({lay, pt, depth, 0.0});
+    }
+    const auto apply = [&](const TuneVal &t) {
+        return smc_set_tuning(c, t.layout, t.pt < 0 ? own.pt : t.pt, t.zchunk < 0 ? own.zchunk : t.zchunk);
+    };
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    TuneVal best{c->layout, c->pt, c->zchunk, 1e30};
+    TuneVal best{c->layout, -1, -1, 1e30};
     smc_status result = SMC_OK;
-    for (int lay : layouts)
-        for (int pt : {4, 8})
-            for (int q = 0; q < nd && result == SMC_OK && layout_fits(lay, c->sn); ++q) {
-                if ((result = smc_set_tuning(c, lay, pt, depths[q])) != SMC_OK) break;
-                double cost = 0.0;
-                for (int set = 0; set < 2 && result == SMC_OK; ++set) {
-                    // (the prior set is scored as smc_step's first iteration would score it)
-                    ScoreLaunch L = c->score_launch(set == 0 ? c->f.words : c->w_eval, c->s_eval, 0, np, true,
-                                                    set == 0 && c->prior_dispersed && c->k_done == 0);
-                    if (c->p.score == SMC_SCORE_MI) L.hist = c->hist_eval;
-                    double best_t = 1e30;  // the fastest of reps launches: robust to interference
-                    for (uint32_t r = 0; r <= reps && result == SMC_OK; ++r) {
-                        float ms = 0.0f;
-                        if (launch_fill_u64(c->s_eval, 6ull * np, c->stream) != hipSuccess ||
-                            hipEventRecord(e0, c->stream) != hipSuccess || launch_score(L, c->stream) != hipSuccess ||
-                            hipEventRecord(e1, c->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                            hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
-                            result = fail(SMC_EDEVICE, "autotune launch failed");
-                        if (r > 0) best_t = std::min(best_t, (double)ms);  // the first launch warms caches
-                    }
-                    cost += (set == 0 ? 1.0 : w_conc) * best_t;
-                }
-                const double avg = cost / (1.0 + w_conc);  // per launch over a registration
-                if (avg < best.ms) best = TuneVal{lay, pt, depths[q], avg};
+    for (const TuneVal &t : candidates) {
+        if ((result = apply(t)) != SMC_OK) break;
+        double cost = 0.0;
+        for (int set = 0; set < 2 && result == SMC_OK; ++set) {
+            // (the prior set is scored as smc_step's first iteration would score it)
+            ScoreLaunch L = c->score_launch(set == 0 ? c->f.words : c->w_eval, c->s_eval, 0, np, true,
+                                            set == 0 && c->prior_dispersed && c->k_done == 0);
+            if (c->p.score == SMC_SCORE_MI) L.hist = c->hist_eval;
+            double best_t = 1e30;  // the fastest of reps launches: robust to interference
+            for (uint32_t r = 0; r <= reps && result == SMC_OK; ++r) {
+                float ms = 0.0f;
+                if (launch_fill_u64(c->s_eval, 6ull * np, c->stream) != hipSuccess ||
+                    hipEventRecord(e0, c->stream) != hipSuccess || launch_score(L, c->stream) != hipSuccess ||
+                    hipEventRecord(e1, c->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                    hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+                    result = fail(SMC_EDEVICE, "autotune launch failed");
+                if (r > 0) best_t = std::min(best_t, (double)ms);  // the first launch warms caches
             }
+            cost += (set == 0 ? 1.0 : w_conc) * best_t;
+        }
+        if (result != SMC_OK) break;
+        const double avg = cost / (1.0 + w_conc);  // per launch over a registration
+        if (avg < best.ms) best = TuneVal{t.layout, t.pt, t.zchunk, avg};
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     // the timed launches left counts in the evaluation histograms
@@ -1315,7 +1326,7 @@ smc_status smc_autotune(smc_ctx *c, uint32_t reps, double *best_ms) {
                         c->stream) != hipSuccess)
         result = fail(SMC_EDEVICE, "histogram clear failed");
     if (result != SMC_OK) return c->mark(result);
-    if ((st = smc_set_tuning(c, best.layout, best.pt, best.zchunk)) != SMC_OK) return st;
+    if ((st = apply(best)) != SMC_OK) return st;
     {
         std::lock_guard<std::mutex> g(tune_mutex());
         tune_cache()[key] = best;
