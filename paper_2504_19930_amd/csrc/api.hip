@@ -150,7 +150,7 @@ float *scratch_of(int device) {
 
 }  // namespace
 
-constexpr int kPrepHits = 8, kPrepWords = kPrepHits + kLayouts;
+constexpr int kPrepHits = 8, kPrepOff = kPrepHits + kLayouts, kPrepWords = kPrepOff + 1;
 
 struct smc_ctx {
     int device = 0;
@@ -167,7 +167,10 @@ struct smc_ctx {
     void *packed[kLayouts] = {};
     uint64_t sentinel[kLayouts] = {};  // per packed layout: value marking elements outside the source FOV
     bool has_sentinel[kLayouts] = {};
-    unsigned long long *prep = nullptr;  // volume sums (kPrepHits), hits of the packed layouts' sentinels
+    // volume sums (kPrepHits), hits of the packed layouts' sentinels, voxels far
+    // from any valid sample
+    unsigned long long *prep = nullptr;
+    bool by_blocks = false;  // trilinear images with a source FOV: block launches where the layout has them
     FilterState f{};
     uint32_t k_done = 0;
     // the current particles are a draw from the uniform prior box (spread over
@@ -264,7 +267,7 @@ struct smc_ctx {
             L.tgt_fov = nullptr;
         } else {
             L.src = src;
-            L.tri = tri;
+            if (by_blocks) L.tri = tri;
             L.src_ok = src_ok;
             L.tgt = tgt;
             L.tgt_fov = tgt_fov;
@@ -673,6 +676,10 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     if (launch_fill_u64(c->prep, kPrepWords, c->stream) != hipSuccess ||
         launch_volume_sums(vols, fovs, sizes, c->prep, c->stream) != hipSuccess)
         return bail(fail(SMC_EDEVICE, "volume statistics launch failed"));
+    const double tgt_spacing[3] = {tgt->sx, tgt->sy, tgt->sz}, src_spacing[3] = {src->sx, src->sy, src->sz};
+    if (corners && p->score != SMC_SCORE_MI &&
+        launch_tri_off(field, c->sn, tgt_spacing, src_spacing, c->prep + kPrepOff, c->stream) != hipSuccess)
+        return bail(fail(SMC_EDEVICE, "image preparation launch failed"));
 
     if ((st = prepare_layout(c, c->layout, layout_buf)) != SMC_OK) return bail(st);
 
@@ -683,6 +690,7 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     if ((st = settle_layouts(c, hs + kPrepHits)) != SMC_OK) return bail(st);
     const Stats tstat = stats_from_sums(hs), sstat = stats_from_sums(hs + 4);
     if (tstat.count == 0) return bail(fail(SMC_EINVAL, "the target FOV is empty"));
+    c->by_blocks = corners && (p->score == SMC_SCORE_MI || tri_pays(hs[kPrepOff], c->sn));
     c->tgt_on = tstat.on;
     c->tgt_count = tstat.count;
 
@@ -1447,6 +1455,8 @@ smc_status warp_apply(const smc_volume *src, const double mat3x4[12], int32_t in
 
 // ===================================================================== batches
 
+constexpr int kBatchClasses = 6;
+
 struct smc_batch {
     hipStream_t stream = nullptr;
     std::vector<smc_ctx *> pairs;
@@ -1464,7 +1474,8 @@ struct smc_batch {
         std::vector<uint32_t> members;
         void *args = nullptr;
         uint32_t *offs = nullptr, *kmax = nullptr, *lists = nullptr;
-    } cls[4];  // 0 masks; 1, 2, 3 trilinear images by source FOV validity mode 0, 1, 2
+    } cls[kBatchClasses];  // 0 masks; trilinear images by source FOV validity mode: 1, 2, 3 (0, 1, 2) in tiles,
+                           // 4, 5 (1, 2) by blocks
     std::vector<uint32_t> images;   // all trilinear image pairs
     std::vector<uint32_t> singles;  // pairs outside the classes (nearest-neighbour images) run per pair
     std::vector<void *> allocs;
@@ -1656,8 +1667,8 @@ smc_status plan_blocks(smc_batch *b, smc_batch::Class &C, bool masks, int vmode)
     return SMC_OK;
 }
 
-// Split the image pairs by source FOV validity mode (one kernel variant per
-// class keeps each variant's register budget) and plan every class.
+// Split the image pairs by kernel and source FOV validity mode (one kernel variant
+// per class keeps each variant's register budget) and plan every class.
 smc_status plan_all(smc_batch *b) {
     // one kernel variant serves a class: every image pair takes the first
     // image pair's layout and particles per group, every mask pair the first
@@ -1674,23 +1685,18 @@ smc_status plan_all(smc_batch *b) {
                     return fail(SMC_EINVAL, "pair %u cannot take the tuning of pair %u", i, members[0]);
         }
     }
-    for (int q = 1; q < 4; ++q) b->cls[q].members.clear();
+    for (int q = 1; q < kBatchClasses; ++q) b->cls[q].members.clear();
     for (uint32_t i : b->images) {
         smc_ctx *c = b->pairs[i];
-        const int vm = score_vmode(c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true));
-        b->cls[1 + vm].members.push_back(i);
+        const ScoreLaunch L = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true);
+        // (block launches have a FOV, so a validity mode of 1 or 2)
+        b->cls[(tri_supported(L) ? 3 : 1) + score_vmode(L)].members.push_back(i);
     }
     smc_status st;
     if ((st = plan_blocks(b, b->cls[0], true, 0)) != SMC_OK) return st;
-    for (int q = 1; q < 4; ++q) {
-        // (all pairs of a class share a layout)
-        const auto &m = b->cls[q].members;
-        bool tri = !m.empty();
-        if (tri) {
-            const smc_ctx *c = b->pairs[m[0]];
-            tri = tri_supported(c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true));
-        }
-        if ((st = tri ? plan_blocks(b, b->cls[q], false, q - 1) : plan_class(b, b->cls[q], q - 1)) != SMC_OK) return st;
+    for (int q = 1; q < kBatchClasses; ++q) {
+        st = q < 4 ? plan_class(b, b->cls[q], q - 1) : plan_blocks(b, b->cls[q], false, q - 3);
+        if (st != SMC_OK) return st;
     }
     return SMC_OK;
 }
@@ -1699,12 +1705,12 @@ smc_status plan_all(smc_batch *b) {
 smc_status record_run(smc_batch *b) {
     HIP_TRY(launch_init_batch(b->states_dev, (uint32_t)b->pairs.size(), b->max_threads, b->stream));
     // the item queues start empty on every run (a fill kernel, so graph replays clear them too)
-    for (int q = 1; q < 4; ++q)
+    for (int q = 1; q < kBatchClasses; ++q)
         if (b->cls[q].plan.n_pairs && !b->cls[q].plan.blocks)
             HIP_TRY(launch_fill_u64((unsigned long long *)b->cls[q].plan.counters, 4ull * std::max(1u, b->kmax_all),
                                     b->stream));
     for (uint32_t k = 1; k <= b->kmax_all; ++k) {
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < kBatchClasses; ++q) {
             const smc_batch::Class &C = b->cls[q];
             HIP_TRY(launch_batch_score(k == 1 && C.has_first ? C.plan_first : C.plan, k, b->stream));
         }

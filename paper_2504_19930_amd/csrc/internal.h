@@ -109,7 +109,7 @@ struct ScoreLaunch {
         const uint32_t *t8 = nullptr, *t16 = nullptr;
     } dice;
     // trilinear images with a source FOV in the one-gather layouts (tri.hip;
-    // nullptr without a FOV): field of the valid
+    // nullptr without a FOV or where tiles are faster): field of the valid
     // cells, target (and FOV) bytes of four slices as dwords, target blocks
     struct Tri {
         const uint8_t *field = nullptr;
@@ -234,6 +234,12 @@ TriSizes tri_sizes(const int32_t sn[3], const int32_t tn[3]);
 hipError_t launch_tri_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint32_t *tz, uint32_t *fz,
                              void *t4, void *t8, void *t16, hipStream_t s);
 bool tri_supported(const ScoreLaunch &L);
+// out += voxels of a field without a valid sample within the reach of a target
+// block of 8^3, and whether so many pay for the block launch of moments
+// (spacings ts, ss in mm).
+hipError_t launch_tri_off(const uint8_t *field, const int32_t sn[3], const double ts[3], const double ss[3],
+                          unsigned long long *out, hipStream_t s);
+bool tri_pays(uint64_t off, const int32_t sn[3]);
 hipError_t launch_tri(const ScoreLaunch &L, hipStream_t s);
 hipError_t launch_tri_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s);
 size_t tri_args_bytes();

@@ -1013,14 +1013,15 @@ KArgs make_args(const ScoreLaunch &L, int pt, int *nz_chunks) {
 
 typedef void (*ScoreKernel)(const KArgs);
 
-// (the layouts of one gather come here without a source FOV only: tri_supported)
+// (histograms in the layouts of one gather come here without a source FOV only:
+// tri_supported)
 constexpr bool one_gather(int layout) {
     return layout == kLayoutOct || layout == kLayoutOctTile || layout == kLayoutLerp;
 }
 
 template <int PT, int LAYOUT, int ACC>
 ScoreKernel pick_tri(int vmode) {
-    if constexpr (one_gather(LAYOUT)) return k_score_image<PT, LAYOUT, true, 0, ACC>;
+    if constexpr (one_gather(LAYOUT) && ACC == 1) return k_score_image<PT, LAYOUT, true, 0, ACC>;
     if constexpr (LAYOUT != kLayoutRaw) {
         if (vmode == 2) return k_score_image<PT, LAYOUT, true, 2, ACC>;
     }
@@ -1080,7 +1081,6 @@ template <int PT, int LAYOUT>
 ScoreKernel pick_batch_image(int vmode) {
     typedef void (*BK)(const BatchArgs);
     BK k;
-    if constexpr (one_gather(LAYOUT)) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, LAYOUT, 0>);
     if constexpr (LAYOUT != kLayoutRaw) {
         if (vmode == 2) return reinterpret_cast<ScoreKernel>(k_batch_score<PT, LAYOUT, 2>);
     }

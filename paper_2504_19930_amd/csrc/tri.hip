@@ -34,6 +34,7 @@
 // behind (1.05 instructions a CU and clock, 26.4 for a plain sample).  More waves
 // (one slice at a time, 95 registers, five waves a SIMD) ran 2 to 9 % slower:
 // their gathers evict each other's lines.
+#include <math.h>
 #include <string.h>
 
 #include <algorithm>
@@ -744,6 +745,24 @@ __global__ __launch_bounds__(256) void k_blocks(const uint2 *t4, uint32_t g4x, u
     }
 }
 
+// Field bytes of state off at a distance of at least `need` (its bytes are 16-byte
+// aligned).
+__global__ __launch_bounds__(256) void k_count_off(const uint8_t *field, uint32_t n, uint32_t need,
+                                                   unsigned long long *out) {
+    const uint32_t stride = gridDim.x * 256u, t = blockIdx.x * 256u + threadIdx.x;
+    uint32_t c = 0u;
+    const auto off = [&](uint32_t b) { return b - need < 128u - need ? 1u : 0u; };
+    for (uint32_t q = t; q < n / 16; q += stride) {
+        const uint4 v = ((const uint4 *)field)[q];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) c += off((w[e / 4] >> (8 * (e % 4))) & 255u);
+    }
+    for (uint32_t q = n / 16 * 16 + t; q < n; q += stride) c += off(field[q]);
+    c = wave_sum(c);
+    if (threadIdx.x % 64u == 0u && c) atomicAdd(out, (unsigned long long)c);
+}
+
 unsigned blocks_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192)); }
 uint32_t cells(int32_t n, int32_t side) { return (uint32_t)((n + side - 1) / side); }
 
@@ -839,12 +858,39 @@ hipError_t launch_tri_target(const uint8_t *vol, const uint8_t *fov, const int32
     return hipGetLastError();
 }
 
-// With a source FOV only: there two fifths of the pairs are skipped (4.37
-// against 5.98 ms on 160^3 images in a 60-degree cone).  Without one there is
-// little to skip, both kernels run at the rate of the texture path, and the
-// tiles of score.hip, whose 32-voxel rows share more cache lines, are a little
-// ahead: 2.63 against 2.69 ms (128 x 130 x 126, N = 1500), 2.02 against 2.16 (60
-// x 150 x 90, N = 3000), histograms 3.69 against 3.96.
+// With a source FOV only, and for moments only if it leaves enough to skip: with
+// an apical cone two fifths of the pairs are skipped (4.37 against 5.98 ms on
+// 160^3 images).  With little to skip both kernels run at the rate of the texture
+// path, and the tiles of score.hip, whose 32-voxel rows share more cache lines,
+// are ahead: without a FOV 2.63 against 2.69 ms (128 x 130 x 126, N = 1500), 2.02
+// against 2.16 (60 x 150 x 90, N = 3000), histograms 3.69 against 3.96; with a FOV
+// of the whole 128 x 120 x 110 (N = 600) 0.83 against 0.94 ms, 1.0 against 1.3 in
+// the first iterations, whose particles lie far apart, and with holes a
+// few voxels apart 1.0 against 1.6.  (Histograms with a FOV are faster by blocks
+// throughout: full FOV 6.6 against 8.2 ms a registration.)
+//
+// The line: the share of source voxels from which a target block of 8^3 reaches
+// no valid sample, against what both kernels took (128 x 120 x 110, N = 600;
+// early, late iterations): 0.07 of them 1.25, 0.90 of the tiles' time; 0.16 1.1,
+// 0.82; 0.25 0.95, 0.79; a cone 0.35 0.86; target voxels of twice the spacing in
+// that cone 0.26 0.99, of four times 0.115 1.14.
+constexpr double kOffShare = 0.12;
+bool tri_pays(uint64_t off, const int32_t sn[3]) {
+    return (double)off >= kOffShare * (double)sn[0] * (double)sn[1] * (double)sn[2];
+}
+
+hipError_t launch_tri_off(const uint8_t *field, const int32_t sn[3], const double ts[3], const double ss[3],
+                          unsigned long long *out, hipStream_t s) {
+    // ball radius of the unit block: exact for cubic source voxels
+    const double radius = sqrt(ts[0] * ts[0] + ts[1] * ts[1] + ts[2] * ts[2]) / cbrt(ss[0] * ss[1] * ss[2]);
+    const double need = ceil((double)kFieldUnit * (3.5 * radius + (double)kFieldMargin));
+    if (!(need <= (double)kFieldDist)) return hipSuccess;  // no such block is ever decided
+    const uint32_t n = (uint32_t)sn[0] * (uint32_t)sn[1] * (uint32_t)sn[2];
+    hipLaunchKernelGGL(k_count_off, dim3(std::min(blocks_for(n / 16 + 1), 256u)), dim3(256), 0, s, field, n,
+                       (uint32_t)need, out);
+    return hipGetLastError();
+}
+
 bool tri_supported(const ScoreLaunch &L) {
     return L.mode == kModeImageTrilinear && L.tri.field != nullptr && L.src_ok != nullptr &&
            (L.layout == kLayoutOct || L.layout == kLayoutOctTile || L.layout == kLayoutLerp);

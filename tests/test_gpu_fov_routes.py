@@ -1,0 +1,101 @@
+"""Images with a source FOV run by blocks where the FOV leaves enough to skip, in
+tiles where it does not (a FOV of the whole image, small cuts, scattered holes):
+every layout gives the raw layout's particles on both sides of that line, a batch
+that mixes them gives the single runs', and a FOV of the whole image costs no more
+than none."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = (45, 38, 41)
+
+
+def _images(shape, seed):
+    z, y, x = np.meshgrid(*[np.arange(n) - 0.5 * (n - 1) for n in shape[::-1]], indexing="ij")
+    rng = np.random.default_rng(seed)
+    r = (x / shape[0]) ** 2 + (y / shape[1]) ** 2 + (z / shape[2]) ** 2
+    return [np.clip(160 * np.exp(-9 * r) + rng.integers(0, 70, r.shape), 0, 255).astype(np.uint8) for _ in range(2)]
+
+
+def _fov(kind, shape):
+    z, y, x = np.meshgrid(*[np.arange(n) for n in shape[::-1]], indexing="ij")
+    if kind == "whole":
+        return np.ones(shape[::-1], np.uint8)
+    if kind == "holes":
+        return (np.random.default_rng(5).random(shape[::-1]) < 0.995).astype(np.uint8)
+    if kind.startswith("cut"):
+        return (x < (1.0 - float(kind[3:])) * shape[0]).astype(np.uint8)
+    return (np.hypot(x - 0.5 * shape[0], y - 0.5 * shape[1]) <= 0.577 * (z + 0.2 * shape[2])).astype(np.uint8)
+
+
+def _params(score, n, k, seed=3):
+    from paper_2504_19930_amd.config import default_params
+    return default_params(score, n, k, 12.0, 5.0, seed=seed)
+
+
+def _run(score, kind, layout, spacing=1.0):
+    import torch
+    from paper_2504_19930_amd.binding import Registration
+    src, tgt = (torch.from_numpy(v).cuda() for v in _images(SHAPE, 1))
+    r = Registration(src, tgt, _params(score, 150, 4), src_fov=torch.from_numpy(_fov(kind, SHAPE)).cuda(),
+                     tgt_spacing=(spacing,) * 3)
+    r.tune(layout=layout)
+    r.run()
+    out = r.trace()["score"], r.particles()["states"], r.evaluate(r.particles()["states"][:40])
+    r.close()
+    return out
+
+
+@pytest.mark.parametrize("score", ["ncc", "ssd"])
+@pytest.mark.parametrize("kind, spacing", [("whole", 1.0), ("holes", 1.0), ("cut0.15", 1.0), ("cut0.4", 1.0),
+                                           ("cone", 1.0), ("cone", 2.5), ("cone", 6.0)])
+def test_layouts_agree(score, kind, spacing):
+    ref = _run(score, kind, "raw", spacing)
+    for layout in ("oct", "octtile", "lerp"):
+        for a, b in zip(ref, _run(score, kind, layout, spacing)):
+            assert np.array_equal(a, b), layout
+
+
+def test_a_mixed_batch_equals_single_runs():
+    import torch
+    from paper_2504_19930_amd.binding import Batch, Registration
+    pairs = []
+    for i, kind in enumerate(["cone", "whole", "cut0.4", "holes", None, "cut0.1"]):
+        shape = tuple(n + 7 * i for n in SHAPE)
+        src, tgt = (torch.from_numpy(v).cuda() for v in _images(shape, i))
+        q = dict(src=src, tgt=tgt, params=dict(_params("ncc", 120 + 40 * i, 3 + i % 3, seed=i), pair_id=i))
+        if kind:
+            q["src_fov"] = torch.from_numpy(_fov(kind, shape)).cuda()
+        pairs.append(q)
+    b = Batch(pairs)
+    for _ in range(2):
+        b.run()
+        for i, q in enumerate(pairs):
+            r = Registration(q["src"], q["tgt"], q["params"], src_fov=q.get("src_fov"))
+            r.run()
+            assert np.array_equal(r.particles()["states"], b.particles(i)["states"]), i
+            assert np.array_equal(r.trace()["score"], b.trace(i)["score"]), i
+            r.close()
+    b.close()
+
+
+def test_a_fov_of_the_whole_image_costs_no_more_than_none():
+    # (the same kernel but for one comparison a sample; by blocks 1.25 to 1.3)
+    import torch
+    from paper_2504_19930_amd.binding import Registration
+    shape = (128, 120, 110)
+    src, tgt = (torch.from_numpy(v).cuda() for v in _images(shape, 1))
+    fov = torch.ones_like(src)
+    runs = [Registration(src, tgt, _params("ncc", 600, 4), src_fov=f) for f in (None, fov)]
+    best = [np.inf, np.inf]
+    for _ in range(6):
+        for i, r in enumerate(runs):
+            r.profile(True)
+            r.reset(3)
+            r.step(4)
+            best[i] = min(best[i], r.profile_read()["score_ms"])
+    for r in runs:
+        r.close()
+    assert best[1] <= 1.12 * best[0], best
