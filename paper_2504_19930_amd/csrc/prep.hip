@@ -88,9 +88,10 @@ __global__ __launch_bounds__(256) void k_source_rows(const uint8_t *vol, const u
 }
 
 // Per volume (blockIdx.y): FOV voxels, nonzero ones, sum and sum of squares.
-// Sixteen bytes a load where both arrays are 16-byte aligned (a byte a load
-// otherwise), few workgroups: every one ends in four atomics on the same words,
-// and 4096 of them took 53 us for 4.1 MB, twice; 128 take 9 us for both volumes.
+// Sixteen bytes a load at any address, few workgroups: every one ends in four
+// atomics on the same words, and 4096 of them took 53 us for 4.1 MB, twice; 128
+// take 9 us for both volumes.  (With a byte a load for volumes that are not 16-byte
+// aligned, smc_init of 800^3 images at an odd address took 9.0 ms, 2.6 so.)
 struct SumsOf {
     const uint8_t *vol[2], *fov[2];
     uint32_t n[2];
@@ -104,12 +105,12 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) {  // 1 in each by
 __global__ __launch_bounds__(256) void k_volume_sums(const SumsOf a, unsigned long long *out) {
     const uint8_t *vol = a.vol[blockIdx.y], *fov = a.fov[blockIdx.y];
     const uint32_t n = a.n[blockIdx.y], stride = gridDim.x * 256, t = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t n16 = (((uintptr_t)vol | (uintptr_t)fov) & 15u) == 0 ? n / 16 : 0u;
+    const uint32_t n16 = n / 16;
     unsigned long long red4[4] = {0ull, 0ull, 0ull, 0ull};
     for (uint32_t q = t; q < n16; q += stride) {
-        const uint4 v4 = ((const uint4 *)vol)[q];
-        uint4 f4 = make_uint4(~0u, ~0u, ~0u, ~0u);
-        if (fov) f4 = ((const uint4 *)fov)[q];
+        uint4 v4, f4 = make_uint4(~0u, ~0u, ~0u, ~0u);
+        __builtin_memcpy(&v4, vol + 16 * (size_t)q, 16);
+        if (fov) __builtin_memcpy(&f4, fov + 16 * (size_t)q, 16);
         const uint32_t v[4] = {v4.x, v4.y, v4.z, v4.w}, f[4] = {f4.x, f4.y, f4.z, f4.w};
         uint32_t c = 0u, o = 0u, s1 = 0u, s2 = 0u;
 #pragma unroll
