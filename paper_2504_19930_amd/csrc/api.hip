@@ -249,6 +249,24 @@ struct smc_ctx {
                                                                                                : layout;
     }
 
+    // Whether the particles of iteration k + 1 lie far apart: each has walked off its
+    // ancestor by more than kApartVoxels source voxels at the target's ends.  (The
+    // cloud is a few times as wide; 160^3 and 120 x 128 x 110 images in a cone, limits
+    // of 20 and 15 degrees: the smaller parts of such launches cost nothing from 3 to 4
+    // voxels on and 1 to 10 % below.)
+    bool apart_after(uint32_t k) const {
+        constexpr double kApartVoxels = 4.0;
+        double rot = 0.0, trans = 0.0, reach = 0.0, voxel = f.geom.ss[0];
+        for (int d = 0; d < 3; ++d) {
+            rot = std::max(rot, f.sigma0[d]);
+            trans = std::max(trans, f.sigma0[3 + d]);
+            reach = std::max(reach, 0.5 * f.geom.ts[d] * tn[d]);
+            voxel = std::min(voxel, f.geom.ss[d]);
+        }
+        const double walk = pow(f.anneal, k > 0 ? (double)k - 1.0 : 0.0);
+        return walk * (rot * reach + trans) > kApartVoxels * voxel;
+    }
+
     // filter == true: only the sums the filter uses must be exact (masks: a, c);
     // dispersed == true: the particles are spread over the prior box
     ScoreLaunch score_launch(const float *words, unsigned long long *sums, uint32_t p0, uint32_t np,
@@ -483,14 +501,16 @@ smc_status ensure_eval(smc_ctx *c, uint32_t n) {
 // frame pair, then every further frame pair of a multi-frame score (integer
 // sums, so the pooled result does not depend on the order).
 hipError_t launch_score_frames(smc_ctx *c, const float *words, unsigned long long *sums, uint32_t *hist,
-                               uint32_t p0, uint32_t np, bool filter, bool dispersed = false) {
+                               uint32_t p0, uint32_t np, bool filter, bool dispersed = false, bool apart = false) {
     const bool mi = c->p.score == SMC_SCORE_MI;
     ScoreLaunch L = c->score_launch(words, sums, p0, np, filter, dispersed);
     if (mi) L.hist = hist;
+    L.apart = apart;
     hipError_t e = launch_score(L, c->stream);
     for (size_t q = 0; q < c->frames.size() && e == hipSuccess; ++q) {
         ScoreLaunch F = c->frames[q]->score_launch(words, sums, p0, np, filter, dispersed);
         if (mi) F.hist = hist;
+        F.apart = apart;
         e = launch_score(F, c->stream);
     }
     // mutual information: the pooled histograms become scores
@@ -748,7 +768,8 @@ smc_status smc_step(smc_ctx *c, uint32_t n_iters) {
         const uint32_t k = c->k_done + 1;
         const bool dispersed = k == 1 && c->prior_dispersed;
         hipError_t e = timed(c, c->ev_score, [&] {
-            return launch_score_frames(c, c->f.words, c->f.sums, c->hist, 0, c->f.n + 1, true, dispersed);
+            return launch_score_frames(c, c->f.words, c->f.sums, c->hist, 0, c->f.n + 1, true, dispersed,
+                                       c->apart_after(k - 1));
         });
         if (e == hipSuccess) e = timed(c, c->ev_filter, [&] { return launch_filter(c->f, k, c->stream); });
         if (e == hipSuccess && k == c->f.n_iters) {

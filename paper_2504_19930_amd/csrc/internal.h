@@ -116,6 +116,8 @@ struct ScoreLaunch {
         const uint32_t *tz = nullptr, *fz = nullptr;
         const void *t4 = nullptr, *t8 = nullptr, *t16 = nullptr;
     } tri;
+    // images by blocks: the particles lie far apart for the source's voxels
+    bool apart = false;
     // masks, ac launches (or nullptr): kWorkSlots counter triples,
     // kWorkSlotWords apart; summed over the slots, word 0 counts the particle x
     // voxel pairs sampled, word 1 the pairs covered (the decided ones

@@ -59,6 +59,11 @@ constexpr int kSumBlocks = 12, kHistBlocks = 48;
 // whose pairs have few particle groups, gains from longer runs (16 pairs 26.8 ms
 // with 16, 25.9 with 32, 26.2 with 64, 27.8 without).
 constexpr uint32_t kRun = 16, kBatchRun = 32;
+// Particles far apart (ScoreLaunch::apart): small parts and longer runs, since the
+// image of a part under all the particles has to stay in the L2.  Rotations up to
+// 180 degrees, 128 x 120 x 110 in a cone, N = 600, K = 6: 13.5 ms with twelve blocks
+// and runs of 16, 9.6 with four and 32 (11.2 in tiles).
+constexpr uint32_t kApartBlocks = 4, kApartRun = 32;
 
 #if defined(__HIP_DEVICE_COMPILE__)
 #define SMC_CONSTANT_AS __attribute__((address_space(4)))
@@ -99,6 +104,7 @@ struct Args {
     uint32_t ysb, zsb;     // element strides (tiled octets: byte strides, see score.hip)
     uint32_t g4[3], g8[3], g16[3], n16;
     uint32_t p0, np, blocks, parts;  // 16^3 blocks per workgroup; workgroups per four particles
+    uint32_t run;                    // consecutive workgroups of an XCD
 };
 
 __device__ __forceinline__ half2v as_half2(uint32_t u) {
@@ -309,20 +315,19 @@ __device__ __forceinline__ void list_blocks(const A &a, uint32_t first, uint32_t
 // VMODE: source FOV validity of a sample: 1 src_ok gathered, 2 packed elements
 // equal to the sentinel.  ACC: 0 moments, 1 histogram, 2 the gathers
 // alone (loaded words XORed into the result).
-template <int LAYOUT, int VMODE, int ACC, uint32_t RUN, typename A>
+template <int LAYOUT, int VMODE, int ACC, typename A>
 __device__ __forceinline__ uint32_t tri_body(const A &a, uint32_t block) {
     constexpr bool HIST = ACC == 1, PROBE = ACC == 2;
     constexpr int BLOCKS = HIST ? kHistBlocks : kSumBlocks;
     __shared__ uint32_t lhist[HIST ? PT : 1][HIST ? kHB : 1];
     __shared__ unsigned long long red[HIST ? 1 : kWaves][PT][6];
     __shared__ Lists<BLOCKS> list;
-    // The dispatcher hands workgroup b to XCD b % 8: each XCD takes runs of RUN
+    // The dispatcher hands workgroup b to XCD b % 8: each XCD takes runs of a.run
     // of the (part, particles) sequence, so the workgroups in flight on it share
     // a part or two, whose source its L2 holds, and all of them their share of
     // the parts that are mostly skipped (the last ones in order)
-    constexpr uint32_t kAll = 8u * RUN;
-    const uint32_t groups = (a.np + PT - 1u) / PT, whole = groups * a.parts / kAll * kAll;
-    const uint32_t seq = block < whole ? block / kAll * kAll + block % 8u * RUN + block / 8u % RUN : block;
+    const uint32_t all = 8u * a.run, groups = (a.np + PT - 1u) / PT, whole = groups * a.parts / all * all;
+    const uint32_t seq = block < whole ? block / all * all + block % 8u * a.run + block / 8u % a.run : block;
     const uint32_t part = seq / groups, group = seq - part * groups;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
     const uint32_t lane = threadIdx.x % 64u;
@@ -633,12 +638,12 @@ __device__ __forceinline__ uint32_t tri_body(const A &a, uint32_t block) {
 
 template <int LAYOUT, int VMODE, int ACC>
 __global__ __launch_bounds__(kThreads) void k_score_tri(const Args a) {
-    tri_body<LAYOUT, VMODE, ACC, kRun>(a, blockIdx.x);
+    tri_body<LAYOUT, VMODE, ACC>(a, blockIdx.x);
 }
 
 template <int LAYOUT>
 __global__ __launch_bounds__(kThreads) void k_probe_tri(const Args a, uint32_t key, uint32_t *out) {
-    const uint32_t chk = tri_body<LAYOUT, 2, 2, kRun>(a, blockIdx.x);
+    const uint32_t chk = tri_body<LAYOUT, 2, 2>(a, blockIdx.x);
     if (chk == key) out[0] = chk;
 }
 
@@ -656,7 +661,7 @@ __global__ __launch_bounds__(kThreads) void k_batch_tri(const Args *pairs_g, con
     }
     if (as_const(kmax_g)[lo] < k) return;  // pairs with fewer iterations are done
     const Args a = as_const(pairs_g)[lo];
-    tri_body<LAYOUT, VMODE, 0, kBatchRun>(a, blockIdx.x - offs[lo]);
+    tri_body<LAYOUT, VMODE, 0>(a, blockIdx.x - offs[lo]);
 }
 
 // ---------------------------------------------------------------- preparation
@@ -766,7 +771,7 @@ __global__ __launch_bounds__(256) void k_count_off(const uint8_t *field, uint32_
 unsigned blocks_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192)); }
 uint32_t cells(int32_t n, int32_t side) { return (uint32_t)((n + side - 1) / side); }
 
-Args make_args(const ScoreLaunch &L) {
+Args make_args(const ScoreLaunch &L, bool batch = false) {
     Args a;
     a.src = L.src_packed;
     a.src_ok = L.src_ok;
@@ -801,10 +806,11 @@ Args make_args(const ScoreLaunch &L) {
     a.np = L.np;
     // fewer blocks a workgroup while the launch would have under 2048 of them
     // (eight per CU)
-    const uint64_t groups = (L.np + PT - 1) / PT, most = L.hist ? kHistBlocks : kSumBlocks;
+    const uint64_t groups = (L.np + PT - 1) / PT, most = L.hist ? kHistBlocks : (L.apart ? (int)kApartBlocks : kSumBlocks);
     const uint64_t want = (uint64_t)a.n16 * groups / 2048u;
     a.blocks = kWaves * (uint32_t)std::min<uint64_t>(most / kWaves, std::max<uint64_t>(1u, want / kWaves));
     a.parts = (a.n16 + a.blocks - 1) / a.blocks;
+    a.run = batch ? kBatchRun : (L.apart ? kApartRun : kRun);
     return a;
 }
 
@@ -921,7 +927,7 @@ hipError_t launch_tri_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, h
 size_t tri_args_bytes() { return sizeof(Args); }
 
 uint64_t tri_args(const ScoreLaunch &L, void *out) {
-    const Args a = make_args(L);
+    const Args a = make_args(L, true);
     memcpy(out, &a, sizeof a);
     return groups_of(a);
 }
