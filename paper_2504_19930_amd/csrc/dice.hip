@@ -355,39 +355,42 @@ __device__ __forceinline__ bool wave_unit(const A &a, uint32_t block, uint32_t &
     return i < a.np;
 }
 
-__global__ __launch_bounds__(kThreads) void k_score_dice(const Args a) {
+// (workgroups first .. of the launch)
+__global__ __launch_bounds__(kThreads) void k_score_dice(const Args a, uint32_t first) {
     __shared__ WaveLds q[kWaves];
     uint32_t part, p;
-    if (blockIdx.x == 0u && threadIdx.x == 0u && a.work)
+    if (first + blockIdx.x == 0u && threadIdx.x == 0u && a.work)
         atomicAdd(a.work + 1, (unsigned long long)a.np * (unsigned long long)a.tn[0] * (unsigned long long)a.tn[1] *
                                   (unsigned long long)a.tn[2]);
-    if (!wave_unit(a, blockIdx.x, part, p)) return;
+    if (!wave_unit(a, first + blockIdx.x, part, p)) return;
     dice_wave<false>(a, part, p, q[threadIdx.x / 64u]);
 }
 
-__global__ __launch_bounds__(kThreads) void k_probe_dice(const Args a, uint32_t key, uint32_t *out) {
+__global__ __launch_bounds__(kThreads) void k_probe_dice(const Args a, uint32_t first, uint32_t key, uint32_t *out) {
     __shared__ WaveLds q[kWaves];
     uint32_t part, p;
-    if (!wave_unit(a, blockIdx.x, part, p)) return;
+    if (!wave_unit(a, first + blockIdx.x, part, p)) return;
     const uint32_t chk = dice_wave<true>(a, part, p, q[threadIdx.x / 64u]);
     if (chk == key) out[0] = chk;
 }
 
 // The mask pairs of a batch: pair d owns workgroups offs[d] .. offs[d + 1) - 1.
 __global__ __launch_bounds__(kThreads) void k_batch_dice(const Args *pairs_g, const uint32_t *offs_g,
-                                                         const uint32_t *kmax_g, uint32_t n_pairs, uint32_t k) {
+                                                         const uint32_t *kmax_g, uint32_t n_pairs, uint32_t k,
+                                                         uint32_t first) {
     __shared__ WaveLds q[kWaves];
     const auto *offs = as_const(offs_g);
+    const uint32_t block = first + blockIdx.x;
     uint32_t lo = 0, hi = n_pairs - 1;
     while (lo < hi) {
         const uint32_t mid = (lo + hi + 1) >> 1;
-        if (offs[mid] <= blockIdx.x) lo = mid;
+        if (offs[mid] <= block) lo = mid;
         else hi = mid - 1;
     }
     if (as_const(kmax_g)[lo] < k) return;  // pairs with fewer iterations are done
     const Args a = as_const(pairs_g)[lo];
     uint32_t part, p;
-    if (!wave_unit(a, blockIdx.x - offs[lo], part, p)) return;
+    if (!wave_unit(a, block - offs[lo], part, p)) return;
     dice_wave<false>(a, part, p, q[threadIdx.x / 64u]);
 }
 
@@ -671,26 +674,25 @@ uint64_t dice_args(const ScoreLaunch &L, void *out) {
 hipError_t launch_dice(const ScoreLaunch &L, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
     const Args a = make_args(L);
-    const uint64_t groups = groups_of(a);
-    if (groups > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_score_dice, dim3((unsigned)groups), dim3(kThreads), 0, s, a);
-    return hipGetLastError();
+    return launch_groups(groups_of(a), [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(k_score_dice, grid, dim3(kThreads), 0, s, a, first);
+    });
 }
 
 hipError_t launch_dice_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
     const Args a = make_args(L);
-    const uint64_t groups = groups_of(a);
-    if (groups > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_probe_dice, dim3((unsigned)groups), dim3(kThreads), 0, s, a, key, out);
-    return hipGetLastError();
+    return launch_groups(groups_of(a), [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(k_probe_dice, grid, dim3(kThreads), 0, s, a, first, key, out);
+    });
 }
 
 hipError_t launch_batch_dice(const void *pairs, const uint32_t *offs, const uint32_t *kmax, uint32_t n_pairs,
                              uint32_t groups, uint32_t k, hipStream_t s) {
-    if (n_pairs == 0 || groups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_dice, dim3(groups), dim3(kThreads), 0, s, (const Args *)pairs, offs, kmax, n_pairs, k);
-    return hipGetLastError();
+    if (n_pairs == 0) return hipSuccess;
+    return launch_groups(groups, [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(k_batch_dice, grid, dim3(kThreads), 0, s, (const Args *)pairs, offs, kmax, n_pairs, k, first);
+    });
 }
 
 }  // namespace smc

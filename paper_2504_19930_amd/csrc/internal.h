@@ -137,6 +137,20 @@ struct ScoreLaunch {
 // Most work items (tiles x particle groups) one scoring launch takes: a grid
 // dimension of signed 32-bit size.
 constexpr uint64_t kMaxScoreItems = 0x7FFFFFFFull;
+// Workgroups of one launch: a grid counts its threads in 32 bits.  launch(first,
+// n) launches workgroups first .. first + n - 1 (first a multiple of 8, the XCDs).
+constexpr uint64_t kMaxGridGroups = 1ull << 23;
+template <typename F>
+hipError_t launch_groups(uint64_t groups, F launch) {
+    if (groups > kMaxScoreItems) return hipErrorInvalidConfiguration;
+    hipError_t e = hipSuccess;
+    for (uint64_t first = 0; first < groups && e == hipSuccess; first += kMaxGridGroups) {
+        const uint64_t left = groups - first;
+        launch((uint32_t)first, dim3((unsigned)(left < kMaxGridGroups ? left : kMaxGridGroups)));
+        e = hipGetLastError();
+    }
+    return e;
+}
 // Items (tiles x particle groups) of a launch of L's shape with np particles.
 uint64_t score_items_for(const ScoreLaunch &L);
 

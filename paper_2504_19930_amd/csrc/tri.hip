@@ -637,13 +637,13 @@ __device__ __forceinline__ uint32_t tri_body(const A &a, uint32_t block) {
 }
 
 template <int LAYOUT, int VMODE, int ACC>
-__global__ __launch_bounds__(kThreads) void k_score_tri(const Args a) {
-    tri_body<LAYOUT, VMODE, ACC>(a, blockIdx.x);
+__global__ __launch_bounds__(kThreads) void k_score_tri(const Args a, uint32_t first) {
+    tri_body<LAYOUT, VMODE, ACC>(a, first + blockIdx.x);
 }
 
 template <int LAYOUT>
-__global__ __launch_bounds__(kThreads) void k_probe_tri(const Args a, uint32_t key, uint32_t *out) {
-    const uint32_t chk = tri_body<LAYOUT, 2, 2>(a, blockIdx.x);
+__global__ __launch_bounds__(kThreads) void k_probe_tri(const Args a, uint32_t first, uint32_t key, uint32_t *out) {
+    const uint32_t chk = tri_body<LAYOUT, 2, 2>(a, first + blockIdx.x);
     if (chk == key) out[0] = chk;
 }
 
@@ -651,17 +651,19 @@ __global__ __launch_bounds__(kThreads) void k_probe_tri(const Args a, uint32_t k
 // offs[d + 1) - 1.
 template <int LAYOUT, int VMODE>
 __global__ __launch_bounds__(kThreads) void k_batch_tri(const Args *pairs_g, const uint32_t *offs_g,
-                                                        const uint32_t *kmax_g, uint32_t n_pairs, uint32_t k) {
+                                                        const uint32_t *kmax_g, uint32_t n_pairs, uint32_t k,
+                                                        uint32_t first) {
     const auto *offs = as_const(offs_g);
+    const uint32_t block = first + blockIdx.x;
     uint32_t lo = 0, hi = n_pairs - 1;
     while (lo < hi) {
         const uint32_t mid = (lo + hi + 1) >> 1;
-        if (offs[mid] <= blockIdx.x) lo = mid;
+        if (offs[mid] <= block) lo = mid;
         else hi = mid - 1;
     }
     if (as_const(kmax_g)[lo] < k) return;  // pairs with fewer iterations are done
     const Args a = as_const(pairs_g)[lo];
-    tri_body<LAYOUT, VMODE, 0>(a, blockIdx.x - offs[lo]);
+    tri_body<LAYOUT, VMODE, 0>(a, block - offs[lo]);
 }
 
 // ---------------------------------------------------------------- preparation
@@ -816,8 +818,8 @@ Args make_args(const ScoreLaunch &L, bool batch = false) {
 
 uint64_t groups_of(const Args &a) { return (uint64_t)a.parts * ((a.np + PT - 1) / PT); }
 
-typedef void (*Kernel)(const Args);
-typedef void (*BatchKernel)(const Args *, const uint32_t *, const uint32_t *, uint32_t, uint32_t);
+typedef void (*Kernel)(const Args, uint32_t);
+typedef void (*BatchKernel)(const Args *, const uint32_t *, const uint32_t *, uint32_t, uint32_t, uint32_t);
 
 template <int LAYOUT, int ACC>
 Kernel pick(int vmode) {
@@ -905,23 +907,21 @@ bool tri_supported(const ScoreLaunch &L) {
 hipError_t launch_tri(const ScoreLaunch &L, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
     const Args a = make_args(L);
-    const uint64_t groups = groups_of(a);
-    if (groups > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
     const int vmode = L.has_sentinel ? 2 : 1;
     const Kernel k = L.hist ? pick<1>(L.layout, vmode) : pick<0>(L.layout, vmode);
-    hipLaunchKernelGGL(k, dim3((unsigned)groups), dim3(kThreads), 0, s, a);
-    return hipGetLastError();
+    return launch_groups(groups_of(a), [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(k, grid, dim3(kThreads), 0, s, a, first);
+    });
 }
 
 hipError_t launch_tri_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
     const Args a = make_args(L);
-    const uint64_t groups = groups_of(a);
-    if (groups > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
     auto *k = L.layout == kLayoutLerp ? k_probe_tri<kLayoutLerp>
                                       : (L.layout == kLayoutOct ? k_probe_tri<kLayoutOct> : k_probe_tri<kLayoutOctTile>);
-    hipLaunchKernelGGL(k, dim3((unsigned)groups), dim3(kThreads), 0, s, a, key, out);
-    return hipGetLastError();
+    return launch_groups(groups_of(a), [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(k, grid, dim3(kThreads), 0, s, a, first, key, out);
+    });
 }
 
 size_t tri_args_bytes() { return sizeof(Args); }
@@ -934,12 +934,13 @@ uint64_t tri_args(const ScoreLaunch &L, void *out) {
 
 hipError_t launch_batch_tri(int layout, int vmode, const void *pairs, const uint32_t *offs, const uint32_t *kmax,
                             uint32_t n_pairs, uint32_t groups, uint32_t k, hipStream_t s) {
-    if (n_pairs == 0 || groups == 0) return hipSuccess;
+    if (n_pairs == 0) return hipSuccess;
     const BatchKernel b = layout == kLayoutLerp
                               ? pick_batch<kLayoutLerp>(vmode)
                               : (layout == kLayoutOct ? pick_batch<kLayoutOct>(vmode) : pick_batch<kLayoutOctTile>(vmode));
-    hipLaunchKernelGGL(b, dim3(groups), dim3(kThreads), 0, s, (const Args *)pairs, offs, kmax, n_pairs, k);
-    return hipGetLastError();
+    return launch_groups(groups, [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(b, grid, dim3(kThreads), 0, s, (const Args *)pairs, offs, kmax, n_pairs, k, first);
+    });
 }
 
 }  // namespace smc

@@ -447,6 +447,8 @@ void spread(WArgs &a, F fits) {
         return (uint64_t)a.bxy * (uint64_t)((a.tn2 + a.zc - 1) / a.zc) * ((a.frames + a.fg - 1) / a.fg);
     };
     a.fg = std::min(a.fg, a.frames);
+    // (more frames a workgroup where the launch would not fit one grid)
+    while (a.fg < a.frames && groups() > kMaxGridGroups) a.fg *= 2;
     while (a.fg > 1 && groups() < kFillGroups) a.fg /= 2;
     while (a.zc > 4 && groups() < kFillGroups && fits(a.zc / 2)) a.zc /= 2;
 }
