@@ -1553,8 +1553,9 @@ smc_status plan_class(smc_batch *b, smc_batch::Class &C, int vmode) {
             return fail(SMC_EINVAL, "batch class mixes tunings (pair %u)", C.members[q]);
         }
         score_args(L, args.data() + ab * q);
-        const uint32_t items = score_items(L);
-        offs[q + 1] = offs[q] + items;
+        const uint64_t items = score_items_for(L);
+        if (offs[q] + items > kMaxScoreItems) return fail(SMC_EINVAL, "the batch's pairs exceed one launch");
+        offs[q + 1] = offs[q] + (uint32_t)items;
         kmax[q] = c->f.n_iters;
         work[q] = (double)items * (double)c->tn[2];
     }
@@ -1608,7 +1609,7 @@ smc_status plan_class(smc_batch *b, smc_batch::Class &C, int vmode) {
         const ScoreLaunch F = c->score_launch(c->f.words, c->f.sums, 0, c->f.n + 1, true, true);
         if (q == 0) flayout = F.layout;
         ok = !c->f.has_proposal && F.layout == flayout && F.layout != layout && F.pt == pt &&
-             score_vmode(F) == vmode && score_items(F) == offs[q + 1] - offs[q];
+             score_vmode(F) == vmode && score_items_for(F) == offs[q + 1] - offs[q];
         if (ok) score_args(F, fargs.data() + ab * q);
     }
     if (ok) {

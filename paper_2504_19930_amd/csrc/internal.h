@@ -159,7 +159,6 @@ hipError_t launch_score(const ScoreLaunch &L, hipStream_t s);
 // source loads without the rest of the kernel's work; see score.hip.
 bool gather_probe_supported(const ScoreLaunch &L);
 hipError_t launch_gather_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out, hipStream_t s);
-void score_grid(const ScoreLaunch &L, dim3 *grid, dim3 *block);
 bool score_pt_supported(int pt);
 // whether a packed trilinear layout can address a source of this shape
 bool layout_fits(int layout, const int32_t sn[3]);
@@ -201,7 +200,6 @@ struct BatchPlan {
     uint32_t *counters;
 };
 size_t score_args_bytes();
-uint32_t score_items(const ScoreLaunch &L);
 void score_args(const ScoreLaunch &L, void *out);
 hipError_t launch_batch_score(const BatchPlan &P, uint32_t k, hipStream_t s);
 const void *batch_kernel(const BatchPlan &P);

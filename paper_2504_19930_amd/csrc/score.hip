@@ -857,9 +857,9 @@ __device__ __forceinline__ void xcd_order(uint32_t b, uint32_t total, uint32_t g
 }
 
 template <int PT>
-__global__ __launch_bounds__(kThreads) void k_score_mask(const KArgs a) {
+__global__ __launch_bounds__(kThreads) void k_score_mask(const KArgs a, uint32_t first, uint32_t items) {
     uint32_t bx, by;
-    xcd_order(blockIdx.x, gridDim.x, (a.np + PT - 1) / PT, &bx, &by);
+    xcd_order(first + blockIdx.x, items, (a.np + PT - 1) / PT, &bx, &by);
     mask_body<PT>(a, bx, by);
 }
 
@@ -873,9 +873,9 @@ constexpr int kImageWaves =
 
 template <int PT, int LAYOUT, bool TRI, int VMODE, int ACC = 0>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kImageWaves<PT, LAYOUT, VMODE, ACC>)))
-void k_score_image(const KArgs a) {
+void k_score_image(const KArgs a, uint32_t first, uint32_t items) {
     uint32_t bx, by;
-    xcd_order(blockIdx.x, gridDim.x, (a.np + PT - 1) / PT, &bx, &by);
+    xcd_order(first + blockIdx.x, items, (a.np + PT - 1) / PT, &bx, &by);
     image_body<PT, LAYOUT, TRI, VMODE, ACC>(a, bx, by);
 }
 
@@ -1011,7 +1011,7 @@ KArgs make_args(const ScoreLaunch &L, int pt, int *nz_chunks) {
     return a;
 }
 
-typedef void (*ScoreKernel)(const KArgs);
+typedef void (*ScoreKernel)(const KArgs, uint32_t, uint32_t);
 
 // (histograms in the layouts of one gather come here without a source FOV only:
 // tri_supported)
@@ -1063,12 +1063,6 @@ bool layout_fits(int layout, const int32_t sn[3]) {
 }
 
 size_t score_args_bytes() { return sizeof(KArgs); }
-
-uint32_t score_items(const ScoreLaunch &L) {
-    dim3 grid, block;
-    score_grid(L, &grid, &block);
-    return grid.x * grid.y;
-}
 
 void score_args(const ScoreLaunch &L, void *out) {
     int chunks;
@@ -1146,23 +1140,12 @@ int score_vmode(const ScoreLaunch &L) {
     return make_args(L, 8, &chunks).vmode;
 }
 
-// Work items (tiles x particle groups) of a launch, in 64 bits.
-uint64_t score_items64(const ScoreLaunch &L) {
+uint64_t score_items_for(const ScoreLaunch &L) {
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
     return (uint64_t)a.tiles_x * (uint64_t)a.tiles_y * (uint64_t)chunks * (uint64_t)((L.np + pt - 1) / pt);
 }
-
-// A one-dimensional grid of one workgroup per item; grid.x = 0 (no launch
-// possible) when the items exceed a grid dimension.
-void score_grid(const ScoreLaunch &L, dim3 *grid, dim3 *block) {
-    const uint64_t items = score_items64(L);
-    *grid = dim3(items <= kMaxScoreItems ? (unsigned)items : 0u, 1, 1);
-    *block = dim3(kThreads, 1, 1);
-}
-
-uint64_t score_items_for(const ScoreLaunch &L) { return score_items64(L); }
 
 hipError_t launch_score(const ScoreLaunch &L, hipStream_t s) {
     if (L.np == 0) return hipSuccess;
@@ -1171,12 +1154,11 @@ hipError_t launch_score(const ScoreLaunch &L, hipStream_t s) {
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
-    dim3 grid, block;
-    score_grid(L, &grid, &block);
-    if (grid.x == 0) return hipErrorInvalidConfiguration;
+    const uint64_t items = score_items_for(L);
     ScoreKernel k = pt == 4 ? pick<4>(L) : (pt == 16 ? pick<16>(L) : pick<8>(L));
-    hipLaunchKernelGGL(k, grid, block, 0, s, a);
-    return hipGetLastError();
+    return launch_groups(items, [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(k, grid, dim3(kThreads), 0, s, a, first, (uint32_t)items);
+    });
 }
 
 // ---------------------------------------------------------------- gather probe
@@ -1240,16 +1222,16 @@ __device__ __forceinline__ uint32_t probe_image_body(const KArgs &a, uint32_t bx
 }
 
 template <int PT, int LAYOUT>
-__global__ __launch_bounds__(kThreads) void k_gather_probe(const KArgs a, uint32_t key, uint32_t *out) {
+__global__ __launch_bounds__(kThreads) void k_gather_probe(const KArgs a, uint32_t first, uint32_t items, uint32_t key, uint32_t *out) {
     uint32_t bx, by;
-    xcd_order(blockIdx.x, gridDim.x, (a.np + PT - 1) / PT, &bx, &by);
+    xcd_order(first + blockIdx.x, items, (a.np + PT - 1) / PT, &bx, &by);
     const uint32_t chk = probe_image_body<PT, LAYOUT>(a, bx, by);
     if (chk == key) out[0] = chk;
 }
 
 template <int PT>
 ScoreKernel probe_kernel(const ScoreLaunch &L) {
-    typedef void (*PK)(const KArgs, uint32_t, uint32_t *);
+    typedef void (*PK)(const KArgs, uint32_t, uint32_t, uint32_t, uint32_t *);
     PK k = nullptr;
     if (L.layout == kLayoutOct) k = k_gather_probe<PT, kLayoutOct>;
     else if (L.layout == kLayoutOctTile) k = k_gather_probe<PT, kLayoutOctTile>;
@@ -1274,13 +1256,12 @@ hipError_t launch_gather_probe(const ScoreLaunch &L, uint32_t key, uint32_t *out
     int chunks;
     const int pt = score_pt_supported(L.pt) ? L.pt : 8;
     const KArgs a = make_args(L, pt, &chunks);
-    dim3 grid, block;
-    score_grid(L, &grid, &block);
-    if (grid.x == 0) return hipErrorInvalidConfiguration;
+    const uint64_t items = score_items_for(L);
     ScoreKernel k = pt == 4 ? probe_kernel<4>(L) : (pt == 16 ? probe_kernel<16>(L) : probe_kernel<8>(L));
-    typedef void (*PK)(const KArgs, uint32_t, uint32_t *);
-    hipLaunchKernelGGL(reinterpret_cast<PK>(k), grid, block, 0, s, a, key, out);
-    return hipGetLastError();
+    typedef void (*PK)(const KArgs, uint32_t, uint32_t, uint32_t, uint32_t *);
+    return launch_groups(items, [&](uint32_t first, dim3 grid) {
+        hipLaunchKernelGGL(reinterpret_cast<PK>(k), grid, dim3(kThreads), 0, s, a, first, (uint32_t)items, key, out);
+    });
 }
 
 }  // namespace smc

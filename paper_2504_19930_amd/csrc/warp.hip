@@ -72,7 +72,7 @@ struct WArgs {
     int32_t sn0, sn1, sn2, tn0, tn1, tn2;
     int64_t src_stride, dst_stride;
     int32_t xblocks, bxy, zchunks, zc;  // tiles per row and per slab, slabs per frame, slices per tile
-    uint32_t total;                     // workgroups
+    uint32_t total, first;              // workgroups; those of this grid begin at first
     uint32_t frames, fg;                // frames; frames per workgroup (groups of fg)
     // staged kernel: per source axis sum_e |w_de| (T_e - 1) over a tile's
     // extents T; LDS row pitch, rows per LDS slice, slice pitch
@@ -87,7 +87,7 @@ struct WTile {
 // Tile of this workgroup: the (x-block, row block, slab, frame group) order
 // split into eight contiguous runs, run r on XCD r.
 __device__ __forceinline__ WTile warp_tile(const WArgs &a) {
-    const uint32_t T = a.total, b = blockIdx.x, xcd = b % 8u, kk = b / 8u, q = T / 8u, r = T % 8u;
+    const uint32_t T = a.total, b = a.first + blockIdx.x, xcd = b % 8u, kk = b / 8u, q = T / 8u, r = T % 8u;
     const uint32_t lin = (xcd < r ? xcd * (q + 1u) : r * (q + 1u) + (xcd - r) * q) + kk;
     const uint32_t per_frame = (uint32_t)a.bxy * (uint32_t)a.zchunks;
     WTile t;
@@ -447,8 +447,6 @@ void spread(WArgs &a, F fits) {
         return (uint64_t)a.bxy * (uint64_t)((a.tn2 + a.zc - 1) / a.zc) * ((a.frames + a.fg - 1) / a.fg);
     };
     a.fg = std::min(a.fg, a.frames);
-    // (more frames a workgroup where the launch would not fit one grid)
-    while (a.fg < a.frames && groups() > kMaxGridGroups) a.fg *= 2;
     while (a.fg > 1 && groups() < kFillGroups) a.fg /= 2;
     while (a.zc > 4 && groups() < kFillGroups && fits(a.zc / 2)) a.zc /= 2;
 }
@@ -481,12 +479,13 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
         spread(a, [](int) { return true; });
         a.zchunks = (tn[2] + a.zc - 1) / a.zc;
         const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
-        if (total > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
         a.total = (uint32_t)total;
-        if (a.zc == 16) hipLaunchKernelGGL(k_warp_nearest<16>, dim3(a.total), block, 0, s, a);
-        else if (a.zc == 8) hipLaunchKernelGGL(k_warp_nearest<8>, dim3(a.total), block, 0, s, a);
-        else hipLaunchKernelGGL(k_warp_nearest<4>, dim3(a.total), block, 0, s, a);
-        return hipGetLastError();
+        return launch_groups(total, [&](uint32_t first, dim3 grid) {
+            a.first = first;
+            if (a.zc == 16) hipLaunchKernelGGL(k_warp_nearest<16>, grid, block, 0, s, a);
+            else if (a.zc == 8) hipLaunchKernelGGL(k_warp_nearest<8>, grid, block, 0, s, a);
+            else hipLaunchKernelGGL(k_warp_nearest<4>, grid, block, 0, s, a);
+        });
     }
 
     // staged trilinear: at least 16 bytes of source, every partial sum of the
@@ -522,13 +521,14 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
     }
     a.zchunks = (tn[2] + a.zc - 1) / a.zc;
     const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
-    if (total > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
     a.total = (uint32_t)total;
-    if (!staged) hipLaunchKernelGGL(k_warp_trilinear, dim3(a.total), block, 0, s, a);
-    else if (a.zc == 16) hipLaunchKernelGGL(k_warp_trilinear_lds<16>, dim3(a.total), block, bytes, s, a);
-    else if (a.zc == 8) hipLaunchKernelGGL(k_warp_trilinear_lds<8>, dim3(a.total), block, bytes, s, a);
-    else hipLaunchKernelGGL(k_warp_trilinear_lds<4>, dim3(a.total), block, bytes, s, a);
-    return hipGetLastError();
+    return launch_groups(total, [&](uint32_t first, dim3 grid) {
+        a.first = first;
+        if (!staged) hipLaunchKernelGGL(k_warp_trilinear, grid, block, 0, s, a);
+        else if (a.zc == 16) hipLaunchKernelGGL(k_warp_trilinear_lds<16>, grid, block, bytes, s, a);
+        else if (a.zc == 8) hipLaunchKernelGGL(k_warp_trilinear_lds<8>, grid, block, bytes, s, a);
+        else hipLaunchKernelGGL(k_warp_trilinear_lds<4>, grid, block, bytes, s, a);
+    });
 }
 
 }  // namespace smc

@@ -1,6 +1,7 @@
 """Launches of 2^24 workgroups and more, whose 2^32 threads do not fit one grid:
 mask and image registrations of a flat target and many particles, single and in a
-batch, and warps of very many frames."""
+batch, evaluations of thousands of states and warps of very many frames (one
+voxel each, which leaves trilinear ones to the kernel without staging)."""
 
 import numpy as np
 import pytest
@@ -81,14 +82,29 @@ def test_batch():
     b.close()
 
 
-def test_warp_of_many_frames():
+@pytest.mark.parametrize("image", [False, True])
+def test_evaluations(image):
+    from paper_2504_19930_amd.binding import Registration
+    # 16384 tiles x 1025 groups of states, against 820 states at a time
+    src, tgt = _flat_pair(4096, 2048, image)
+    r = Registration(src, tgt, _params("ncc" if image else "dice", 8))
+    r.tune(tile_depth=16)
+    rng = np.random.default_rng(2)
+    states = rng.uniform(-1, 1, (4100, 6)) * np.array([2e-3] * 3 + [3.0] * 3)
+    sums = r.evaluate(states)
+    assert len(np.unique(sums[:, 1])) > 10
+    assert np.array_equal(sums, np.concatenate([r.evaluate(s) for s in np.array_split(states, 5)]))
+    r.close()
+
+
+@pytest.mark.parametrize("interp, frames", [("nearest", 65535), ("trilinear", 16400)])
+def test_warp_of_many_frames(interp, frames):
     import torch
     from paper_2504_19930_amd import binding
-    frames = 65535
     src = torch.randint(1, 256, (frames, 1, 1, 1), dtype=torch.uint8, device="cuda")
     dst = torch.full((frames, 256, 512, 1), 7, dtype=torch.uint8, device="cuda")
     M = np.concatenate([np.eye(3), np.zeros((3, 1))], axis=1)
-    binding.warp_apply(binding.volume(src[0]), M, "nearest", dst, n_frames=frames, src_frame_stride=1,
+    binding.warp_apply(binding.volume(src[0]), M, interp, dst, n_frames=frames, src_frame_stride=1,
                        dst_frame_stride=256 * 512)
     assert torch.equal(dst[:, 0, 0, 0], src[:, 0, 0, 0])
     dst[:, 0, 0, 0] = 0
