@@ -625,34 +625,32 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
     uint8_t *tz = nullptr, *fz = nullptr, *layout_buf = nullptr;
     const DiceSizes ds = dice_sizes(c->sn, c->tn);
     const TriSizes ts = tri_sizes(c->sn, c->tn);
-    // (scratch of the field's passes: gap_x, gap_y, and an image's two bitmaps)
-    const uint64_t scratch_bytes = images ? 2 * ts.gap + 2 * ts.bits : ds.gap_x + ds.gap_y;
+    // scratch of the field's passes: a byte a voxel, and an image's two bitmaps; it
+    // lies where arrays that are made later will be
+    const uint64_t scratch_bytes = images ? vs + 2 * ts.bits : vs;
     if (!layout_fits(c->layout, c->sn)) c->layout = layout_fits(kLayoutOct, c->sn) ? kLayoutOct : kLayoutRaw;
     if (!images) {
         c->reserve(&c->src_prep, vs);
-        c->reserve(&c->tgt_prep, vt);
+        c->reserve(&c->tgt_prep, std::max<uint64_t>(vt, scratch_bytes));
         c->reserve(&bits, ds.bits);
         c->reserve(&field, ds.field);
         c->reserve(&t4, ds.t4);
         c->reserve(&t8, ds.t8);
         c->reserve(&t16, ds.t16);
         c->reserve(&c->work, kWorkSlots * kWorkSlotWords);
-        c->reserve(&scratch, scratch_bytes);
     } else if (corners) {
+        // (the layout if it is large enough, else the target's dwords)
+        if (c->layout != kLayoutRaw && packed_bytes(c->layout, c->sn) >= scratch_bytes) {
+            if ((st = c->alloc(&layout_buf, packed_bytes(c->layout, c->sn))) != SMC_OK) return bail(st);
+            scratch = layout_buf;
+        }
         c->reserve(&c->src_ok, vs);
         c->reserve(&field, ts.field);
-        c->reserve(&tz, ts.tz);
+        c->reserve(&tz, scratch ? ts.tz : std::max(ts.tz, scratch_bytes));
         if (tgt->fov) c->reserve(&fz, ts.tz);
         c->reserve(&t4, ts.t4);
         c->reserve(&t8, ts.t8);
         c->reserve(&t16, ts.t16);
-        // the field is done before the layout is packed: it borrows its memory
-        if (c->layout != kLayoutRaw && packed_bytes(c->layout, c->sn) >= scratch_bytes) {
-            if ((st = c->alloc(&layout_buf, packed_bytes(c->layout, c->sn))) != SMC_OK) return bail(st);
-            scratch = layout_buf;
-        } else {
-            c->reserve(&scratch, scratch_bytes);
-        }
     } else if (src->fov) {
         c->src_ok = const_cast<uint8_t *>(src->fov);
     }
@@ -661,22 +659,21 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
 
     // prepared inputs
     if (!images) {
-        uint16_t *gap_x = (uint16_t *)scratch, *gap_y = (uint16_t *)(scratch + ds.gap_x);
         c->dice.bits = (const uint32_t *)bits;
         c->dice.field = field;
         c->dice.t4 = t4;
         c->dice.t8 = (const uint32_t *)t8;
         c->dice.t16 = (const uint32_t *)t16;
         if (launch_mask_source(src->data, src->fov, c->sn, c->src_prep, (uint32_t *)bits, c->stream) != hipSuccess ||
-            launch_field((const uint32_t *)bits, (const uint32_t *)bits, c->sn, gap_x, gap_y, field, c->stream) !=
+            launch_field((const uint32_t *)bits, (const uint32_t *)bits, c->sn, c->tgt_prep, field, c->stream) !=
                 hipSuccess ||
             launch_dice_target(tgt->data, tgt->fov, c->tn, c->tgt_prep, t4, (uint32_t *)t8, (uint32_t *)t16,
                                c->stream) != hipSuccess ||
             launch_fill_u64(c->work, kWorkSlots * kWorkSlotWords, c->stream) != hipSuccess)
             return bail(fail(SMC_EDEVICE, "mask preparation launch failed"));
     } else if (corners) {
+        if (!scratch) scratch = tz;
         uint32_t *may = (uint32_t *)scratch, *must = (uint32_t *)(scratch + ts.bits);
-        uint16_t *gap_x = (uint16_t *)(scratch + 2 * ts.bits), *gap_y = (uint16_t *)(scratch + 2 * ts.bits + ts.gap);
         c->tri.field = field;
         c->tri.tz = (const uint32_t *)tz;
         c->tri.fz = (const uint32_t *)fz;
@@ -684,7 +681,7 @@ smc_status smc_init(smc_ctx **out, const smc_volume *src, const smc_volume *tgt,
         c->tri.t8 = t8;
         c->tri.t16 = t16;
         if (launch_corner_valid(src->fov, c->sn, c->src_ok, may, must, c->stream) != hipSuccess ||
-            launch_field(may, must, c->sn, gap_x, gap_y, field, c->stream) != hipSuccess ||
+            launch_field(may, must, c->sn, scratch + 2 * ts.bits, field, c->stream) != hipSuccess ||
             launch_tri_target(tgt->data, tgt->fov, c->tn, (uint32_t *)tz, (uint32_t *)fz, t4, t8, t16, c->stream) !=
                 hipSuccess)
             return bail(fail(SMC_EDEVICE, "image preparation launch failed"));

@@ -399,12 +399,36 @@ __global__ __launch_bounds__(kThreads) void k_batch_dice(const Args *pairs_g, co
 // The field, one axis at a time.  Gaps are whole voxels between two voxels'
 // boxes, 0 where they touch; kWindow and more read as kWindow, and squared
 // distances saturate at 255 (both lower bounds).  Voxels outside the source
-// are off.  Byte pairs hold the distances to the nearest voxel that may be on
-// (low) and that may be off (high).
-//
+// are off.  Of a voxel's distances to the nearest voxel that may be on and to
+// that may be off one is 0, so a byte holds both: the distance, and in bit 7
+// that it is the one to off.  (Two bytes a voxel took as long, and twice
+// the memory between the passes.)
+constexpr uint32_t kToOff = 128u;
+
+// The squared distances within a slice are sums of two squares: 97 values below
+// 255.  Their numbers, and per byte the distances to on (low) and off (high).
+struct SquareCodes {
+    uint8_t number[256] = {};
+    uint32_t pair[256] = {};
+    constexpr SquareCodes() {
+        uint32_t count = 0;
+        for (uint32_t d = 0; d < 256; ++d) {
+            bool sum = d == 255;  // (255 and more)
+            for (uint32_t a = 0; a <= kWindow && !sum; ++a)
+                for (uint32_t b = 0; b <= kWindow && !sum; ++b) sum = a * a + b * b == d;
+            if (!sum) continue;
+            number[d] = (uint8_t)count;
+            pair[count] = d;
+            pair[count | kToOff] = d << 16;
+            ++count;
+        }
+    }
+};
+__device__ const SquareCodes kSquareCodes{};
+
 // x: gaps along the rows, four voxels a thread.
 __global__ __launch_bounds__(256) void k_field_x(const uint32_t *may, const uint32_t *must, int32_t nx, uint32_t ny,
-                                                 uint32_t rows, uint32_t W, uint16_t *out) {
+                                                 uint32_t rows, uint32_t W, uint8_t *out) {
     const uint32_t quads = (uint32_t)(nx + 3) / 4, n = quads * rows;
     for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
         const uint32_t row = q / quads, z = row / ny;
@@ -427,8 +451,17 @@ __global__ __launch_bounds__(256) void k_field_x(const uint32_t *may, const uint
             const uint32_t gr = rt ? (uint32_t)__ffs(rt) - 1u : (uint32_t)kWindow;
             return min(gl, gr);
         };
-        for (int j = 0; j < 4 && xa + j < nx; ++j)
-            out[row * (uint32_t)nx + xa + j] = (uint16_t)(gap(on >> j) | (gap(off >> j) << 8));
+        uint32_t v = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t to_on = gap(on >> j);
+            v |= (to_on ? to_on : gap(off >> j) | kToOff) << (8 * j);
+        }
+        uint8_t *o = out + row * (uint32_t)nx + xa;
+        if (xa + 4 <= nx)
+            __builtin_memcpy(o, &v, 4);
+        else
+            for (int j = 0; xa + j < nx; ++j) o[j] = (uint8_t)(v >> (8 * j));
     }
 }
 
@@ -450,8 +483,11 @@ __device__ __forceinline__ u16x2 envelope(const u16x2 *v) {
 }
 
 // y: squared distances within a slice.
-__global__ __launch_bounds__(256) void k_field_y(const uint16_t *gx, int32_t nx, int32_t ny, int32_t nz,
-                                                 uint16_t *out) {
+__global__ __launch_bounds__(256) void k_field_y(const uint8_t *gx, int32_t nx, int32_t ny, int32_t nz,
+                                                 uint8_t *out) {
+    __shared__ uint8_t number[256];
+    number[threadIdx.x] = kSquareCodes.number[threadIdx.x];
+    __syncthreads();
     const uint32_t strips = (uint32_t)(ny + kStrip - 1) / kStrip, n = (uint32_t)nx * strips * (uint32_t)nz;
     for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
         const uint32_t t = q / (uint32_t)nx, z = t / strips;
@@ -462,22 +498,25 @@ __global__ __launch_bounds__(256) void k_field_y(const uint16_t *gx, int32_t nx,
         for (int e = 0; e < kStrip + 2 * kWindow; ++e) {
             const int32_t y = y0 + e - kWindow;
             const uint32_t g = y >= 0 && y < ny ? gx[line + (uint32_t)(nx * y)] : (uint32_t)kWindow;  // outside: off
-            const u16x2 p = {(uint16_t)(g & 255u), (uint16_t)(g >> 8)};
-            v[e] = p * p;
+            const uint16_t d = (uint16_t)((g & 127u) * (g & 127u));
+            v[e] = g & kToOff ? u16x2{0, d} : u16x2{d, 0};
         }
 #pragma unroll
         for (int j = 0; j < kStrip; ++j) {
             if (y0 + j >= ny) break;
             const u16x2 m = envelope(v + j);
-            out[line + (uint32_t)(nx * (y0 + j))] =
-                (uint16_t)(min((uint32_t)m.x, 255u) | (min((uint32_t)m.y, 255u) << 8));
+            const uint32_t code = number[min((uint32_t)max(m.x, m.y), 255u)];
+            out[line + (uint32_t)(nx * (y0 + j))] = (uint8_t)(m.x ? code : code | kToOff);
         }
     }
 }
 
 // z, and the field byte: 0 where a voxel of the other state touches (always
 // sampled).
-__global__ __launch_bounds__(256) void k_field_z(const uint16_t *gy, uint32_t plane, int32_t nz, uint8_t *out) {
+__global__ __launch_bounds__(256) void k_field_z(const uint8_t *gy, uint32_t plane, int32_t nz, uint8_t *out) {
+    __shared__ uint32_t pair[256];
+    pair[threadIdx.x] = kSquareCodes.pair[threadIdx.x];
+    __syncthreads();
     const uint32_t strips = (uint32_t)(nz + kStrip - 1) / kStrip, n = plane * strips;
     for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < n; q += gridDim.x * 256u) {
         const uint32_t t = q / plane;
@@ -487,8 +526,8 @@ __global__ __launch_bounds__(256) void k_field_z(const uint16_t *gy, uint32_t pl
 #pragma unroll
         for (int e = 0; e < kStrip + 2 * kWindow; ++e) {
             const int32_t z = z0 + e - kWindow;
-            const uint32_t g = z >= 0 && z < nz ? gy[line + plane * (uint32_t)z] : 255u;  // outside: off
-            v[e] = u16x2{(uint16_t)(g & 255u), (uint16_t)(g >> 8)};
+            v[e] = u16x2{255, 0};  // outside: off
+            if (z >= 0 && z < nz) v[e] = __builtin_bit_cast(u16x2, pair[gy[line + plane * (uint32_t)z]]);
         }
 #pragma unroll
         for (int j = 0; j < kStrip; ++j) {
@@ -628,7 +667,6 @@ DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]) {
     const uint64_t n = (uint64_t)sn[0] * sn[1] * sn[2];
     s.bits = 4ull * cells(sn[0], 32) * (uint64_t)sn[1] * (uint64_t)sn[2];
     s.field = n;
-    s.gap_x = s.gap_y = 2ull * n;
     const auto grid = [&](int32_t side) {
         return (uint64_t)cells(tn[0], side) * cells(tn[1], side) * cells(tn[2], side);
     };
@@ -638,15 +676,15 @@ DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]) {
     return s;
 }
 
-hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint16_t *gap_x, uint16_t *gap_y,
-                        uint8_t *field, hipStream_t s) {
+hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint8_t *gaps, uint8_t *field,
+                        hipStream_t s) {
     const int64_t rows = (int64_t)n[1] * n[2], plane = (int64_t)n[0] * n[1];
     hipLaunchKernelGGL(k_field_x, dim3(blocks_for((n[0] + 3) / 4 * rows)), dim3(256), 0, s, may, must, n[0],
-                       (uint32_t)n[1], (uint32_t)rows, cells(n[0], 32), gap_x);
+                       (uint32_t)n[1], (uint32_t)rows, cells(n[0], 32), field);
     hipLaunchKernelGGL(k_field_y, dim3(blocks_for(((int64_t)n[1] + kStrip - 1) / kStrip * n[0] * n[2])), dim3(256), 0, s,
-                       (const uint16_t *)gap_x, n[0], n[1], n[2], gap_y);
+                       (const uint8_t *)field, n[0], n[1], n[2], gaps);
     hipLaunchKernelGGL(k_field_z, dim3(blocks_for(((int64_t)n[2] + kStrip - 1) / kStrip * plane)), dim3(256), 0, s,
-                       (const uint16_t *)gap_y, (uint32_t)plane, n[2], field);
+                       (const uint8_t *)gaps, (uint32_t)plane, n[2], field);
     return hipGetLastError();
 }
 

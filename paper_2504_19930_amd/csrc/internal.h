@@ -218,16 +218,15 @@ hipError_t launch_mask_source(const uint8_t *vol, const uint8_t *fov, const int3
 hipError_t launch_corner_valid(const uint8_t *fov, const int32_t n[3], uint8_t *out, uint32_t *may, uint32_t *must,
                                hipStream_t s);
 constexpr uint32_t kWorkSlots = 64, kWorkSlotWords = 16;
-// Device bytes of the structures of the filter's mask launches (dice.hip);
-// gap_x and gap_y are scratch of launch_field.
+// Device bytes of the structures of the filter's mask launches (dice.hip).
 struct DiceSizes {
-    uint64_t bits, field, gap_x, gap_y, t4, t8, t16;
+    uint64_t bits, field, t4, t8, t16;
 };
 DiceSizes dice_sizes(const int32_t sn[3], const int32_t tn[3]);
 // Distance field of a source from bitmaps of the voxels that may be on and that
-// certainly are.
-hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint16_t *gap_x, uint16_t *gap_y,
-                        uint8_t *field, hipStream_t s);
+// certainly are; gaps is scratch, a byte a voxel.
+hipError_t launch_field(const uint32_t *may, const uint32_t *must, const int32_t n[3], uint8_t *gaps, uint8_t *field,
+                        hipStream_t s);
 hipError_t launch_dice_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint8_t *prep, void *t4,
                               uint32_t *t8, uint32_t *t16, hipStream_t s);
 hipError_t launch_dice(const ScoreLaunch &L, hipStream_t s);
@@ -240,9 +239,9 @@ uint64_t dice_args(const ScoreLaunch &L, void *out);
 hipError_t launch_batch_dice(const void *pairs, const uint32_t *offs, const uint32_t *kmax, uint32_t n_pairs,
                              uint32_t groups, uint32_t k, hipStream_t s);
 // The same for trilinear images with a source FOV (tri.hip); may, must
-// (bits bytes each), gap_x and gap_y (gap bytes each) are scratch.
+// (bits bytes each) are scratch.
 struct TriSizes {
-    uint64_t bits, field, gap, tz, t4, t8, t16;
+    uint64_t bits, field, tz, t4, t8, t16;
 };
 TriSizes tri_sizes(const int32_t sn[3], const int32_t tn[3]);
 hipError_t launch_tri_target(const uint8_t *vol, const uint8_t *fov, const int32_t n[3], uint32_t *tz, uint32_t *fz,

@@ -842,7 +842,6 @@ TriSizes tri_sizes(const int32_t sn[3], const int32_t tn[3]) {
     const uint64_t n = (uint64_t)sn[0] * sn[1] * sn[2];
     s.bits = 4ull * cells(sn[0], 32) * (uint64_t)sn[1] * (uint64_t)sn[2];
     s.field = n;
-    s.gap = 2ull * n;
     s.tz = 4ull * (uint64_t)tn[0] * tn[1] * cells(tn[2], 4);
     s.t4 = 8ull * cells(tn[0], 4) * cells(tn[1], 4) * cells(tn[2], 4);
     s.t8 = 16ull * cells(tn[0], 8) * cells(tn[1], 8) * cells(tn[2], 8);
