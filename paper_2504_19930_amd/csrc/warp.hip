@@ -72,7 +72,7 @@ struct WArgs {
     int32_t sn0, sn1, sn2, tn0, tn1, tn2;
     int64_t src_stride, dst_stride;
     int32_t xblocks, bxy, zchunks, zc;  // tiles per row and per slab, slabs per frame, slices per tile
-    uint32_t total, first;              // workgroups; those of this grid begin at first
+    uint32_t total;                     // workgroups
     uint32_t frames, fg;                // frames; frames per workgroup (groups of fg)
     // staged kernel: per source axis sum_e |w_de| (T_e - 1) over a tile's
     // extents T; LDS row pitch, rows per LDS slice, slice pitch
@@ -84,10 +84,14 @@ struct WTile {
     int x0, y0, k0, k1, frame;  // frame: the group of frames fg * frame .. fg * frame + fg - 1
 };
 
-// Tile of this workgroup: the (x-block, row block, slab, frame group) order
+// Workgroups in rows of kMaxGridGroups (a grid counts the threads of a dimension in
+// 32 bits); those past the last one have nothing to do.
+__device__ __forceinline__ uint32_t warp_group() { return blockIdx.y * (uint32_t)kMaxGridGroups + blockIdx.x; }
+
+// Tile of workgroup b: the (x-block, row block, slab, frame group) order
 // split into eight contiguous runs, run r on XCD r.
-__device__ __forceinline__ WTile warp_tile(const WArgs &a) {
-    const uint32_t T = a.total, b = a.first + blockIdx.x, xcd = b % 8u, kk = b / 8u, q = T / 8u, r = T % 8u;
+__device__ __forceinline__ WTile warp_tile(const WArgs &a, uint32_t b) {
+    const uint32_t T = a.total, xcd = b % 8u, kk = b / 8u, q = T / 8u, r = T % 8u;
     const uint32_t lin = (xcd < r ? xcd * (q + 1u) : r * (q + 1u) + (xcd - r) * q) + kk;
     const uint32_t per_frame = (uint32_t)a.bxy * (uint32_t)a.zchunks;
     WTile t;
@@ -148,7 +152,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ZC == 16 ? 
 void k_warp_trilinear_lds(const WArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     __shared__ __attribute__((aligned(16))) uint8_t tile[ZC * kWY * kWX];
-    const WTile t = warp_tile(a);
+    if (warp_group() >= a.total) return;
+    const WTile t = warp_tile(a, warp_group());
     const uint32_t sn0 = (uint32_t)a.sn0, sn01 = (uint32_t)a.sn0 * (uint32_t)a.sn1;
     const uint32_t nbytes = sn01 * (uint32_t)a.sn2;
 
@@ -292,7 +297,8 @@ void k_warp_trilinear_lds(const WArgs a) {
 template <int ZC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_warp_nearest(const WArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[2][ZC * kWY * kWX];
-    const WTile t = warp_tile(a);
+    if (warp_group() >= a.total) return;
+    const WTile t = warp_tile(a, warp_group());
     int i, j;
     warp_column(t, i, j);
     const uint32_t sn0 = (uint32_t)a.sn0, sn01 = (uint32_t)a.sn0 * (uint32_t)a.sn1;
@@ -344,7 +350,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
 // gather from the source frame.
 __global__ __launch_bounds__(256) void k_warp_trilinear(const WArgs a) {
     constexpr int kZU = 4;  // slices per batch of loads (eight taps each)
-    const WTile t = warp_tile(a);
+    if (warp_group() >= a.total) return;
+    const WTile t = warp_tile(a, warp_group());
     int i, j;
     warp_column(t, i, j);
     if (i >= a.tn0 || j >= a.tn1) return;
@@ -451,6 +458,10 @@ void spread(WArgs &a, F fits) {
     while (a.zc > 4 && groups() < kFillGroups && fits(a.zc / 2)) a.zc /= 2;
 }
 
+dim3 grid_of(uint64_t total) {
+    return dim3((unsigned)std::min(total, kMaxGridGroups), (unsigned)((total + kMaxGridGroups - 1) / kMaxGridGroups));
+}
+
 }  // namespace
 
 hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const float w[12], bool trilinear,
@@ -479,13 +490,13 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
         spread(a, [](int) { return true; });
         a.zchunks = (tn[2] + a.zc - 1) / a.zc;
         const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
+        if (total > kMaxScoreItems) return hipErrorInvalidConfiguration;
         a.total = (uint32_t)total;
-        return launch_groups(total, [&](uint32_t first, dim3 grid) {
-            a.first = first;
-            if (a.zc == 16) hipLaunchKernelGGL(k_warp_nearest<16>, grid, block, 0, s, a);
-            else if (a.zc == 8) hipLaunchKernelGGL(k_warp_nearest<8>, grid, block, 0, s, a);
-            else hipLaunchKernelGGL(k_warp_nearest<4>, grid, block, 0, s, a);
-        });
+        const dim3 grid = grid_of(total);
+        if (a.zc == 16) hipLaunchKernelGGL(k_warp_nearest<16>, grid, block, 0, s, a);
+        else if (a.zc == 8) hipLaunchKernelGGL(k_warp_nearest<8>, grid, block, 0, s, a);
+        else hipLaunchKernelGGL(k_warp_nearest<4>, grid, block, 0, s, a);
+        return hipGetLastError();
     }
 
     // staged trilinear: at least 16 bytes of source, every partial sum of the
@@ -521,14 +532,14 @@ hipError_t launch_warp_apply(const uint8_t *src, const int32_t sn[3], const floa
     }
     a.zchunks = (tn[2] + a.zc - 1) / a.zc;
     const uint64_t total = (uint64_t)a.bxy * (uint64_t)a.zchunks * ((frames + a.fg - 1) / a.fg);
+    if (total > kMaxScoreItems) return hipErrorInvalidConfiguration;
     a.total = (uint32_t)total;
-    return launch_groups(total, [&](uint32_t first, dim3 grid) {
-        a.first = first;
-        if (!staged) hipLaunchKernelGGL(k_warp_trilinear, grid, block, 0, s, a);
-        else if (a.zc == 16) hipLaunchKernelGGL(k_warp_trilinear_lds<16>, grid, block, bytes, s, a);
-        else if (a.zc == 8) hipLaunchKernelGGL(k_warp_trilinear_lds<8>, grid, block, bytes, s, a);
-        else hipLaunchKernelGGL(k_warp_trilinear_lds<4>, grid, block, bytes, s, a);
-    });
+    const dim3 grid = grid_of(total);
+    if (!staged) hipLaunchKernelGGL(k_warp_trilinear, grid, block, 0, s, a);
+    else if (a.zc == 16) hipLaunchKernelGGL(k_warp_trilinear_lds<16>, grid, block, bytes, s, a);
+    else if (a.zc == 8) hipLaunchKernelGGL(k_warp_trilinear_lds<8>, grid, block, bytes, s, a);
+    else hipLaunchKernelGGL(k_warp_trilinear_lds<4>, grid, block, bytes, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace smc
