@@ -219,11 +219,14 @@ smc_status smc_set_frames(smc_ctx *ctx, uint32_t n_extra, const smc_volume *src_
  * layouts cost 2, 4, 8 or 16 bytes per source voxel of device memory,
  * prepared on the stream.  particles_per_group: particles sharing one pass
  * over a target column, 4, 8 or 16.  tile_depth: target
- * slices per tile, 1 .. 256 (a tile is 32 x 8 x tile_depth voxels; shallower
- * tiles cull more exactly -- a tile whose image cannot reach the source is
- * skipped -- at the cost of more partial sums).  The filter's mask launches
- * and, on sources with a FOV, the layouts of one gather (3, 4 and 5) use
- * neither: they decide blocks of the target by a distance field of the source.  A negative value keeps the current setting.  Defaults
+ * slices per tile at most, 1 .. 256 (a tile is 32 x 8 x tile_depth voxels;
+ * shallower tiles cull more exactly -- a tile whose image cannot reach the source is
+ * skipped -- at the cost of more partial sums; a launch of fewer than 384 tiles
+ * times groups takes shallower ones, down to 4 slices, to fill the device).  The
+ * filter's mask launches and, on sources with a FOV that leaves enough to skip
+ * (mutual information: any FOV), the layouts of one gather (3, 4 and 5) use neither:
+ * they decide blocks of the target by a distance field of the source.  A
+ * negative value keeps the current setting.  Defaults
  * come from measurements on MI355X: 4 particles per group; tile depth 16 for
  * masks and 256 for images.  A packed layout addresses its source
  * with 32-bit offsets: SMC_EINVAL if the packed source reaches 4 GiB or one

@@ -6,7 +6,7 @@
 // whole block of target voxels whether every sample of it is valid (inside the
 // source and its FOV) or none is: blocks of 16^3, then 8^3, then 4^3.  Blocks
 // without a valid sample are skipped -- with an apical cone two fifths of the
-// pairs -- and blocks with nothing but valid samples drop the per-sample tests:
+// pairs; FOVs that leave little to skip go by tiles, see tri_pays -- and blocks with nothing but valid samples drop the per-sample tests:
 // three compares, a select, the sentinel and the lane mask, and the sums n, t
 // and t^2, which are the target block's own.
 //
@@ -29,9 +29,9 @@
 // elements, concentrated cloud): 5.98 ms a launch over whole tiles with every
 // sample tested, 4.69 with blocks down to 8^3, 4.55 with each load issued as its
 // offset is known, 4.37 with 4^3 blocks.  A whole registration 193 -> 141 ms; 16
-// uneven pairs 33.6 -> 25.9 ms.  Bound: the texture path (busy 96 %, about 28
-// clocks a wave's 16-byte gather, 25 cache-line accesses) with VALU issue close
-// behind (1.05 instructions a CU and clock, 26.4 for a plain sample).  More waves
+// uneven pairs 33.6 -> 25.9 ms.  Bound: the texture path (TD 97 %, TA 90 % busy,
+// about 28 clocks a wave's 16-byte gather, 30 cache accesses a wave's load) with VALU
+// issue close behind (0.97 instructions a CU and clock, 29.5 a load).  More waves
 // (one slice at a time, 95 registers, five waves a SIMD) ran 2 to 9 % slower:
 // their gathers evict each other's lines.
 #include <math.h>

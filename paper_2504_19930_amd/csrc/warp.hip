@@ -23,9 +23,10 @@
 // touches, four to eight lines under rotation).  Tiles are 16 slices deep, or 8
 // or 4 where the box of a deeper one is too large (rotations by more than some
 // 20 and 35 degrees).  Trilinear, direct: one workgroup per tile and frame, every
-// tap a byte gather; the host takes it when no box fits (strong magnification of
-// the target) or coordinates reach 2^20 (where the margin would no longer cover
-// FP32 rounding).
+// tap a byte gather; the host takes it when no box fits (with equal spacings one
+// in twenty rotations by 45 degrees, a third by 60, half by 70 to 80 and 120; a
+// magnified target) or coordinates reach 2^20 (where the margin would no longer
+// cover FP32 rounding).
 //
 // The 16-byte accesses take any address, so odd sizes and views go the same way:
 // trilinear 7 frames of 97 x 150 x 203, 20 degrees, 148 us with byte gathers,
