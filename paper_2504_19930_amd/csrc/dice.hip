@@ -28,7 +28,7 @@
 // 4^3 by a field of 2^3-voxel cells and 19 VALU instructions a gather; 26.7 ms
 // with the block list in floats, a byte of target bits a lane and eighths of a
 // voxel (15); 24.0 ms with the field at voxels.  Bound: the texture path (TD 96 %,
-// TA 94 % busy; 16.1 VALU instructions a wave's load, 0.89 a CU and clock); six to
+// TA 94 % busy; 16 VALU instructions a wave's load, 0.89 a CU and clock); six to
 // eight waves a SIMD (fewer registers) ran no faster than five.
 //
 // Every mask goes this way.  Off the usual, a registration of 128 x 120 x 110 masks
@@ -408,8 +408,9 @@ __global__ __launch_bounds__(kThreads) void k_batch_dice(const Args *pairs_g, co
 // distances saturate at 255 (both lower bounds).  Voxels outside the source
 // are off.  Of a voxel's distances to the nearest voxel that may be on and to
 // that may be off one is 0, so a byte holds both: the distance, and in bit 7
-// that it is the one to off.  (Two bytes a voxel took as long, and twice
-// the memory between the passes.)
+// that it is the one to off.  Passes of 8.2 M voxels 15, 25 and 46 us; with two
+// bytes a voxel 17, 26 and 29, and four times the memory between them, which each
+// context then held or paid 80 us to give back.
 constexpr uint32_t kToOff = 128u;
 
 // The squared distances within a slice are sums of two squares: 97 values below

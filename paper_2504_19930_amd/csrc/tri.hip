@@ -31,7 +31,7 @@
 // offset is known, 4.37 with 4^3 blocks.  A whole registration 193 -> 141 ms; 16
 // uneven pairs 33.6 -> 25.9 ms.  Bound: the texture path (TD 97 %, TA 90 % busy,
 // about 28 clocks a wave's 16-byte gather, 30 cache accesses a wave's load) with VALU
-// issue close behind (0.97 instructions a CU and clock, 29.5 a load).  More waves
+// issue close behind (0.98 instructions a CU and clock, 30 a load).  More waves
 // (one slice at a time, 95 registers, five waves a SIMD) ran 2 to 9 % slower:
 // their gathers evict each other's lines.
 #include <math.h>
